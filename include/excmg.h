@@ -78,11 +78,18 @@ extern "C" {
  * reduction, which makes an iteration one kernel launch instead of two; it keeps s = M p and w = M r and moves 80
  * bytes per unknown and iteration instead of 64.  With this flag every grid runs the two-pass CG as written. */
 #define EXCMG_TWO_PASS_CG 256u
+/* Grids above 2^21 unknowns (in FP64, and in FP32 under EXCMG_FP32_IR) run the CG in pairs of iterations, in two sweeps
+ * a pair: the first forms M p and M (M p) and sums the products from which the second iteration's coefficients follow,
+ * the second makes both iterations.  The same iterates up to rounding and the same iteration counts (a pair stops
+ * after its first iteration where that one converges or reaches the cap), at half the bytes of two sweeps an iteration.
+ * EXCMG_TWO_PASS_CG turns this off too. */
 
 #define EXCMG_MAX_LEVELS 16
 #define EXCMG_MAX_HISTORY 256
 
 /* Kernel classes reported by EXCMG_WANT_TIMING. */
+/* (the CG classes: the first and second sweep of an iteration, or of a pair of iterations; kernel_calls counts
+ * iterations in both, kernel_ms all the sweeps' time) */
 #define EXCMG_K_CG_A 0      /* p = r + beta p; partial sums of p.Mp                          (FP64) */
 #define EXCMG_K_CG_B 1      /* u += alpha p; r -= alpha Mp; partial sums of r.r              (FP64) */
 #define EXCMG_K_CG_A32 2    /* the same two passes in FP32 (inner solves of EXCMG_FP32_IR) */
@@ -96,7 +103,8 @@ extern "C" {
 #define EXCMG_K_GRADIENT 10
 #define EXCMG_K_OTHER 11
 #define EXCMG_K_CG_A0 12     /* the FP64 passes of a grid's first CG iteration, where p = r: pass A reads r and */
-#define EXCMG_K_CG_B0 13     /* writes no p, pass B reads r once for both operands (EXCMG_K_CG_A/B: the others) */
+#define EXCMG_K_CG_B0 13     /* writes no p, pass B reads r once for both operands (EXCMG_K_CG_A/B: the others);
+                                the first pair's sweeps, counted once, where iterations run in pairs */
 #define EXCMG_K_CLASSES 14
 
 typedef struct excmg_handle excmg_handle;
@@ -143,7 +151,7 @@ typedef struct {
   double ms_total;                           /* wall time of the call, ms */
   double kernel_ms[EXCMG_K_CLASSES];         /* EXCMG_WANT_TIMING: summed kernel time per class on the finest
                                                 grid, ms (CG launches made after it converged are not counted) */
-  int32_t kernel_calls[EXCMG_K_CLASSES];     /* EXCMG_WANT_TIMING: launches per class */
+  int32_t kernel_calls[EXCMG_K_CLASSES];     /* EXCMG_WANT_TIMING: launches per class (CG classes: iterations) */
   double kernel_ms_finest[EXCMG_K_CLASSES];  /* the same, finest grid only */
   int32_t kernel_calls_finest[EXCMG_K_CLASSES];
   int32_t history_len;                       /* EXCMG_WANT_HISTORY: entries in history */
@@ -162,7 +170,8 @@ int excmg_plan(const excmg_problem *p, int32_t *levels, int32_t n_coarse_out[3])
 int excmg_setup(const excmg_problem *p, void *workspace, size_t bytes, void *hip_stream, excmg_handle **h);
 
 /* Algorithm 1.  f: node array (every node is read); g: node array (only boundary nodes are read).
- * u (out): node array, the finest-grid solution with its boundary equal to g.
+ * u (out): node array, the finest-grid solution with its boundary equal to g (its contents change during the call:
+ * the relaxation keeps a work vector there; after an error other than EXCMG_ERR_NOCONV they are undefined).
  * u_ext (out, nullable): EXP_true(u_h, u_2h), the sixth-order extrapolated solution on the finest grid
  * (Algorithm 1, optional step; Sections 4.2.1 and 4.3); needs at least two grids.
  * stats (host, nullable). */
@@ -193,7 +202,7 @@ int excmg_gradient(excmg_handle *h, const double *u, double *ux, double *uy, dou
  * upstream gradient G = dL/du (node array).  Solves M lambda = G_I (M = -A_h restricted to the interior, the same
  * symmetric operator) by the same cascade with the level data taken from G, then
  *   dLdf = -R^T lambda on every node (R f = (6 f_c + sum of the 6 face neighbours)/2, eq. compact),
- *   dLdg = A_IB^T lambda + G on boundary nodes, 0 inside.
+ *   dLdg = A_IB^T lambda + G on boundary nodes, 0 inside (dLdf or dLdg serves as a work vector during the call).
  * lambda_out (nullable): lambda as a node array with zero boundary.  Uses the handle's tolerance and precision. */
 int excmg_adjoint(excmg_handle *h, const double *G, double *dLdf, double *dLdg, double *lambda_out,
                   excmg_stats *stats);
@@ -261,7 +270,9 @@ int excmg_autotune(excmg_handle *h, int32_t *zc_out, int32_t *depth_out);
 
 /* Sweep shapes (host calls).  A sweep of grid `level` (0 = coarsest) of kind EXCMG_SWEEP_*: the CG passes A and B in
  * FP64, in FP32 (EXCMG_FP32_IR), and the FP64 passes of a grid's first iteration (used on grids whose passes do not
- * finalize their own reductions).  shape[4] (host) = {z chunk in planes (even, 2..4096), prefetch depth (2, 3, 4 or
+ * finalize their own reductions, and on the finest grid where iterations run in pairs).  Grids that run iterations in
+ * pairs take the passes' shapes for the pair's two sweeps, whose tiles have 4, 12 or 13 rows for heights 4, 8 and 16
+ * and which prefetch one to three planes.  shape[4] (host) = {z chunk in planes (even, 2..4096), prefetch depth (2, 3, 4 or
  * 6), non-temporal policy (0 or 1), tile height in rows of 64 nodes (4, 8 or 16)}.  excmg_get_sweep reads the shape
  * in use (the setup's default or the autotuner's choice); excmg_set_sweep replaces it for every later call on this
  * handle (so that a shape found by excmg_autotune can be saved and restored without tuning again, or a shape

@@ -1,0 +1,58 @@
+// Device helpers shared by the CG sweep kernels (kernels_cg.hip, kernels_two.hip).
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <type_traits>
+#include <utility>
+
+namespace excmg {
+
+namespace {
+
+constexpr int kXcds = 8;
+
+// Bijection from the hardware workgroup id to a logical tile id such that logical ids [x*per, (x+1)*per) run on XCD x.
+__device__ __forceinline__ int xcd_remap(int b, int nb) {
+  const int per = nb / kXcds, rem = nb % kXcds;
+  const int x = b % kXcds, l = b / kXcds;
+  const int start = (x < rem) ? x * (per + 1) : rem * (per + 1) + (x - rem) * per;
+  return start + l;
+}
+
+__device__ __forceinline__ double wave_sum(double v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+
+// Tile shape of the stencil sweeps (x is the fast axis: one wavefront covers one 64-node row segment).
+constexpr int TX = 64;
+__device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
+
+// Loads and stores of data a sweep touches once: non-temporal (streaming) when NTP, so that they do not displace the
+// operand's halo lines, which neighbouring tiles read again, from the caches.
+template <bool NTP, typename T>
+__device__ __forceinline__ T ld1(const T *p) {
+  if constexpr (NTP) return __builtin_nontemporal_load(p);
+  else return *p;
+}
+template <bool NTP, typename T>
+__device__ __forceinline__ void st1(T v, T *p) {
+  if constexpr (NTP) __builtin_nontemporal_store(v, p);
+  else *p = v;
+}
+
+// f(integral_constant<int, 0>), ..., f(integral_constant<int, N - 1>), in that order
+template <typename F, int... Q>
+__device__ __forceinline__ void static_for_impl(F &&f, std::integer_sequence<int, Q...>) {
+  (f(std::integral_constant<int, Q>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F &&f) {
+  static_for_impl(f, std::make_integer_sequence<int, N>{});
+}
+
+}  // namespace
+
+}  // namespace excmg

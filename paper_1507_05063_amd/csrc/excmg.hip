@@ -36,7 +36,8 @@ struct Level {
   Stencil st;
   Sweep sw, sw32;  // stencil sweeps over g and g32 (residual kernels)
   Sweep swA, swB, swA32, swB32;  // CG passes A and B in FP64 and FP32 (z chunk chosen by the autotuner)
-  Sweep swA0, swB0;  // the FP64 passes of a grid's first iteration (p = r), on grids whose passes finalize apart
+  Sweep swA0, swB0;  // the FP64 passes of a grid's first iterations (p = r), on grids launched without graphs
+  bool shaped;       // the CG passes' shapes were tuned or set (else batched solves take their own default)
   double *u;   // this grid's solution, all nodes (boundary = g)
 };
 
@@ -137,6 +138,13 @@ constexpr unsigned kTimingEvent = hipEventDisableSystemFence;
 // bytes of a CG state that the host reads after a solve (everything but the history)
 constexpr size_t kStateHead = offsetof(CgState, hist);
 
+// The two-step sweeps relax the grids above this size.  On smaller grids a step of the march, about 1.4 us whatever the grid, outweighs the bytes saved: at 127^3 unknowns a
+// pair takes 64 us, four self-finalizing sweeps 62 us.
+constexpr long long kTwoMinUnknowns = 1LL << 21;
+bool two_grid(const Level &lv, const excmg_problem &p) {
+  return !(p.flags & EXCMG_TWO_PASS_CG) && lv.g.interior() > kTwoMinUnknowns;
+}
+
 int make_layout(const excmg_problem *p, Layout *Lo) {
   int e = validate(p);
   if (e) return e;
@@ -159,9 +167,18 @@ int make_layout(const excmg_problem *p, Layout *Lo) {
     const bool big = lv.g.interior() >= (1LL << 23);
     lv.sw = make_sweep(lv.g, lv.st, big ? kResidChunk : 0, 2, big ? 1 : 0);
     lv.sw32 = make_sweep(lv.g32, lv.st, 0);
-    lv.swA = lv.swB = make_sweep(lv.g, lv.st, 0, 2, big ? 1 : 0);
-    lv.swA0 = lv.swB0 = lv.swA;
-    lv.swA32 = lv.swB32 = lv.sw32;
+    if (!two_grid(lv, *p)) {
+      lv.swA = lv.swB = make_sweep(lv.g, lv.st, 0, 2, big ? 1 : 0);
+      lv.swA32 = lv.swB32 = lv.sw32;
+    } else {
+      lv.swA = two_default(lv.g, lv.st, false, false, 0);
+      lv.swB = two_default(lv.g, lv.st, false, true, big ? 1 : 0);
+      lv.swA32 = two_default(lv.g32, lv.st, true, false, 0);
+      lv.swB32 = two_default(lv.g32, lv.st, true, true, big ? 1 : 0);
+    }
+    lv.swA0 = lv.swA;
+    lv.swB0 = lv.swB;
+    lv.shaped = false;
     lv.u = nullptr;
     Lo->off_u[l] = off;
     off = align256(off + (size_t)lv.g.elems * sizeof(double));
@@ -201,7 +218,7 @@ int make_layout(const excmg_problem *p, Layout *Lo) {
 struct TimedLaunch {
   int cls;
   int level;
-  int iter;  // CG iteration index of a CG-class launch (-1: always counted)
+  int iter;  // CG iteration index of a CG-class launch (-1: always counted), or the pair of a two-step one
   int outer; // FP32_IR outer step (-1 otherwise)
   hipEvent_t a, b;
 };
@@ -241,6 +258,11 @@ struct excmg_handle {
   // a handle of excmg_solve_noalloc: no events, graphs, capture stream or pinned memory; CG states are read back with
   // plain stream copies
   bool noalloc = false;
+  // the fourth vector of the finest grid's two-step FP64 sweeps: one of the current call's output arrays, which is
+  // written with its result only after the sweeps (null between calls, or where none can serve)
+  double *xfin = nullptr;
+  Grid gxfin = {};
+  int two_pairs = 0;  // pairs of the last two-step solve (kernel timing)
   // graphs of a batched round's CG iterations (excmg_solve_batched, on the batch's first handle), by launch shape
   struct BatchGraph {
     std::vector<long long> key;
@@ -362,9 +384,11 @@ int read_state(excmg_handle *h, CgState *dst, const CgState *src) {
 int read_hist(excmg_handle *h, CgState *dst, const CgState *src) { return read_record(h, dst, src, sizeof(CgState)); }
 
 // Per-level iteration counts of CG-class timed launches, to drop launches made after convergence.
+// (launches: the CG iterations, or the pairs where the two-step sweeps make them)
 struct LevelIters {
   int iters[EXCMG_MAX_LEVELS];
-  std::vector<int> inner[EXCMG_MAX_LEVELS];  // FP32_IR: inner iterations of each outer step
+  int launches[EXCMG_MAX_LEVELS];
+  std::vector<int> inner[EXCMG_MAX_LEVELS];  // FP32_IR: launches of each outer step's inner solve
 };
 
 // Iterations launched before the first look at the CG state, and at most per look: in a single solve (launched as
@@ -446,6 +470,81 @@ void launch_cg1_step(excmg_handle *h, int l, hipStream_t s, int par) {
                        sweep_blocks(lv.sw), grid_tol(h->p, l, h->lo.L), par ? pb : pa, s);
 }
 
+// The two-step sweeps (kernels_two.hip) relax the large grids (two_grid), unless EXCMG_TWO_PASS_CG asks for two
+// sweeps an iteration.  They need a fourth vector beside r, p0 and p1: below the finest it follows r in r's buffer (which holds
+// the finest grid); the FP32 refinement, which leaves the FP64 p0 idle, has it there; the finest FP64 grid takes an
+// output array of the call (bind_output).  Byte offsets in a plane are 32 bits.
+bool plane_fits(const Grid &g, size_t size) { return (unsigned long long)g.sz * size < (1ull << 32); }
+bool two_below(const Layout &lo, const Level &lv) { return cg1_stride(lv) + lv.g.elems <= lo.gfin.elems; }
+bool use_two(const excmg_handle *h, int l, int fp32) {
+  const Layout &lo = h->lo;
+  const Level &lv = lo.lev[l];
+  if (!two_grid(lv, h->p)) return false;
+  if (fp32) return plane_fits(lv.g32, sizeof(float));
+  if (!plane_fits(lv.g, sizeof(double))) return false;
+  if (l == lo.L - 1) return h->xfin != nullptr && plane_fits(h->gxfin, sizeof(double));
+  return two_below(lo, lv);
+}
+TwoVecs<double> two_vecs64(const excmg_handle *h, int l) {
+  const Level &lv = h->lo.lev[l];
+  if (l == h->lo.L - 1) return {lv.u, h->r, h->p0, h->p1, h->xfin, h->gxfin};
+  return {lv.u, h->r, h->p0, h->p1, h->r + cg1_stride(lv), lv.g};
+}
+TwoVecs<float> two_vecs32(const excmg_handle *h, int l) {
+  return {h->d32, h->r32, h->p32a, h->p32b, (float *)h->p0, h->lo.lev[l].g32};
+}
+
+// An output array of the call (a dense node array of the finest grid) as the finest grid's fourth vector: its
+// interior nodes packed in rows of the widest alignment that fits the array.  avoid: an input of the call that is read
+// after the sweeps (null: none); an output that overlaps it is not used.
+void bind_output(excmg_handle *h, double *out, const double *avoid) {
+  const Grid &d = h->lo.gdense;
+  const long long nodes = d.nodes();
+  if (!out || h->xfin) return;
+  if (avoid && out < avoid + nodes && avoid < out + nodes) return;
+  const long long lead = (long long)(((128 - ((uintptr_t)out & 127)) & 127) / sizeof(double));
+  for (int a = 16; a >= 1; a /= 2) {
+    Grid x;
+    x.nx = d.nx; x.ny = d.ny; x.nz = d.nz;
+    x.sy = (long long)(d.nx - 1 + a - 1) / a * a;
+    x.sz = x.sy * (d.ny - 1);
+    x.elems = x.sz * (d.nz - 1);
+    if (lead + x.elems > nodes) continue;
+    x.off = lead - 1 - x.sy - x.sz;  // node (1,1,1) is the first
+    h->xfin = out;
+    h->gxfin = x;
+    return;
+  }
+}
+// the binding lasts for the call
+struct OutputBinding {
+  excmg_handle *h;
+  ~OutputBinding() { h->xfin = nullptr; }
+};
+
+// Iterations 2 * pair and 2 * pair + 1 of grid l by the two-step sweeps.
+void launch_pair(excmg_handle *h, int l, int fp32, hipStream_t s, int pair, int outer) {
+  Level &lv = h->lo.lev[l];
+  if (fp32) {
+    const TwoVecs<float> v = two_vecs32(h, l);
+    {
+      Tick t(h, EXCMG_K_CG_A32, l, pair, outer);
+      launch_two_g<float>(lv.swA32, v, h->cs2, h->partials, s);
+    }
+    Tick t(h, EXCMG_K_CG_B32, l, pair, outer);
+    launch_two_u<float>(lv.swB32, v, h->cs2, h->partials, s);
+    return;
+  }
+  const TwoVecs<double> v = two_vecs64(h, l);
+  const bool first = pair == 0;  // (never in a graph)
+  {
+    Tick t(h, EXCMG_K_CG_A, l, pair);
+    launch_two_g<double>(first ? lv.swA0 : lv.swA, v, h->cs, h->partials, s);
+  }
+  Tick t(h, EXCMG_K_CG_B, l, pair);
+  launch_two_u<double>(first ? lv.swB0 : lv.swB, v, h->cs, h->partials, s);
+}
+
 // One CG iteration of grid l on stream s: FP64 (fp32 = 0) on u, r, p, or the FP32 inner solve (fp32 = 1) on d32, r32,
 // p32.  first: the first FP64 iteration of a self-finalizing grid, whose pass A sums the residual sweep's partials.
 // launched: iteration index for the kernel timing.
@@ -510,10 +609,14 @@ int launch_iteration_graph(excmg_handle *h, int l, int fp32, int si) {
   if (!ex) {
     hipGraph_t g = nullptr;
     HIPCHECK(hipStreamBeginCapture(h->cap, hipStreamCaptureModeThreadLocal));
-    // (the single-reduction CG: graphs start at odd iterations, after the first one's direct launch)
-    const bool cg1 = !fp32 && use_cg1(h, l);
+    // (the single-reduction CG: graphs start at odd iterations, after the first one's direct launch; the two-step
+    // sweeps: pairs, from the first on, in the shapes of the later ones)
+    const bool two = use_two(h, l, fp32);
+    const bool cg1 = !two && !fp32 && use_cg1(h, l);
     for (int q = 0; q < kGraphSizes[si]; ++q) {
-      if (cg1) launch_cg1_step(h, l, h->cap, (1 + q) & 1);
+      if (two) {
+        if (q % 2 == 0) launch_pair(h, l, fp32, h->cap, -1, -1);
+      } else if (cg1) launch_cg1_step(h, l, h->cap, (1 + q) & 1);
       else launch_iteration(h, l, fp32, false, h->cap, -1, -1);
     }
     const hipError_t ec = hipStreamEndCapture(h->cap, &g);
@@ -534,7 +637,12 @@ int launch_iteration_graph(excmg_handle *h, int l, int fp32, int si) {
 // the new launched count.
 int launch_iterations(excmg_handle *h, int l, int fp32, int nb, int launched, int outer, int *err) {
   *err = EXCMG_OK;
-  const bool selfred64 = !fp32 && self_finalizing(h->lo.lev[l], false);
+  const bool two = use_two(h, l, fp32);
+  if (two && !use_graphs(h, l)) {
+    for (int q = 0; q < nb; q += 2, launched += 2) launch_pair(h, l, fp32, h->stream, launched / 2, outer);
+    return launched;
+  }
+  const bool selfred64 = !two && !fp32 && self_finalizing(h->lo.lev[l], false);
   if (!use_graphs(h, l)) {
     for (int q = 0; q < nb; ++q, ++launched)
       launch_iteration(h, l, fp32, selfred64 && launched == 0, h->stream, launched, outer);
@@ -572,11 +680,12 @@ int cg64(excmg_handle *h, int l, const RhsSrc &rs, bool finest, int *iters, doub
   const hipStream_t s = h->stream;
   const int hist_on = (finest && st && (h->p.flags & EXCMG_WANT_HISTORY)) ? 1 : 0;
   const int maxit = grid_cap(h, l);
-  const bool selfred = self_finalizing(lv, false);
+  const bool two = use_two(h, l, 0);
+  const bool selfred = !two && self_finalizing(lv, false);
   double *partsB = h->partials + h->lo.npart;
   {
     Tick t(h, EXCMG_K_RESID, l);
-    if (use_cg1(h, l)) {  // r, then w = M r with the partials of the first iteration's two inner products
+    if (!two && use_cg1(h, l)) {  // r, then w = M r with the partials of the first iteration's two inner products
       launch_residual_partials(lv.sw, lv.u, rs, h->r, cg1_resid_parts(h), s);
       launch_selfred_init(h->cs, maxit, hist_on, 0, s);
       launch_cg1_init(cg1_sweep(lv), cg1_vec(h, lv, 0, 0), cg1_vec(h, lv, 0, 1), partsB, s);
@@ -602,6 +711,7 @@ int cg64(excmg_handle *h, int l, const RhsSrc &rs, bool finest, int *iters, doub
     nb = next_batch(hs.rho, hs.rho0, hs.iter, hs.stop2, kSolveFirst, kSolveMax);
   }
   *iters = hs.iter;
+  h->two_pairs = two ? hs.pairs : 0;
   *relres = hs.bnorm2 > 0.0 ? sqrt(hs.rho / hs.bnorm2) : 0.0;
   if (!isfinite(hs.bnorm2)) return EXCMG_ERR_NONFINITE;
   if (hist_on) {
@@ -654,7 +764,7 @@ int cg_ir(excmg_handle *h, int l, const RhsSrc &rs, bool finest, int *iters, int
       nb = next_batch(hi.rho, hi.rho0, hi.iter, hi.stop2, kSolveFirst, kSolveMax);
     }
     total += hi.iter;
-    if (inner_counts) inner_counts->push_back(hi.iter);
+    if (inner_counts) inner_counts->push_back(use_two(h, l, 1) ? hi.pairs : hi.iter);
     if (hi.status == EXCMG_ERR_BREAKDOWN) return EXCMG_ERR_BREAKDOWN;
     {
       Tick t(h, EXCMG_K_OTHER, l);
@@ -747,7 +857,7 @@ int collect_timing(excmg_handle *h, excmg_stats *st, const LevelIters &li) {
         const std::vector<int> &v = li.inner[t.level];
         limit = (t.outer < (int)v.size()) ? v[t.outer] : 0;
       } else {
-        limit = li.iters[t.level];
+        limit = li.launches[t.level];
       }
       if (t.iter >= limit) continue;
     }
@@ -764,6 +874,13 @@ int collect_timing(excmg_handle *h, excmg_stats *st, const LevelIters &li) {
       st->kernel_calls_finest[cls] += 1;
     }
   }
+  // the CG classes count iterations: a two-step launch of the later pairs makes up to two (the first pair's class one)
+  auto count = [&](int a, int b, int n) {
+    st->kernel_calls[a] = st->kernel_calls[b] = st->kernel_calls_finest[a] = st->kernel_calls_finest[b] = n;
+  };
+  const int Lv = h->lo.L - 1;
+  if (h->two_pairs > 0) count(EXCMG_K_CG_A, EXCMG_K_CG_B, li.iters[Lv] > 0 ? li.iters[Lv] - 1 : 0);
+  if (!li.inner[Lv].empty() && use_two(h, Lv, 1)) count(EXCMG_K_CG_A32, EXCMG_K_CG_B32, li.iters[Lv]);
   return EXCMG_OK;
 }
 
@@ -818,7 +935,7 @@ int cascade(excmg_handle *h, int mode, const double *f, const double *g, excmg_s
         final_status = EXCMG_ERR_NOCONV;
       else if (e)
         return e;
-      if (li) li->iters[l] = exact ? 0 : it;
+      if (li) li->iters[l] = li->launches[l] = exact ? 0 : it;
       if (st) {
         st->iters[l] = it;
         st->relres[l] = rr;
@@ -850,6 +967,7 @@ int cascade(excmg_handle *h, int mode, const double *f, const double *g, excmg_s
     int e = EXCMG_OK;
     int it = 0, outer = 0, dit = 0;
     double rr = 0.0;
+    h->two_pairs = 0;
     if (l <= 1) {
       {
         Tick t(h, EXCMG_K_OTHER, l);
@@ -892,7 +1010,10 @@ int cascade(excmg_handle *h, int mode, const double *f, const double *g, excmg_s
         return d ? d : e;
       }
     }
-    if (li) li->iters[l] = l <= 1 ? dit : it;
+    if (li) {
+      li->iters[l] = l <= 1 ? dit : it;
+      li->launches[l] = swept(lo, l) && h->two_pairs > 0 ? h->two_pairs : li->iters[l];
+    }
     if (st) {
       st->iters[l] = it;
       st->ir_outer[l] = outer;
@@ -973,11 +1094,12 @@ void batch_entry(excmg_handle *h, int problem, int l, const double *f, const dou
   E->eta = h->p.inner_tol > 0.0 ? h->p.inner_tol : 1e-5;
   // every entry of a batched launch has the launch's tile height (bty: the batch's, for the FP64 and the FP32
   // passes); a grid tuned alone to another keeps its z chunk here
-  E->swA = with_height(lv.swA, bty[0]);
-  E->swB = with_height(lv.swB, bty[0]);
+  const Sweep own = make_sweep(lv.g, lv.st, 0), own32 = make_sweep(lv.g32, lv.st, 0);
+  E->swA = with_height(lv.shaped ? lv.swA : own, bty[0]);
+  E->swB = with_height(lv.shaped ? lv.swB : own, bty[0]);
   E->swR = default_height(lv.sw);
-  E->swA32 = with_height(lv.swA32, bty[1]);
-  E->swB32 = with_height(lv.swB32, bty[1]);
+  E->swA32 = with_height(lv.shaped ? lv.swA32 : own32, bty[1]);
+  E->swB32 = with_height(lv.shaped ? lv.swB32 : own32, bty[1]);
   E->g = lv.g;
   E->g32 = lv.g32;
   E->gd = lo.gdense;
@@ -1439,6 +1561,7 @@ int batched_autotune(excmg_handle *const *hs, int count, char *ws, int32_t *zc_o
           const Sweep sw = make_sweep(prec ? lv.g32 : lv.g, lv.st, zc, depth, 1, ty);
           if (prec) lv.swA32 = lv.swB32 = sw;
           else lv.swA = lv.swB = sw;
+          lv.shaped = true;
         }
         if (zc_out) zc_out[2 * t + prec] = zc;
       }
@@ -1563,7 +1686,7 @@ int excmg_setup(const excmg_problem *p, void *workspace, size_t bytes, void *hip
     delete h;
     return EXCMG_ERR_HIP;
   }
-  launch_clear_gbnd2(h->cs, h->cs2, h->stream);
+  launch_clear_state(h->cs, h->cs2, h->stream);
   if (hipGetLastError() != hipSuccess || hipStreamSynchronize(h->stream) != hipSuccess) {
     delete h;
     return EXCMG_ERR_HIP;
@@ -1596,7 +1719,7 @@ int excmg_solve_noalloc(const excmg_problem *p, const double *f, const double *g
   if ((e = scratch_address(h.device, &ws))) return e;
   h.ws = (char *)ws;
   bind_workspace(&h);
-  launch_clear_gbnd2(h.cs, h.cs2, h.stream);  // what excmg_setup clears: the CG states' boundary norm terms
+  launch_clear_state(h.cs, h.cs2, h.stream);  // what excmg_setup clears: the CG states' boundary norm terms
   if ((e = last_error())) return e;
   return solve_on(&h, f, g, u, u_ext, st);
 }
@@ -1612,6 +1735,9 @@ int solve_on(excmg_handle *h, const double *f, const double *g, double *u, doubl
   reset_timing(h);
   LevelIters li;
   memset(li.iters, 0, sizeof(li.iters));
+  memset(li.launches, 0, sizeof(li.launches));
+  OutputBinding binding{h};
+  bind_output(h, u, nullptr);  // (f and g are last read by the finest grid's residual, before the sweeps)
   const int status = cascade(h, 0, f, g, st, h->noalloc ? nullptr : &li);
   if (status != EXCMG_OK && status != EXCMG_ERR_NOCONV) return status;
   Layout &lo = h->lo;
@@ -1668,6 +1794,10 @@ int excmg_adjoint(excmg_handle *h, const double *G, double *dLdf, double *dLdg, 
   reset_timing(h);
   LevelIters li;
   memset(li.iters, 0, sizeof(li.iters));
+  memset(li.launches, 0, sizeof(li.launches));
+  OutputBinding binding{h};
+  bind_output(h, dLdf, G);
+  bind_output(h, dLdg, G);
   const int status = cascade(h, 1, G, nullptr, st, &li);
   if (status != EXCMG_OK && status != EXCMG_ERR_NOCONV) return status;
   Layout &lo = h->lo;
@@ -1700,6 +1830,9 @@ int excmg_autotune(excmg_handle *h, int32_t *zc_out, int32_t *depth_out) {
   HIPCHECK(hipEventCreateWithFlags(&eb, kTimingEvent));
   int rc = EXCMG_OK;
   double *pa = h->partials, *pb = h->partials + lo.npart;
+  OutputBinding binding{h};  // the finest grid's trials have its own solution array for the fourth vector
+  h->xfin = lo.lev[lo.L - 1].u;
+  h->gxfin = lo.gfin;
   for (int l = 0; l < lo.L && rc == EXCMG_OK; ++l) {
     Level &lv = lo.lev[l];
     if (!swept(lo, l)) continue;  // solved by the single-workgroup kernel
@@ -1707,16 +1840,19 @@ int excmg_autotune(excmg_handle *h, int32_t *zc_out, int32_t *depth_out) {
     // A grid whose iterations run as graphs of self-finalizing passes is tuned on those kernels, with the shapes that
     // keep it self-finalizing; their launches are short, so each trial times a burst of them queued behind a delay
     // (back to back, as in a graph) instead of one launch between two events, whose own cost would hide the kernel.
-    const bool burst = use_graphs(h, l) && sweep_blocks(lv.sw) <= selfred_max_blocks();
+    // (the two-step sweeps always finalize their own reductions)
+    const bool two_any = use_two(h, l, 0) || (ir && use_two(h, l, 1));
+    const bool burst = use_graphs(h, l) && (two_any || sweep_blocks(lv.sw) <= selfred_max_blocks());
     // a grid that will run the single-reduction CG has its pass-B shape (which that CG uses) timed on that CG's
     // iterations (the trial state makes every launch of parity 1 run iteration 1 in full)
-    const bool cg1 = burst && cg1_eligible(h, l);
+    const bool cg1 = burst && !two_any && cg1_eligible(h, l);
     // kinds: FP64 passes, FP32 passes (refinement grids), and the FP64 passes of the first iteration (p = r: pass A
     // reads r alone, pass B takes p from r's buffer) on grids whose passes finalize apart
     for (int kind = 0; kind < 3 && rc == EXCMG_OK; ++kind) {
       if ((kind == 1 && !ir) || (kind == 2 && burst)) continue;
       const int prec = kind == 1;
       const bool first = kind == 2;
+      const bool two = use_two(h, l, prec);
       const Grid &g = prec ? lv.g32 : lv.g;
       for (int pass = 0; pass < 2 && rc == EXCMG_OK; ++pass) {
         float best = 1e30f;
@@ -1733,7 +1869,10 @@ int excmg_autotune(excmg_handle *h, int32_t *zc_out, int32_t *depth_out) {
           float tmin = 1e30f;
           for (int rep = 0; rep < reps && rc == EXCMG_OK; ++rep) {
             const bool cg1_trial = cg1 && prec == 0 && pass == 1;
-            if (burst) {
+            if (two) {
+              launch_tune_state(h->cs2, first ? 0 : 1, s);
+              if (burst) launch_delay(kTuneDelayUs, s);
+            } else if (burst) {
               launch_tune_selfred(h->cs2, pass ? pa : pb, cg1_trial ? 2 * sweep_blocks(sw) : nb_other, s);
               launch_delay(kTuneDelayUs, s);
             } else {
@@ -1741,7 +1880,15 @@ int excmg_autotune(excmg_handle *h, int32_t *zc_out, int32_t *depth_out) {
             }
             if (hipEventRecord(ea, s) != hipSuccess) rc = EXCMG_ERR_HIP;
             for (int q = 0; q < (burst ? kTuneBurst : 1); ++q) {
-              if (cg1_trial) {  // u and p: the first two slots of p1's buffer (the grid's u may not be bound yet)
+              if (two && prec == 0) {
+                const TwoVecs<double> v = two_vecs64(h, l);
+                if (pass == 0) launch_two_g<double>(sw, v, h->cs2, h->partials, s);
+                else launch_two_u<double>(sw, v, h->cs2, h->partials, s);
+              } else if (two) {
+                const TwoVecs<float> v = two_vecs32(h, l);
+                if (pass == 0) launch_two_g<float>(sw, v, h->cs2, h->partials, s);
+                else launch_two_u<float>(sw, v, h->cs2, h->partials, s);
+              } else if (cg1_trial) {  // u and p: the first two slots of p1's buffer (the grid's u may not be bound yet)
                 launch_cg1_iteration(sw, h->p1 + cg1_stride(lv), h->p1, cg1_vec(h, lv, 1, 0), cg1_vec(h, lv, 1, 1),
                                      cg1_vec(h, lv, 1, 2), cg1_vec(h, lv, 0, 0), cg1_vec(h, lv, 0, 1),
                                      cg1_vec(h, lv, 0, 2), h->cs2, 1, pa, cg1_resid_parts(h), sweep_blocks(lv.sw),
@@ -1783,7 +1930,9 @@ int excmg_autotune(excmg_handle *h, int32_t *zc_out, int32_t *depth_out) {
           if (ty > 4 && ty / 2 >= g.ny - 1) continue;  // a tile at least twice the grid's height
           const Sweep sw = make_sweep(g, lv.st, zc, depth, nt, ty);
           if (3LL * sweep_blocks(sw) > lo.npart) continue;
-          if (burst && sweep_blocks(sw) > selfred_max_blocks()) continue;
+          if (two && depth > 3) continue;  // runs as 3
+          if (two && pass == 0 && nt) continue;  // pass G touches every array with halos
+          if (burst && !two && sweep_blocks(sw) > selfred_max_blocks()) continue;
           if (cg1 && prec == 0 && pass == 1 && 4LL * sweep_blocks(sw) > lo.npart) continue;
           timed.push_back({trial(sw, 3), sw});
         }
@@ -1799,6 +1948,7 @@ int excmg_autotune(excmg_handle *h, int32_t *zc_out, int32_t *depth_out) {
         }
         if (rc) break;
         dst = bsw;
+        lv.shaped = true;
       }
     }
   }
@@ -1877,6 +2027,7 @@ int excmg_set_sweep(excmg_handle *h, int32_t level, int32_t kind, const int32_t 
   DeviceGuard dg(h->device);
   HIPCHECK(hipStreamSynchronize(h->stream));  // no launch of an earlier call still uses the old shape
   *sw = nw;
+  h->lo.lev[level].shaped = true;
   h->drop_graphs();  // captured with the old sweep shapes
   return EXCMG_OK;
 }

@@ -186,6 +186,13 @@ struct CgState {
                    // under EXCMG_STOP_F_G, else 0 (set at setup and by boundary_g2_kernel)
   double rhoA[2];
   double alphaA[2];  // the single-reduction CG: alpha of iteration k in slot k mod 2
+  // The two-step sweeps (pass G sets the first four, pass U the others)
+  double alpha1, beta0;  // the second iteration's step, and its beta
+  int single;            // this pair makes one iteration only
+  int pairs;             // pairs made (which buffers hold r and p)
+  double cross, alast;   // r.r_before and alpha of the last iteration
+  unsigned count;        // workgroups that have finished the current launch (0 between launches)
+  int tune;              // the autotuner's trials: the scalars stay as they are
   double hist[EXCMG_MAX_HISTORY];
 };
 
@@ -237,6 +244,21 @@ void launch_probe_sweep(int mode, int u, bool nt, bool chunk, int wg_per_cu, con
 // one CG iteration with the reductions finalized inside the sweeps: pass A reads nb_prev partial sums from partsB
 // (the residual's [r.r | b.b] before iteration 0, pass B's r.r afterwards) and writes partsA; pass B reads nbA from
 // partsA and writes partsB
+// Vectors of the two-step sweeps (x in a layout gx of its own, the others in the sweep's)
+template <typename T>
+struct TwoVecs {
+  T *u, *r, *p0, *p1, *x;
+  Grid gx;
+};
+// the two sweeps of a pair of CG iterations; each finalizes its own sums (parts: 5 per workgroup of two_sweep)
+template <typename T>
+void launch_two_g(const Sweep &swA, const TwoVecs<T> &v, CgState *cs, double *parts, hipStream_t st);
+template <typename T>
+void launch_two_u(const Sweep &swB, const TwoVecs<T> &v, CgState *cs, double *parts, hipStream_t st);
+Sweep two_sweep(const Sweep &sw);  // the sweep with the two-step tiles of its height
+// the default shape of pass G or U over a grid
+Sweep two_default(const Grid &g, const Stencil &st, bool fp32, bool pass_u, int nt);
+
 template <typename T>
 void launch_selfred_a(const Sweep &swA, T *r, T *p0, T *p1, CgState *cs, const double *partsB, int nb_prev,
                       double tol, double *partsA, hipStream_t st);
@@ -249,8 +271,8 @@ int selfred_max_blocks();
 void launch_selfred_init(CgState *cs, int max_iters, int hist_on, int preset, hipStream_t st);
 // cs->gbnd2 = the sum of g^2 over the boundary nodes of grid g (0 if rs.fg is 0 or rs.mode is 1); one workgroup
 void launch_boundary_g2(const RhsSrc &rs, const Grid &g, CgState *cs, hipStream_t st);
-// cs->gbnd2 = 0 for each state (at setup)
-void launch_clear_gbnd2(CgState *a, CgState *b, hipStream_t st);
+// gbnd2 and count = 0 for each state (at setup)
+void launch_clear_state(CgState *a, CgState *b, hipStream_t st);
 // residual sweep writing [r.r | b.b] partials without a finalize (for the self-finalizing iterations)
 // The single-reduction CG of self-finalizing grids (kernels_cg.hip): the init sweep w = M r with the partial sums
 // of r.r and w.r into parts, and iteration k (launch parity par) from r, w, s into ro, wo, so (u, p in place), from

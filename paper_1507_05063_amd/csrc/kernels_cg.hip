@@ -28,27 +28,12 @@
 #include <type_traits>
 #include <utility>
 
+#include "cg_device.h"
 #include "excmg_internal.h"
 
 namespace excmg {
 
 namespace {
-
-constexpr int kXcds = 8;
-
-// Bijection from the hardware workgroup id to a logical tile id such that logical ids [x*per, (x+1)*per) run on XCD x.
-__device__ __forceinline__ int xcd_remap(int b, int nb) {
-  const int per = nb / kXcds, rem = nb % kXcds;
-  const int x = b % kXcds, l = b / kXcds;
-  const int start = (x < rem) ? x * (per + 1) : rem * (per + 1) + (x - rem) * per;
-  return start + l;
-}
-
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
 
 // Sum over the workgroup, deterministic; the result is valid in thread 0.
 template <int NT>
@@ -65,8 +50,6 @@ __device__ __forceinline__ double block_sum(double v, double *sh) {
   return t;
 }
 
-// Tile shape of the stencil sweeps (x is the fast axis: one wavefront covers one 64-node row segment).
-constexpr int TX = 64;
 // Threads of a workgroup with tile height TY, and the rows of one LDS plane buffer: the (TX+2) x (TY+2) tile with its
 // halo, padded so that every fetch slot of the workgroup (a whole number of slots per thread) has an entry and the
 // staging stores need no bounds test.  A taller tile re-reads fewer halo rows per node (2 per TY rows); a shorter one
@@ -82,31 +65,6 @@ constexpr bool height_ok() { return TY == 4 || TY == 8 || TY == 16; }
 constexpr int kTy = 4;
 constexpr int NT = Tile<kTy>::NT;
 constexpr int kTileRows = Tile<kTy>::Rows;
-
-__device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
-
-// Loads and stores of data a sweep touches once: non-temporal (streaming) when NTP, so that they do not displace the
-// operand's halo lines, which neighbouring tiles read again, from the caches.
-template <bool NTP, typename T>
-__device__ __forceinline__ T ld1(const T *p) {
-  if constexpr (NTP) return __builtin_nontemporal_load(p);
-  else return *p;
-}
-template <bool NTP, typename T>
-__device__ __forceinline__ void st1(T v, T *p) {
-  if constexpr (NTP) __builtin_nontemporal_store(v, p);
-  else *p = v;
-}
-
-// f(integral_constant<int, 0>), ..., f(integral_constant<int, N - 1>), in that order
-template <typename F, int... Q>
-__device__ __forceinline__ void static_for_impl(F &&f, std::integer_sequence<int, Q...>) {
-  (f(std::integral_constant<int, Q>{}), ...);
-}
-template <int N, typename F>
-__device__ __forceinline__ void static_for(F &&f) {
-  static_for_impl(f, std::make_integer_sequence<int, N>{});
-}
 
 // Prefetch depths the z-march is built for.  Deeper prefetch keeps more bytes in flight per thread, which the FP32
 // sweeps need (half the bytes per load of FP64 at the same latency); it costs registers.
@@ -325,6 +283,8 @@ __device__ void state_init(CgState *cs, double rho, double bb, double tol, int m
   cs->status = 0;
   cs->max_iters = max_iters;
   cs->hist_on = hist_on;
+  cs->pairs = 0;
+  cs->tune = 0;
   const bool finite = isfinite(rho) && isfinite(bb);
   cs->done = (!finite || rho <= cs->stop2) ? 1 : 0;
   if (!finite) cs->status = EXCMG_ERR_BREAKDOWN;
@@ -396,6 +356,8 @@ __device__ void state_ir(CgState *outer, CgState *inner, double r64, double bb, 
   inner->max_iters = max_inner;
   inner->hist_on = 0;
   inner->done = (outer->done || !(r32 > 0.0)) ? 1 : 0;
+  inner->pairs = 0;
+  inner->tune = 0;
   inner->iterA = 0;
   inner->iterB = 0;
   inner->preset = 1;  // a self-finalizing inner solve takes rho and stop2 from here
@@ -1051,9 +1013,12 @@ __global__ __launch_bounds__(FT) void boundary_g2_kernel(RhsSrc rs, Grid g, CgSt
   if (threadIdx.x == 0) cs->gbnd2 = t;
 }
 
-__global__ void clear_gbnd2_kernel(CgState *a, CgState *b) {
+// what a CG state holds from before its first solve
+__global__ void clear_state_kernel(CgState *a, CgState *b) {
   a->gbnd2 = 0.0;
   b->gbnd2 = 0.0;
+  a->count = 0;
+  b->count = 0;
 }
 
 // --------------------------------------------------------------------------------------------------------- finalize
@@ -1108,12 +1073,19 @@ __device__ void tune_state(CgState *cs) {
   cs->status = 0;
   cs->max_iters = 1 << 30;
   cs->hist_on = 0;
+  // the two-step sweeps: the pair of that iteration, whose sums leave the state alone
+  cs->alpha1 = 0.0;
+  cs->beta0 = 0.0;
+  cs->single = 0;
+  cs->pairs = 1;
+  cs->tune = 1;
 }
 
 // the same at iteration iter: 0 for the trials of a first iteration's passes (p = r)
 __global__ void tune_state_kernel(CgState *cs, int iter) {
   tune_state(cs);
   cs->iter = iter;
+  cs->pairs = iter;
 }
 
 // the trial state of a self-finalizing pass (iteration 1 of both passes, never converged) and n partial sums of 1 for
@@ -1837,7 +1809,7 @@ void launch_boundary_g2(const RhsSrc &rs, const Grid &g, CgState *cs, hipStream_
   boundary_g2_kernel<<<1, FT, 0, st>>>(rs, g, cs);
 }
 
-void launch_clear_gbnd2(CgState *a, CgState *b, hipStream_t st) { clear_gbnd2_kernel<<<1, 1, 0, st>>>(a, b); }
+void launch_clear_state(CgState *a, CgState *b, hipStream_t st) { clear_state_kernel<<<1, 1, 0, st>>>(a, b); }
 
 void launch_selfred_init(CgState *cs, int max_iters, int hist_on, int preset, hipStream_t st) {
   selfred_init_kernel<<<1, 1, 0, st>>>(cs, max_iters, hist_on, preset);
@@ -1873,6 +1845,7 @@ template void launch_selfred_b<float>(const Sweep &, float *, float *, float *, 
                                       const double *, int, double *, hipStream_t);
 
 int selfred_max_blocks() { return kSelfRedMaxBlocks; }
+
 
 // f(depth, height) for the single-reduction CG sweeps, which prefetch 2 or 3 planes (a deeper depth runs as 3)
 template <typename F>
