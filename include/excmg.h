@@ -71,18 +71,17 @@ extern "C" {
  * reproduces both the paper's printed finest-grid errors (Tables 1-12, read as the grids of one run) and its printed
  * finest-grid iteration counts.  At most one of EXCMG_STOP_F_G and this flag. */
 #define EXCMG_STOP_F_G_BELOW_FINEST 64u
-/* CG form on the small grids below the finest (at most 2^18 unknowns, from the third grid on) whose iterations
- * finalize their own reductions.  Default:
- * the single-reduction form of Chronopoulos and Gear, the same Krylov iterates as Algorithm 1's CG in exact
- * arithmetic (so the same iteration counts up to rounding), with both inner products of an iteration from one
- * reduction, which makes an iteration one kernel launch instead of two; it keeps s = M p and w = M r and moves 80
- * bytes per unknown and iteration instead of 64.  With this flag every grid runs the two-pass CG as written. */
+/* CG form.  With this flag every grid runs the two-pass CG as Algorithm 1 has it (one workgroup up to 8000 unknowns).
+ * Default, from the third grid on and with the same iterates up to rounding and so the same iteration counts:
+ * - FP64 grids whose vectors fit the chip (up to about 2^21 unknowns, 128^3 cells): the whole CG in one launch, in the
+ *   single-reduction form of Chronopoulos and Gear (the same Krylov iterates as Algorithm 1's in exact arithmetic).
+ *   Its workgroups wait for one another, so such launches of one process take turns on a device; where another
+ *   process keeps them from running together for about a second, the call starts over without that form.
+ * - Grids above 2^21 unknowns (in FP64, and in FP32 under EXCMG_FP32_IR): pairs of iterations in two sweeps a pair.  The
+ *   first forms M p and M (M p) and sums the products from which the second iteration's coefficients follow, the
+ *   second makes both iterations (one where it converges or reaches the cap after the first), at half the bytes of
+ *   two sweeps an iteration. */
 #define EXCMG_TWO_PASS_CG 256u
-/* Grids above 2^21 unknowns (in FP64, and in FP32 under EXCMG_FP32_IR) run the CG in pairs of iterations, in two sweeps
- * a pair: the first forms M p and M (M p) and sums the products from which the second iteration's coefficients follow,
- * the second makes both iterations.  The same iterates up to rounding and the same iteration counts (a pair stops
- * after its first iteration where that one converges or reaches the cap), at half the bytes of two sweeps an iteration.
- * EXCMG_TWO_PASS_CG turns this off too. */
 
 #define EXCMG_MAX_LEVELS 16
 #define EXCMG_MAX_HISTORY 256
@@ -257,15 +256,15 @@ int excmg_autotune_batched(excmg_handle *const *hs, int32_t count, void *batch_w
  * of loads in flight per thread) and each cache policy (ordinary or non-temporal loads and stores of the data a
  * sweep touches once), on the handle's own work buffers (no caller array is read or written), and keeps the fastest
  * per grid and kernel for every later call on this handle.  Grids below the finest, whose iterations run as graphs
- * of self-finalizing passes, are timed on those kernels, with the shapes that keep them self-finalizing; on those
- * that run the single-reduction CG (see EXCMG_TWO_PASS_CG) the pass-B shape, which that CG uses, is timed on its
- * iterations.
+ * of self-finalizing passes, are timed on those kernels, with the shapes that keep them self-finalizing.  Grids that
+ * run iterations in pairs are timed on the pair's sweeps; grids relaxed in one launch have no shape to tune (see
+ * EXCMG_TWO_PASS_CG) and keep the default's.
  * zc_out, depth_out (host, nullable, 4 * levels entries each): per grid, pass A and pass B in FP64, then in FP32 (0
  * where the grid is not relaxed that way): the chunk, and depth + 10 (if the non-temporal policy won) + 100 * tile
  * height.  Batched solves (excmg_solve_batched) keep the chunk and use the handle's batch shape
  * (excmg_get_batch_shape; excmg_autotune_batched chooses it).
- * Optional: without it the handle uses a fixed default (16 planes, fewer on small grids; 4 rows; depth 2;
- * ordinary). */
+ * Optional: without it the handle uses a default: for pairs of iterations the shape whose rounds of resident
+ * workgroups take the least estimated time, else 16 planes, fewer on small grids; 4 rows; depth 2; ordinary. */
 int excmg_autotune(excmg_handle *h, int32_t *zc_out, int32_t *depth_out);
 
 /* Sweep shapes (host calls).  A sweep of grid `level` (0 = coarsest) of kind EXCMG_SWEEP_*: the CG passes A and B in

@@ -94,8 +94,8 @@ class Solver:
         looser on the coarser ones (0: tol everywhere, Algorithm 1).
         tol_coarse: 0, or in (0, 1) with tol_order 0: every grid below the finest relaxes to tol_coarse, the finest
         to tol.
-        two_pass_cg: run the two-pass CG as written on every grid (default: the single-reduction form on the
-        small grids below the finest, up to 2^18 unknowns, one launch per iteration)."""
+        two_pass_cg: run the two-pass CG as written on every grid (default: FP64 grids that fit the chip relaxed in one
+        launch, pairs of iterations in two sweeps on the largest grids)."""
         torch = _torch()
         self.n = tuple(int(v) for v in n)
         self.box = tuple(float(v) for v in box)

@@ -53,6 +53,14 @@ __device__ __forceinline__ void static_for(F &&f) {
   static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
+// a node of a plane by its byte offset there (32 bits: the launchers refuse larger planes), so that a load is one
+// uniform base and one 32-bit offset
+template <typename T>
+__device__ __forceinline__ T *at_byte(T *plane, unsigned off) {
+  return reinterpret_cast<T *>(reinterpret_cast<std::conditional_t<std::is_const_v<T>, const char, char> *>(plane) +
+                               off);
+}
+
 }  // namespace
 
 }  // namespace excmg

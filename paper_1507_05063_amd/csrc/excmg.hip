@@ -5,8 +5,9 @@
 //                formed on the fly by every kernel that needs it (never stored)
 //   grids 0, 1   DSOLVE: single-workgroup CG to rounding                                     (Algorithm 1, coarsest grids)
 //   grids >= 2   w = EXP_finite(u_{l-1}, u_{l-2}), then CG from w until ||r|| <= tol ||b||   (Algorithm 1, the loop):
-//                one single-workgroup launch on grids of at most 8000 unknowns, otherwise two stencil sweeps and
-//                two single-workgroup reductions per iteration
+//                one launch of the resident CG on FP64 grids that fit the chip (kernels_resident.hip), pairs of
+//                iterations in two sweeps on the largest grids (kernels_two.hip), else one single-workgroup launch on
+//                grids of at most 8000 unknowns, or two stencil sweeps and their reductions per iteration
 //   finest       u_ext = EXP_true(u_h, u_2h) on request; u copied to the caller's dense array
 // The library allocates no device memory: every array lives in the caller's workspace.  The host reads the CG state
 // back (one small copy and a stream sync) after every batch of iterations; iterations launched after convergence
@@ -37,6 +38,7 @@ struct Level {
   Sweep sw, sw32;  // stencil sweeps over g and g32 (residual kernels)
   Sweep swA, swB, swA32, swB32;  // CG passes A and B in FP64 and FP32 (z chunk chosen by the autotuner)
   Sweep swA0, swB0;  // the FP64 passes of a grid's first iterations (p = r), on grids launched without graphs
+  ResidentPlan res;  // the resident CG's bricks (threads 0: the grid does not run it)
   bool shaped;       // the CG passes' shapes were tuned or set (else batched solves take their own default)
   double *u;   // this grid's solution, all nodes (boundary = g)
 };
@@ -179,6 +181,7 @@ int make_layout(const excmg_problem *p, Layout *Lo) {
     lv.swA0 = lv.swA;
     lv.swB0 = lv.swB;
     lv.shaped = false;
+    lv.res = {};
     lv.u = nullptr;
     Lo->off_u[l] = off;
     off = align256(off + (size_t)lv.g.elems * sizeof(double));
@@ -263,6 +266,7 @@ struct excmg_handle {
   double *xfin = nullptr;
   Grid gxfin = {};
   int two_pairs = 0;  // pairs of the last two-step solve (kernel timing)
+  bool apart = false; // this call relaxes no grid by the resident CG (a workgroup of it gave up waiting)
   // graphs of a batched round's CG iterations (excmg_solve_batched, on the batch's first handle), by launch shape
   struct BatchGraph {
     std::vector<long long> key;
@@ -316,6 +320,10 @@ struct DeviceGuard {
   } while (0)
 
 inline int last_error() { return hipGetLastError() == hipSuccess ? EXCMG_OK : EXCMG_ERR_HIP; }
+
+constexpr int kResidentTick = -2;  // TimedLaunch.iter of a resident CG: all iterations' passes in one launch
+
+constexpr int kMaxDevices = 64;
 
 // Kernel timing: a pair of events around each launch on the finest grid when EXCMG_WANT_TIMING is set (the coarser
 // grids' launches are replayed from graphs, and their event records would cost as much as the kernels they time).
@@ -431,51 +439,15 @@ bool self_finalizing(const Level &lv, bool fp32) {
   return sweep_blocks(a) <= m && sweep_blocks(b) <= m && sweep_blocks(lv.sw) <= m;
 }
 
-// The single-reduction CG (launch_cg1_*) on grid l: FP64 self-finalizing grids of at most kCg1MaxUnknowns from the
-// third to the one below the finest (the direct solves keep the two-pass form), unless EXCMG_TWO_PASS_CG.  Its vectors: u; p in p1's buffer;
-// two sets of (r, w, s), one after the other in r's buffer (set 0, where the residual sweep leaves r) and in p0's
-// (set 1), which the iterations read and write alternately (each buffer holds the finest grid, three times a grid
-// below it).  Its partial sums: the iterations' alternately in the two halves of the partials buffer, the residual
-// sweep's in the second quarter, the init sweep's in the second half.
-constexpr long long kCg1Align = 32;  // doubles (256 bytes)
-// Grids up to this many unknowns, where an iteration's two launches cost more than their bytes: 512^3 step, grids
-// 32^3 / 64^3 / 128^3 / 256^3 0.476 / 0.585 / 1.06 / 1.72 ms in the two-pass form, 0.374 / 0.540 / 1.115 / 2.91 ms in
-// this one (which moves 80 bytes per unknown and iteration against 64, plus the sweep w = M r at the start)
-constexpr long long kCg1MaxUnknowns = 1LL << 18;
-long long cg1_stride(const Level &lv) { return (lv.g.elems + kCg1Align - 1) / kCg1Align * kCg1Align; }
-Sweep cg1_sweep(const Level &lv) { return lv.swB; }
-// everything use_cg1 asks of grid l but that its passes finalize themselves with the sweep of at most 1/4 of the
-// partials buffer's half
-bool cg1_eligible(const excmg_handle *h, int l) {
-  const Layout &lo = h->lo;
-  const Level &lv = lo.lev[l];
-  if ((h->p.flags & EXCMG_TWO_PASS_CG) || l < 2 || l >= lo.L - 1 || lv.g.interior() > kCg1MaxUnknowns) return false;
-  return 4LL * sweep_blocks(lv.sw) <= lo.npart && 2 * cg1_stride(lv) + lv.g.elems <= lo.gfin.elems;
-}
-bool use_cg1(const excmg_handle *h, int l) {
-  const Level &lv = h->lo.lev[l];
-  return cg1_eligible(h, l) && self_finalizing(lv, false) && 4LL * sweep_blocks(cg1_sweep(lv)) <= h->lo.npart;
-}
-double *cg1_resid_parts(const excmg_handle *h) { return h->partials + h->lo.npart / 2; }
-// vector j (0 r, 1 w, 2 s) of set q
-double *cg1_vec(excmg_handle *h, const Level &lv, int q, int j) { return (q ? h->p0 : h->r) + j * cg1_stride(lv); }
-
-// Iteration `launched` of the single-reduction CG on grid l (par: its parity): reads set par, writes set 1 - par
-void launch_cg1_step(excmg_handle *h, int l, hipStream_t s, int par) {
-  Level &lv = h->lo.lev[l];
-  double *pa = h->partials, *pb = h->partials + h->lo.npart;
-  launch_cg1_iteration(cg1_sweep(lv), lv.u, h->p1, cg1_vec(h, lv, par, 0), cg1_vec(h, lv, par, 1),
-                       cg1_vec(h, lv, par, 2), cg1_vec(h, lv, 1 - par, 0), cg1_vec(h, lv, 1 - par, 1),
-                       cg1_vec(h, lv, 1 - par, 2), h->cs, par, par ? pa : pb, cg1_resid_parts(h),
-                       sweep_blocks(lv.sw), grid_tol(h->p, l, h->lo.L), par ? pb : pa, s);
-}
+// the fourth vector of a grid below the finest: this many elements into r's buffer (whole cache lines)
+long long vec_stride(const Level &lv) { return (lv.g.elems + 31) / 32 * 32; }
 
 // The two-step sweeps (kernels_two.hip) relax the large grids (two_grid), unless EXCMG_TWO_PASS_CG asks for two
 // sweeps an iteration.  They need a fourth vector beside r, p0 and p1: below the finest it follows r in r's buffer (which holds
 // the finest grid); the FP32 refinement, which leaves the FP64 p0 idle, has it there; the finest FP64 grid takes an
 // output array of the call (bind_output).  Byte offsets in a plane are 32 bits.
 bool plane_fits(const Grid &g, size_t size) { return (unsigned long long)g.sz * size < (1ull << 32); }
-bool two_below(const Layout &lo, const Level &lv) { return cg1_stride(lv) + lv.g.elems <= lo.gfin.elems; }
+bool two_below(const Layout &lo, const Level &lv) { return vec_stride(lv) + lv.g.elems <= lo.gfin.elems; }
 bool use_two(const excmg_handle *h, int l, int fp32) {
   const Layout &lo = h->lo;
   const Level &lv = lo.lev[l];
@@ -488,7 +460,7 @@ bool use_two(const excmg_handle *h, int l, int fp32) {
 TwoVecs<double> two_vecs64(const excmg_handle *h, int l) {
   const Level &lv = h->lo.lev[l];
   if (l == h->lo.L - 1) return {lv.u, h->r, h->p0, h->p1, h->xfin, h->gxfin};
-  return {lv.u, h->r, h->p0, h->p1, h->r + cg1_stride(lv), lv.g};
+  return {lv.u, h->r, h->p0, h->p1, h->r + vec_stride(lv), lv.g};
 }
 TwoVecs<float> two_vecs32(const excmg_handle *h, int l) {
   return {h->d32, h->r32, h->p32a, h->p32b, (float *)h->p0, h->lo.lev[l].g32};
@@ -571,10 +543,6 @@ void launch_iteration(excmg_handle *h, int l, int fp32, bool first, hipStream_t 
     }
     return;
   }
-  if (use_cg1(h, l)) {  // (never the finest grid: no kernel timing)
-    launch_cg1_step(h, l, s, launched & 1);
-    return;
-  }
   if (self_finalizing(lv, false)) {
     {
       Tick t(h, EXCMG_K_CG_A, l, launched);
@@ -609,15 +577,11 @@ int launch_iteration_graph(excmg_handle *h, int l, int fp32, int si) {
   if (!ex) {
     hipGraph_t g = nullptr;
     HIPCHECK(hipStreamBeginCapture(h->cap, hipStreamCaptureModeThreadLocal));
-    // (the single-reduction CG: graphs start at odd iterations, after the first one's direct launch; the two-step
-    // sweeps: pairs, from the first on, in the shapes of the later ones)
+    // (the two-step sweeps: pairs, from the first on, in the shapes of the later ones)
     const bool two = use_two(h, l, fp32);
-    const bool cg1 = !two && !fp32 && use_cg1(h, l);
     for (int q = 0; q < kGraphSizes[si]; ++q) {
-      if (two) {
-        if (q % 2 == 0) launch_pair(h, l, fp32, h->cap, -1, -1);
-      } else if (cg1) launch_cg1_step(h, l, h->cap, (1 + q) & 1);
-      else launch_iteration(h, l, fp32, false, h->cap, -1, -1);
+      if (!two) launch_iteration(h, l, fp32, false, h->cap, -1, -1);
+      else if (q % 2 == 0) launch_pair(h, l, fp32, h->cap, -1, -1);
     }
     const hipError_t ec = hipStreamEndCapture(h->cap, &g);
     if (ec != hipSuccess) return EXCMG_ERR_HIP;
@@ -685,11 +649,7 @@ int cg64(excmg_handle *h, int l, const RhsSrc &rs, bool finest, int *iters, doub
   double *partsB = h->partials + h->lo.npart;
   {
     Tick t(h, EXCMG_K_RESID, l);
-    if (!two && use_cg1(h, l)) {  // r, then w = M r with the partials of the first iteration's two inner products
-      launch_residual_partials(lv.sw, lv.u, rs, h->r, cg1_resid_parts(h), s);
-      launch_selfred_init(h->cs, maxit, hist_on, 0, s);
-      launch_cg1_init(cg1_sweep(lv), cg1_vec(h, lv, 0, 0), cg1_vec(h, lv, 0, 1), partsB, s);
-    } else if (selfred) {
+    if (selfred) {
       launch_residual_partials(lv.sw, lv.u, rs, h->r, partsB, s);
       launch_selfred_init(h->cs, maxit, hist_on, 0, s);
     } else {
@@ -827,6 +787,93 @@ int small_cg(excmg_handle *h, int l, const RhsSrc &rs, bool exact, bool finest, 
   return hs.status;
 }
 
+// The resident CG's bricks of every grid that runs it: the FP64 relaxations, unless EXCMG_TWO_PASS_CG, as far as a
+// grid fits the device's CUs.  (Not on the per-thread default stream, which another thread could not wait for.)
+int plan_resident(excmg_handle *h) {
+  int cus = 0;
+  HIPCHECK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device));
+  if ((h->p.flags & EXCMG_TWO_PASS_CG) || h->stream == hipStreamPerThread || h->device >= kMaxDevices) return EXCMG_OK;
+  for (int l = 2; l < h->lo.L; ++l) {
+    Level &lv = h->lo.lev[l];
+    if (h->p.precision == EXCMG_FP64 || lv.g.interior() < kIrMinUnknowns)
+      lv.res = resident_plan(lv.g, cus < 256 ? cus : 256);
+  }
+  return EXCMG_OK;
+}
+
+// Per device, the handle whose call in progress launched the resident CG last.  Its workgroups wait for one another, so
+// those of two launches must never compete for the CUs: a launch first waits for the other handle's stream (calls on
+// different handles only overlap from different host threads).  A call gives the place up when its work is done.
+struct ResidentTurn {
+  std::mutex mu;
+  const excmg_handle *last = nullptr;
+};
+ResidentTurn g_resident[kMaxDevices];
+struct ResidentCall {
+  excmg_handle *h;
+  ~ResidentCall() {
+    if (h->device < 0 || h->device >= kMaxDevices) return;
+    ResidentTurn &t = g_resident[h->device];
+    {
+      std::lock_guard<std::mutex> lock(t.mu);
+      if (t.last != h) return;
+    }
+    (void)hipStreamSynchronize(h->stream);
+    std::lock_guard<std::mutex> lock(t.mu);
+    if (t.last == h) t.last = nullptr;
+  }
+};
+
+// Internal outcome: a workgroup of the resident CG gave up waiting (its grid is as it was: the call starts over with
+// the sweeps).
+constexpr int kGaveUp = -1001;
+
+// The resident CG of grid l from the current u, in one launch (defer: as small_cg).
+int resident_cg(excmg_handle *h, int l, const RhsSrc &rs, bool finest, int *iters, double *relres, excmg_stats *st,
+                bool defer) {
+  Level &lv = h->lo.lev[l];
+  const int hist_on = (finest && st && (h->p.flags & EXCMG_WANT_HISTORY)) ? 1 : 0;
+  Resident a;
+  a.g = lv.g;
+  a.u = lv.u;
+  a.rs = rs;
+  a.st = lv.st;
+  a.cs = h->cs;
+  a.scratch = h->p1;
+  a.W0 = h->r;
+  a.W1 = h->p0;
+  a.tol = grid_tol(h->p, l, h->lo.L);
+  a.cap = grid_cap(h, l);
+  a.hist_on = hist_on;
+  a.plan = lv.res;
+  {
+    Tick t(h, EXCMG_K_CG_A, l, kResidentTick);
+    ResidentTurn &turn = g_resident[h->device];
+    std::lock_guard<std::mutex> lock(turn.mu);
+    if (turn.last && turn.last != h) HIPCHECK(hipStreamSynchronize(turn.last->stream));
+    turn.last = h;
+    launch_resident(a, h->stream);
+  }
+  int e = last_error();
+  if (e) return e;
+  if (defer) {
+    launch_publish(h->cs, h->defer_dev + (size_t)l * kStateHead, kStateHead, h->stream);
+    *iters = 0;
+    *relres = 0.0;
+    return last_error();
+  }
+  CgState hs;
+  e = hist_on ? read_hist(h, &hs, h->cs) : read_state(h, &hs, h->cs);
+  if (e) return e;
+  if (hs.abort) return kGaveUp;
+  if (hist_on) {
+    const int n = hs.iter + 1 < EXCMG_MAX_HISTORY ? hs.iter + 1 : EXCMG_MAX_HISTORY;
+    st->history_len = n;
+    for (int q = 0; q < n; ++q) st->history[q] = hs.hist[q];
+  }
+  return small_cg_outcome(hs, l, false, iters, relres, st);
+}
+
 // Kernel timing on or off; the event pool is created the first time it is turned on.
 int set_timing(excmg_handle *h, bool on) {
   if (on && h->pool.empty()) {
@@ -863,6 +910,17 @@ int collect_timing(excmg_handle *h, excmg_stats *st, const LevelIters &li) {
     }
     float ms = 0.0f;
     HIPCHECK(hipEventElapsedTime(&ms, t.a, t.b));
+    if (t.iter == kResidentTick) {  // shared out evenly over its iterations' passes
+      const int it = li.iters[t.level];
+      for (int q = 0; it > 0 && q < 2; ++q) {
+        const int first = q ? EXCMG_K_CG_B0 : EXCMG_K_CG_A0, rest = q ? EXCMG_K_CG_B : EXCMG_K_CG_A;
+        st->kernel_ms[first] = st->kernel_ms_finest[first] = ms / (2 * it);
+        st->kernel_calls[first] = st->kernel_calls_finest[first] = 1;
+        st->kernel_ms[rest] = st->kernel_ms_finest[rest] = ms / (2 * it) * (it - 1);
+        st->kernel_calls[rest] = st->kernel_calls_finest[rest] = it - 1;
+      }
+      continue;
+    }
     // the first iteration (p = r) moves fewer bytes than the others: its own classes
     int cls = t.cls;
     if (t.iter == 0 && t.outer < 0 && cls == EXCMG_K_CG_A) cls = EXCMG_K_CG_A0;
@@ -927,6 +985,7 @@ int cascade(excmg_handle *h, int mode, const double *f, const double *g, excmg_s
       if (!deferred[l]) continue;
       CgState hs;
       memcpy(&hs, buf.data() + (size_t)l * kStateHead, kStateHead);
+      if (hs.abort) return kGaveUp;
       const bool exact = l <= 1;
       int it = 0;
       double rr = 0.0;
@@ -995,11 +1054,13 @@ int cascade(excmg_handle *h, int mode, const double *f, const double *g, excmg_s
       }
       e = last_error();
       if (e) return e;
-      if (!swept(lo, l)) {
+      if (lv.res.threads && !h->apart) {
+        deferred[l] = l < L - 1;
+        e = resident_cg(h, l, rs, l == L - 1, &it, &rr, st, deferred[l]);
+      } else if (!swept(lo, l)) {
         deferred[l] = l < L - 1;
         e = small_cg(h, l, rs, false, l == L - 1, &it, &rr, st, deferred[l]);
-      }
-      else if (h->p.precision == EXCMG_FP64 || lv.g.interior() < kIrMinUnknowns)
+      } else if (h->p.precision == EXCMG_FP64 || lv.g.interior() < kIrMinUnknowns)
         e = cg64(h, l, rs, l == L - 1, &it, &rr, st);
       else
         e = cg_ir(h, l, rs, l == L - 1, &it, &outer, &rr, st, li ? &li->inner[l] : nullptr);
@@ -1025,6 +1086,27 @@ int cascade(excmg_handle *h, int mode, const double *f, const double *g, excmg_s
   return e ? e : final_status;
 }
 
+void clear_stats(excmg_stats *st) {
+  if (st) memset(st, 0, sizeof(*st));
+}
+
+// The cascade, once more without the resident CG if a workgroup of it gave up waiting for the others (which takes
+// another process holding CUs for about a second).
+int run_cascade(excmg_handle *h, int mode, const double *f, const double *g, excmg_stats *st, LevelIters *li) {
+  ResidentCall call{h};
+  int e = cascade(h, mode, f, g, st, li);
+  if (e != kGaveUp) return e;
+  HIPCHECK(hipStreamSynchronize(h->stream));
+  clear_stats(st);
+  reset_timing(h);
+  if (li) *li = LevelIters{};
+  launch_clear_state(h->cs, h->cs2, h->stream);
+  h->apart = true;
+  e = cascade(h, mode, f, g, st, li);
+  h->apart = false;
+  return e;
+}
+
 void fill_level_stats(excmg_handle *h, excmg_stats *st) {
   if (!st) return;
   const bool ev = h->lev_ev[h->lo.L] != nullptr;
@@ -1035,10 +1117,6 @@ void fill_level_stats(excmg_handle *h, excmg_stats *st) {
     float ms = 0.0f;
     if (ev && hipEventElapsedTime(&ms, h->lev_ev[l], h->lev_ev[l + 1]) == hipSuccess) st->ms_level[l] = ms;
   }
-}
-
-void clear_stats(excmg_stats *st) {
-  if (st) memset(st, 0, sizeof(*st));
 }
 
 // ------------------------------------------------------------------------------------------------ batched solve
@@ -1588,7 +1666,6 @@ namespace {
 
 int solve_on(excmg_handle *h, const double *f, const double *g, double *u, double *u_ext, excmg_stats *st);
 
-constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 void *g_scratch_ptr[kMaxDevices];
 
@@ -1653,6 +1730,10 @@ int excmg_setup(const excmg_problem *p, void *workspace, size_t bytes, void *hip
   }
   h->ws = (char *)workspace;
   bind_workspace(h);
+  if ((e = plan_resident(h))) {
+    delete h;
+    return e;
+  }
   // Thomas factors of the (1,4,1) systems: m_1 = 4, m_i = 4 - 1/m_{i-1}; the table holds 1/m_i at index i.
   const Level &fin = h->lo.lev[h->lo.L - 1];
   for (int d = 0; d < 3; ++d) {
@@ -1719,6 +1800,7 @@ int excmg_solve_noalloc(const excmg_problem *p, const double *f, const double *g
   if ((e = scratch_address(h.device, &ws))) return e;
   h.ws = (char *)ws;
   bind_workspace(&h);
+  if ((e = plan_resident(&h))) return e;
   launch_clear_state(h.cs, h.cs2, h.stream);  // what excmg_setup clears: the CG states' boundary norm terms
   if ((e = last_error())) return e;
   return solve_on(&h, f, g, u, u_ext, st);
@@ -1738,7 +1820,7 @@ int solve_on(excmg_handle *h, const double *f, const double *g, double *u, doubl
   memset(li.launches, 0, sizeof(li.launches));
   OutputBinding binding{h};
   bind_output(h, u, nullptr);  // (f and g are last read by the finest grid's residual, before the sweeps)
-  const int status = cascade(h, 0, f, g, st, h->noalloc ? nullptr : &li);
+  const int status = run_cascade(h, 0, f, g, st, h->noalloc ? nullptr : &li);
   if (status != EXCMG_OK && status != EXCMG_ERR_NOCONV) return status;
   Layout &lo = h->lo;
   const Level &fin = lo.lev[lo.L - 1];
@@ -1798,7 +1880,7 @@ int excmg_adjoint(excmg_handle *h, const double *G, double *dLdf, double *dLdg, 
   OutputBinding binding{h};
   bind_output(h, dLdf, G);
   bind_output(h, dLdg, G);
-  const int status = cascade(h, 1, G, nullptr, st, &li);
+  const int status = run_cascade(h, 1, G, nullptr, st, &li);
   if (status != EXCMG_OK && status != EXCMG_ERR_NOCONV) return status;
   Layout &lo = h->lo;
   const Level &fin = lo.lev[lo.L - 1];
@@ -1835,7 +1917,7 @@ int excmg_autotune(excmg_handle *h, int32_t *zc_out, int32_t *depth_out) {
   h->gxfin = lo.gfin;
   for (int l = 0; l < lo.L && rc == EXCMG_OK; ++l) {
     Level &lv = lo.lev[l];
-    if (!swept(lo, l)) continue;  // solved by the single-workgroup kernel
+    if (!swept(lo, l) || lv.res.threads) continue;  // solved in one launch
     const bool ir = l >= 2 && (h->p.precision == EXCMG_FP32_IR) && lv.g.interior() >= kIrMinUnknowns;
     // A grid whose iterations run as graphs of self-finalizing passes is tuned on those kernels, with the shapes that
     // keep it self-finalizing; their launches are short, so each trial times a burst of them queued behind a delay
@@ -1843,9 +1925,6 @@ int excmg_autotune(excmg_handle *h, int32_t *zc_out, int32_t *depth_out) {
     // (the two-step sweeps always finalize their own reductions)
     const bool two_any = use_two(h, l, 0) || (ir && use_two(h, l, 1));
     const bool burst = use_graphs(h, l) && (two_any || sweep_blocks(lv.sw) <= selfred_max_blocks());
-    // a grid that will run the single-reduction CG has its pass-B shape (which that CG uses) timed on that CG's
-    // iterations (the trial state makes every launch of parity 1 run iteration 1 in full)
-    const bool cg1 = burst && !two_any && cg1_eligible(h, l);
     // kinds: FP64 passes, FP32 passes (refinement grids), and the FP64 passes of the first iteration (p = r: pass A
     // reads r alone, pass B takes p from r's buffer) on grids whose passes finalize apart
     for (int kind = 0; kind < 3 && rc == EXCMG_OK; ++kind) {
@@ -1868,12 +1947,11 @@ int excmg_autotune(excmg_handle *h, int32_t *zc_out, int32_t *depth_out) {
         auto trial = [&](const Sweep &sw, int reps) -> float {
           float tmin = 1e30f;
           for (int rep = 0; rep < reps && rc == EXCMG_OK; ++rep) {
-            const bool cg1_trial = cg1 && prec == 0 && pass == 1;
             if (two) {
               launch_tune_state(h->cs2, first ? 0 : 1, s);
               if (burst) launch_delay(kTuneDelayUs, s);
             } else if (burst) {
-              launch_tune_selfred(h->cs2, pass ? pa : pb, cg1_trial ? 2 * sweep_blocks(sw) : nb_other, s);
+              launch_tune_selfred(h->cs2, pass ? pa : pb, nb_other, s);
               launch_delay(kTuneDelayUs, s);
             } else {
               launch_tune_state(h->cs2, first ? 0 : 1, s);
@@ -1888,11 +1966,6 @@ int excmg_autotune(excmg_handle *h, int32_t *zc_out, int32_t *depth_out) {
                 const TwoVecs<float> v = two_vecs32(h, l);
                 if (pass == 0) launch_two_g<float>(sw, v, h->cs2, h->partials, s);
                 else launch_two_u<float>(sw, v, h->cs2, h->partials, s);
-              } else if (cg1_trial) {  // u and p: the first two slots of p1's buffer (the grid's u may not be bound yet)
-                launch_cg1_iteration(sw, h->p1 + cg1_stride(lv), h->p1, cg1_vec(h, lv, 1, 0), cg1_vec(h, lv, 1, 1),
-                                     cg1_vec(h, lv, 1, 2), cg1_vec(h, lv, 0, 0), cg1_vec(h, lv, 0, 1),
-                                     cg1_vec(h, lv, 0, 2), h->cs2, 1, pa, cg1_resid_parts(h), sweep_blocks(lv.sw),
-                                     1.0, pb, s);
               } else if (burst && prec == 0) {
                 if (pass == 0) launch_selfred_a<double>(sw, h->r, h->p0, h->p1, h->cs2, pb, nb_other, 1.0, pa, s);
                 else launch_selfred_b<double>(sw, h->r, h->r, h->p0, h->p1, h->cs2, pa, nb_other, pb, s);
@@ -1933,7 +2006,6 @@ int excmg_autotune(excmg_handle *h, int32_t *zc_out, int32_t *depth_out) {
           if (two && depth > 3) continue;  // runs as 3
           if (two && pass == 0 && nt) continue;  // pass G touches every array with halos
           if (burst && !two && sweep_blocks(sw) > selfred_max_blocks()) continue;
-          if (cg1 && prec == 0 && pass == 1 && 4LL * sweep_blocks(sw) > lo.npart) continue;
           timed.push_back({trial(sw, 3), sw});
         }
         if (rc) break;

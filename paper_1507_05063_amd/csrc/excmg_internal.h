@@ -181,11 +181,10 @@ struct CgState {
   // inner solves) instead of the residual's partial sums.
   int iterA, iterB;
   int preset;
-  int pad_;
+  int abort;       // the resident CG: a workgroup gave up waiting for the others (nothing was written)
   double gbnd2;    // added to the squared norm of the stopping test: the sum of g^2 over the grid's boundary nodes
                    // under EXCMG_STOP_F_G, else 0 (set at setup and by boundary_g2_kernel)
   double rhoA[2];
-  double alphaA[2];  // the single-reduction CG: alpha of iteration k in slot k mod 2
   // The two-step sweeps (pass G sets the first four, pass U the others)
   double alpha1, beta0;  // the second iteration's step, and its beta
   int single;            // this pair makes one iteration only
@@ -244,6 +243,26 @@ void launch_probe_sweep(int mode, int u, bool nt, bool chunk, int wg_per_cu, con
 // one CG iteration with the reductions finalized inside the sweeps: pass A reads nb_prev partial sums from partsB
 // (the residual's [r.r | b.b] before iteration 0, pass B's r.r afterwards) and writes partsA; pass B reads nbA from
 // partsA and writes partsB
+// The resident CG (kernels_resident.hip): a brick shape on gx x gy x gz workgroups
+struct ResidentPlan {
+  int brick, gx, gy, gz, threads;  // threads 0: the grid does not fit
+  size_t lds;
+};
+ResidentPlan resident_plan(const Grid &g, int blocks);
+struct Resident {
+  Grid g;
+  double *u;
+  RhsSrc rs;
+  Stencil st;
+  CgState *cs;
+  double *scratch;  // the slots of the meetings and the packed x faces: an array in the grid's layout holds them
+  double *W0, *W1;  // published layers of w, in the grid's layout
+  double tol;
+  int cap, hist_on;
+  ResidentPlan plan;
+};
+void launch_resident(const Resident &a, hipStream_t st);
+
 // Vectors of the two-step sweeps (x in a layout gx of its own, the others in the sweep's)
 template <typename T>
 struct TwoVecs {
@@ -274,14 +293,6 @@ void launch_boundary_g2(const RhsSrc &rs, const Grid &g, CgState *cs, hipStream_
 // gbnd2 and count = 0 for each state (at setup)
 void launch_clear_state(CgState *a, CgState *b, hipStream_t st);
 // residual sweep writing [r.r | b.b] partials without a finalize (for the self-finalizing iterations)
-// The single-reduction CG of self-finalizing grids (kernels_cg.hip): the init sweep w = M r with the partial sums
-// of r.r and w.r into parts, and iteration k (launch parity par) from r, w, s into ro, wo, so (u, p in place), from
-// the partials of the previous launch (or the init's) and, at k = 0, the residual sweep's partsR (nbR workgroups);
-// both use sweep sw (depth 2 or 3).
-void launch_cg1_init(const Sweep &sw, const double *r, double *w, double *parts, hipStream_t st);
-void launch_cg1_iteration(const Sweep &sw, double *u, double *p, const double *r, const double *w, const double *s,
-                          double *ro, double *wo, double *so, CgState *cs, int par, const double *partsIn,
-                          const double *partsR, int nbR, double tol, double *partsOut, hipStream_t st);
 void launch_residual_partials(const Sweep &sw, const double *u, const RhsSrc &rs, double *r, double *parts,
                               hipStream_t st);
 

@@ -41,14 +41,6 @@ struct Two {
   static_assert(Ring <= NT, "one ring node per thread at most");
 };
 
-// a node of a plane by its byte offset there (32 bits: the launchers refuse larger planes), so that a load is one
-// uniform base and one 32-bit offset
-template <typename T>
-__device__ __forceinline__ T *at_byte(T *plane, unsigned off) {
-  return reinterpret_cast<T *>(reinterpret_cast<std::conditional_t<std::is_const_v<T>, const char, char> *>(plane) +
-                               off);
-}
-
 // T: precision; D: planes of loads in flight; FIRST: p = r (no p_old).  P: the policy of the pass: mid(m, k, on, idx,
 // r, p, q) at q's plane k (returns the staged second operand; on: an output node of the tile), fin(m, k, idx, c, t) at
 // an output node of plane k, two planes behind (c: the second operand there, t: M of it);
