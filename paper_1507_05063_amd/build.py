@@ -7,7 +7,7 @@ import tempfile
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libexcmg.so")
-SOURCES = ["excmg.hip", "kernels_cg.hip", "kernels_two.hip", "kernels_resident.hip", "kernels_transfer.hip", "kernels_grad.hip", "kernels_probe.hip"]
+SOURCES = ["excmg.hip", "kernels_cg.hip", "kernels_transfer.hip", "kernels_grad.hip", "kernels_probe.hip"]
 ARCH = "gfx950"
 
 FLAGS = [

@@ -23,6 +23,10 @@
 #include <vector>
 
 #include "excmg_internal.h"
+// The relaxations of the largest grids and of those that fit the chip are compiled with the driver: the other kernel
+// sources are translation units of their own, and the slowest of them (kernels_cg.hip) sets the build's time.
+#include "kernels_resident.hip"
+#include "kernels_two.hip"
 
 using namespace excmg;
 

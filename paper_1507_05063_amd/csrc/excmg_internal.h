@@ -240,9 +240,6 @@ void launch_probe_mix_nt(const double *a, double *b, double *c, long long n, hip
 void launch_probe_sweep(int mode, int u, bool nt, bool chunk, int wg_per_cu, const double *a, double *b, double *c,
                         long long n, double *sink, hipStream_t st);
 
-// one CG iteration with the reductions finalized inside the sweeps: pass A reads nb_prev partial sums from partsB
-// (the residual's [r.r | b.b] before iteration 0, pass B's r.r afterwards) and writes partsA; pass B reads nbA from
-// partsA and writes partsB
 // The resident CG (kernels_resident.hip): a brick shape on gx x gy x gz workgroups
 struct ResidentPlan {
   int brick, gx, gy, gz, threads;  // threads 0: the grid does not fit
