@@ -2178,7 +2178,7 @@ int excmg_op_apply(const int32_t n[3], const double box[3], const double *x, dou
     if (!(box[d] > 0.0)) return EXCMG_ERR_ARG;
   const hipStream_t s = (hipStream_t)hip_stream;
   const Grid g = dense_grid(n[0], n[1], n[2]);
-  HIPCHECK(hipMemsetAsync(y, 0, (size_t)g.elems * sizeof(double), s));
+  launch_zero_boundary(g, y, s);
   launch_apply(g, x, g, y, make_stencil(box[0] / n[0], box[1] / n[1], box[2] / n[2]), s);
   int e = last_error();
   if (e) return e;
@@ -2194,7 +2194,6 @@ int excmg_op_rhs(const int32_t n[3], const double box[3], const double *f, const
     if (!(box[d] > 0.0)) return EXCMG_ERR_ARG;
   const hipStream_t s = (hipStream_t)hip_stream;
   const Grid gd = dense_grid(n[0], n[1], n[2]);
-  HIPCHECK(hipMemsetAsync(b, 0, (size_t)gd.elems * sizeof(double), s));
   RhsSrc rs;
   rs.gf = gd;
   rs.f = f;

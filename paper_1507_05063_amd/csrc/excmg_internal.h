@@ -321,7 +321,11 @@ void launch_small_cg(const Grid &gu, double *u, const RhsSrc &rs, const Grid &gw
 // y = M x (interior of x only), y = 0 on the boundary
 void launch_apply(const Grid &gx, const double *x, const Grid &gy, double *y, const Stencil &s, hipStream_t st);
 
-// level data b (layout gb) on the interior, from rhs_at
+// A's couplings to the Dirichlet values at the outermost interior layer of g, into out there (nothing in mode 1)
+void launch_boundary_terms(const RhsSrc &rs, const Grid &g, double *out, hipStream_t st);
+// 0 on the boundary nodes of g
+void launch_zero_boundary(const Grid &g, double *u, hipStream_t st);
+// level data b (layout gb) on the interior, 0 on the boundary (mode 0)
 void launch_rhs(const RhsSrc &rs, const Grid &gb, double *b, hipStream_t st);
 // boundary nodes of u <- g (finest dense g sampled at stride s); interior set to 0 if zero_interior
 void launch_set_boundary(const Grid &gg, const double *g, int stride, const Grid &gu, double *u, int zero_interior,

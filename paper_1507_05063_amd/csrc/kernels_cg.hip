@@ -814,7 +814,8 @@ __device__ __forceinline__ void boundary_terms_block(const RhsSrc &rs, const Gri
 }
 
 __global__ __launch_bounds__(256) void boundary_terms_kernel(RhsSrc rs, Grid g, double *out) {
-  boundary_terms_block(rs, g, out, blockIdx.x, blockIdx.y, blockIdx.z);
+  const int gx = (max(g.nx, max(g.ny, g.nz)) - 1 + 255) / 256;
+  boundary_terms_block(rs, g, out, blockIdx.x % gx, blockIdx.x / gx, blockIdx.y);
 }
 
 // cs->gbnd2 = the sum of g^2 over the boundary nodes of grid g, the boundary half of the squared norm of the stopping
@@ -1623,10 +1624,10 @@ static void with_shape(const Sweep &sw, F &&f) {
   }
 }
 
-static void launch_boundary_terms(const RhsSrc &rs, const Grid &g, double *out, hipStream_t st) {
+void launch_boundary_terms(const RhsSrc &rs, const Grid &g, double *out, hipStream_t st) {
   if (rs.mode != 0) return;
   const int m = (g.nx > g.ny ? (g.nx > g.nz ? g.nx : g.nz) : (g.ny > g.nz ? g.ny : g.nz)) - 1;
-  dim3 grid((m + 255) / 256, m, 6);
+  dim3 grid((m + 255) / 256 * m, 6);
   boundary_terms_kernel<<<grid, 256, 0, st>>>(rs, g, out);
 }
 

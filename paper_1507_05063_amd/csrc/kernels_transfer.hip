@@ -5,6 +5,8 @@
 //   set_boundary, copy: layout and boundary helpers
 #include <math.h>
 
+#include <algorithm>
+
 #include "excmg_internal.h"
 
 namespace excmg {
@@ -16,13 +18,52 @@ __device__ __forceinline__ bool on_boundary(int i, int j, int k, int nx, int ny,
 }
 
 // ------------------------------------------------------------------------------------------------------------ rhs
-// One thread per interior node of the level grid gb (rhs_at: eq. compact with the Dirichlet values eliminated).
-__global__ void rhs_kernel(RhsSrc rs, Grid gb, double *__restrict__ b) {
-  const int i = 1 + blockIdx.x * blockDim.x + threadIdx.x;
-  const int j = 1 + blockIdx.y;
-  const int k = 1 + blockIdx.z;
-  if (i >= gb.nx) return;
-  b[gb.at(i, j, k)] = rhs_at(rs, gb.nx, gb.ny, gb.nz, i, j, k);
+// b = -R f + A_IB g on the interior of gb, 0 on its boundary.  One thread per column of kRz planes, f of three planes
+// in registers.  A's couplings to the Dirichlet values, which only the outermost interior layer has, are in b already
+// (launch_boundary_terms): formed here, they kept a row's first and last wavefront in a loop over 26 neighbours for two
+// lanes (117 us on 191 x 127 x 159 unknowns; now 27 us and 7 us for the boundary terms; the f read and b written alone
+// take 13 us).
+constexpr int kRz = 8;
+__global__ __launch_bounds__(256) void rhs_kernel(RhsSrc rs, Grid gb, double *__restrict__ b) {
+  const int i = blockIdx.x * 64 + (threadIdx.x & 63), j = blockIdx.y * 4 + (threadIdx.x >> 6), k0 = blockIdx.z * kRz;
+  if (i > gb.nx || j > gb.ny) return;
+  const int k1 = min(k0 + kRz, gb.nz + 1);
+  const bool edge = i == 0 || j == 0 || i == gb.nx || j == gb.ny;
+  const bool rim = i == 1 || j == 1 || i == gb.nx - 1 || j == gb.ny - 1;
+  const long long sx = rs.s, sy = rs.s * rs.gf.sy, sz = rs.s * rs.gf.sz;
+  const double *f = rs.f + rs.gf.at(i * rs.s, j * rs.s, 0);
+  double fm = 0.0, fc = 0.0, fp = 0.0;
+  if (!edge) {
+    fm = f[max(k0 - 1, 0) * sz];
+    fc = f[k0 * sz];
+  }
+  for (int k = k0; k < k1; ++k) {
+    double *out = &b[gb.at(i, j, k)];
+    if (edge || k == 0 || k == gb.nz) {
+      *out = 0.0;
+      if (!edge) fp = f[min(k + 1, gb.nz) * sz];
+    } else {
+      const double *c = f + k * sz;
+      fp = c[sz];
+      const double rf = 0.5 * (6.0 * fc + (c[sx] + c[-sx]) + (c[sy] + c[-sy]) + (fp + fm));
+      *out = (rim || k == 1 || k == gb.nz - 1) ? -rf + *out : -rf;
+    }
+    fm = fc;
+    fc = fp;
+  }
+}
+
+// 0 on the boundary nodes of g (layer: x = 0, x = nx, y = 0, ...)
+__global__ __launch_bounds__(256) void zero_boundary_kernel(Grid g, double *__restrict__ u) {
+  const int layer = blockIdx.y;
+  const int na = layer < 2 ? g.ny : g.nx, nb = layer < 4 ? g.nz : g.ny;
+  const long long e = (long long)blockIdx.x * 256 + threadIdx.x;
+  const int a = (int)(e % (na + 1)), b = (int)(e / (na + 1));
+  if (b > nb) return;
+  const int far = layer & 1;
+  if (layer < 2) u[g.at(far ? g.nx : 0, a, b)] = 0.0;
+  else if (layer < 4) u[g.at(a, far ? g.ny : 0, b)] = 0.0;
+  else u[g.at(a, b, far ? g.nz : 0)] = 0.0;
 }
 
 // Node-wise kernels run 256 threads per workgroup over (x segment, y, z) = (bx, j, k).
@@ -357,30 +398,59 @@ __global__ __launch_bounds__(TTX *TTY) void exp_true_kernel(Grid gh, const doubl
 }
 
 // ------------------------------------------------------------------------------------------------------- adjoint
-// Gather form of the transposes, one thread per node of the finest grid (dense outputs):
+// Gather form of the transposes on the finest grid (dense outputs):
 //   dLdf(n) = -(3 lam_n [n interior] + 1/2 * sum of lam over the interior face neighbours of n)
 //   dLdg(n) = sum over interior neighbours m of A's coefficient for the offset m - n, times lam_m, plus G(n),
 //             on boundary nodes; 0 inside.
-__global__ void adjoint_kernel(Grid gl, const double *__restrict__ lam, Grid gd, const double *__restrict__ G,
-                               double *__restrict__ dLdf, double *__restrict__ dLdg, double a, double bb, double c) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  const int j = blockIdx.y;
-  const int k = blockIdx.z;
-  const int nx = gl.nx, ny = gl.ny, nz = gl.nz;
-  if (i > nx) return;
-  auto L = [&](int ii, int jj, int kk) -> double {
-    if (ii <= 0 || jj <= 0 || kk <= 0 || ii >= nx || jj >= ny || kk >= nz) return 0.0;
-    return lam[gl.at(ii, jj, kk)];
-  };
-  const double rt = 3.0 * L(i, j, k) +
-                    0.5 * ((L(i + 1, j, k) + L(i - 1, j, k)) + (L(i, j + 1, k) + L(i, j - 1, k)) +
-                           (L(i, j, k + 1) + L(i, j, k - 1)));
-  const long long q = gd.at(i, j, k);
-  dLdf[q] = -rt;
-  if (!on_boundary(i, j, k, nx, ny, nz)) {
-    dLdg[q] = 0.0;
-    return;
+// One thread per column of kRz planes with lam of three planes in registers; the couplings of the boundary nodes, a
+// loop over 18 neighbours, run in a kernel of their own over the six faces (within one kernel they held up every row's
+// first and last wavefront: 270 us at 256^3, 133 us now; lam read and both outputs written alone take 82 us).
+__device__ __forceinline__ double lam_at(const Grid &g, const double *lam, int i, int j, int k) {
+  if (i <= 0 || j <= 0 || k <= 0 || i >= g.nx || j >= g.ny || k >= g.nz) return 0.0;
+  return lam[g.at(i, j, k)];
+}
+
+// dLdf on every node, and dLdg = 0 inside
+__global__ __launch_bounds__(256) void adjoint_kernel(Grid gl, const double *__restrict__ lam, Grid gd,
+                                                      double *__restrict__ dLdf, double *__restrict__ dLdg) {
+  const int i = blockIdx.x * 64 + (threadIdx.x & 63), j = blockIdx.y * 4 + (threadIdx.x >> 6), k0 = blockIdx.z * kRz;
+  if (i > gl.nx || j > gl.ny) return;
+  const int k1 = min(k0 + kRz, gl.nz + 1);
+  const bool edge = i == 0 || j == 0 || i == gl.nx || j == gl.ny;
+  double lm = lam_at(gl, lam, i, j, k0 - 1), lc = lam_at(gl, lam, i, j, k0);
+  for (int k = k0; k < k1; ++k) {
+    const double lp = lam_at(gl, lam, i, j, k + 1);
+    const double rt = 3.0 * lc + 0.5 * ((lam_at(gl, lam, i + 1, j, k) + lam_at(gl, lam, i - 1, j, k)) +
+                                        (lam_at(gl, lam, i, j + 1, k) + lam_at(gl, lam, i, j - 1, k)) + (lp + lm));
+    const long long q = gd.at(i, j, k);
+    __builtin_nontemporal_store(-rt, &dLdf[q]);
+    if (!edge && k > 0 && k < gl.nz) __builtin_nontemporal_store(0.0, &dLdg[q]);
+    lm = lc;
+    lc = lp;
   }
+}
+
+// dLdg on the boundary nodes; layers as in zero_boundary_kernel, every node in the first layer that holds it
+__global__ __launch_bounds__(256) void adjoint_boundary_kernel(Grid gl, const double *__restrict__ lam, Grid gd,
+                                                               const double *G, double *dLdg, double a, double bb,
+                                                               double c) {
+  const int layer = blockIdx.y;
+  const int np = layer < 2 ? gl.ny : gl.nx, nq = layer < 4 ? gl.nz : gl.ny;
+  const long long e = (long long)blockIdx.x * 256 + threadIdx.x;
+  const int p = (int)(e % (np + 1)), q = (int)(e / (np + 1));
+  if (q > nq) return;
+  const bool far = layer & 1;
+  int i, j, k;
+  if (layer < 2) {
+    i = far ? gl.nx : 0; j = p; k = q;
+  } else if (layer < 4) {
+    i = p; j = far ? gl.ny : 0; k = q;
+    if (i == 0 || i == gl.nx) return;
+  } else {
+    i = p; j = q; k = far ? gl.nz : 0;
+    if (i == 0 || i == gl.nx || j == 0 || j == gl.ny) return;
+  }
+  auto L = [&](int ii, int jj, int kk) { return lam_at(gl, lam, ii, jj, kk); };
   const double fx = 4.0 * a - bb - c, fy = 4.0 * bb - a - c, fz = 4.0 * c - a - bb;
   const double exy = 0.5 * (a + bb), exz = 0.5 * (a + c), eyz = 0.5 * (bb + c);
   double s = fx * (L(i + 1, j, k) + L(i - 1, j, k)) + fy * (L(i, j + 1, k) + L(i, j - 1, k)) +
@@ -388,7 +458,8 @@ __global__ void adjoint_kernel(Grid gl, const double *__restrict__ lam, Grid gd,
   s += exy * ((L(i + 1, j + 1, k) + L(i - 1, j + 1, k)) + (L(i + 1, j - 1, k) + L(i - 1, j - 1, k)));
   s += exz * ((L(i + 1, j, k + 1) + L(i - 1, j, k + 1)) + (L(i + 1, j, k - 1) + L(i - 1, j, k - 1)));
   s += eyz * ((L(i, j + 1, k + 1) + L(i, j - 1, k + 1)) + (L(i, j + 1, k - 1) + L(i, j - 1, k - 1)));
-  dLdg[q] = s + G[q];
+  const long long m = gd.at(i, j, k);
+  dLdg[m] = s + G[m];
 }
 
 // ---------------------------------------------------------------------------------------------------- batched form
@@ -431,13 +502,23 @@ __global__ __launch_bounds__(ET) void b_exp_finite_kernel(BatchList L) {
                    false);
 }
 
+// workgroups of 256 for the nodes of the largest face
+inline int face_blocks(const Grid &g) {
+  const long long x = g.nx + 1, y = g.ny + 1, z = g.nz + 1;
+  return (int)((std::max(x * y, std::max(x * z, y * z)) + 255) / 256);
+}
 inline dim3 node_grid(const Grid &g, int bx) { return dim3((g.nx + 1 + bx - 1) / bx, g.ny + 1, g.nz + 1); }
-inline dim3 interior_grid(const Grid &g, int bx) { return dim3((g.nx - 1 + bx - 1) / bx, g.ny - 1, g.nz - 1); }
 
 }  // namespace
 
 void launch_rhs(const RhsSrc &rs, const Grid &gb, double *b, hipStream_t st) {
-  rhs_kernel<<<interior_grid(gb, 256), 256, 0, st>>>(rs, gb, b);
+  launch_boundary_terms(rs, gb, b, st);
+  dim3 grid(gb.nx / 64 + 1, gb.ny / 4 + 1, gb.nz / kRz + 1);
+  rhs_kernel<<<grid, 256, 0, st>>>(rs, gb, b);
+}
+
+void launch_zero_boundary(const Grid &g, double *u, hipStream_t st) {
+  zero_boundary_kernel<<<dim3(face_blocks(g), 6), 256, 0, st>>>(g, u);
 }
 
 void launch_set_boundary(const Grid &gg, const double *g, int stride, const Grid &gu, double *u, int zero_interior,
@@ -476,8 +557,10 @@ void launch_check_finite(const double *a, long long n, int *flag, hipStream_t st
 
 void launch_adjoint_transposes(const Grid &gl, const double *lam, const Grid &gd, const double *G, double *dLdf,
                                double *dLdg, double hx, double hy, double hz, hipStream_t st) {
-  adjoint_kernel<<<node_grid(gl, 256), 256, 0, st>>>(gl, lam, gd, G, dLdf, dLdg, 1.0 / (hx * hx), 1.0 / (hy * hy),
-                                                     1.0 / (hz * hz));
+  // (the boundary first: it reads G, which dLdf or dLdg may lie over)
+  adjoint_boundary_kernel<<<dim3(face_blocks(gl), 6), 256, 0, st>>>(gl, lam, gd, G, dLdg, 1.0 / (hx * hx),
+                                                                       1.0 / (hy * hy), 1.0 / (hz * hz));
+  adjoint_kernel<<<dim3(gl.nx / 64 + 1, gl.ny / 4 + 1, gl.nz / kRz + 1), 256, 0, st>>>(gl, lam, gd, dLdf, dLdg);
 }
 
 int b_blocks_nodes(const Grid &g) { return ((g.nx + 1 + 255) / 256) * (g.ny + 1) * (g.nz + 1); }
