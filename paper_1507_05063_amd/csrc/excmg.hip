@@ -23,10 +23,12 @@
 #include <vector>
 
 #include "excmg_internal.h"
-// The relaxations of the largest grids and of those that fit the chip are compiled with the driver: the other kernel
-// sources are translation units of their own, and the slowest of them (kernels_cg.hip) sets the build's time.
+// The relaxations of the largest grids and of those that fit the chip, and the direct solve, are compiled with the
+// driver: the other kernel sources are translation units of their own, and the slowest of them (kernels_cg.hip) sets
+// the build's time.
 #include "kernels_resident.hip"
 #include "kernels_two.hip"
+#include "kernels_direct.hip"
 
 using namespace excmg;
 
@@ -141,8 +143,12 @@ int guess_kind(uint32_t flags) {
 // costs would sit between the timed kernels).  Results are read on the host only after a stream synchronization.
 constexpr unsigned kTimingEvent = hipEventDisableSystemFence;
 
-// bytes of a CG state that the host reads after a solve (everything but the history)
-constexpr size_t kStateHead = offsetof(CgState, hist);
+// the workspace's share of a grid's outcome
+constexpr size_t kDeferBytes = 144;
+static_assert(sizeof(Outcome) <= kDeferBytes, "a deferred outcome");
+// the outcomes' place in the pinned memory, past a whole CG state, and what a handle pins
+constexpr size_t kPinOutcomes = 4096, kPinBytes = 8192;
+static_assert(sizeof(CgState) <= kPinOutcomes && EXCMG_MAX_LEVELS * sizeof(Outcome) <= kPinBytes - kPinOutcomes, "pinned");
 
 // The two-step sweeps relax the grids above this size.  On smaller grids a step of the march, about 1.4 us whatever the grid, outweighs the bytes saved: at 127^3 unknowns a
 // pair takes 64 us, four self-finalizing sweeps 62 us.
@@ -212,7 +218,7 @@ int make_layout(const excmg_problem *p, Layout *Lo) {
   Lo->off_part = off; off = align256(off + 2 * (size_t)Lo->npart * sizeof(double));  // two halves: A and B
   Lo->off_cs = off; off = align256(off + sizeof(CgState));
   Lo->off_cs2 = off; off = align256(off + sizeof(CgState));
-  Lo->off_defer = off; off = align256(off + EXCMG_MAX_LEVELS * kStateHead);
+  Lo->off_defer = off; off = align256(off + EXCMG_MAX_LEVELS * kDeferBytes);
   for (int d = 0; d < 3; ++d) {
     Lo->off_invm[d] = off;
     off = align256(off + (size_t)(fin.n[d] + 1) * sizeof(double));
@@ -246,7 +252,7 @@ struct excmg_handle {
   float *r32, *p32a, *p32b, *d32;
   double *partials;
   CgState *cs, *cs2;
-  char *defer_dev;  // per grid, the CG state (without its history) of a one-launch solve, read after the cascade
+  char *defer_dev;  // per grid, the outcome of a one-launch solve of a handle without pinned memory
   double *inv_m[3];
   int *flag;
   std::vector<double> inv_m_host[3];
@@ -395,6 +401,13 @@ int read_state(excmg_handle *h, CgState *dst, const CgState *src) {
 
 int read_hist(excmg_handle *h, CgState *dst, const CgState *src) { return read_record(h, dst, src, sizeof(CgState)); }
 
+// Where the device writes the outcome of grid l's one-launch solve: pinned host memory that the host reads once the
+// stream is idle, or the workspace.
+Outcome *outcome_slot(excmg_handle *h, int l) {
+  char *base = h->noalloc ? h->defer_dev : (char *)h->pin_dev + kPinOutcomes;
+  return (Outcome *)base + l;
+}
+
 // Per-level iteration counts of CG-class timed launches, to drop launches made after convergence.
 // (launches: the CG iterations, or the pairs where the two-step sweeps make them)
 struct LevelIters {
@@ -470,6 +483,8 @@ TwoVecs<float> two_vecs32(const excmg_handle *h, int l) {
   return {h->d32, h->r32, h->p32a, h->p32b, (float *)h->p0, h->lo.lev[l].g32};
 }
 
+bool overlap(const double *a, long long na, const double *b, long long nb) { return a < b + nb && b < a + na; }
+
 // An output array of the call (a dense node array of the finest grid) as the finest grid's fourth vector: its
 // interior nodes packed in rows of the widest alignment that fits the array.  avoid: an input of the call that is read
 // after the sweeps (null: none); an output that overlaps it is not used.
@@ -477,7 +492,7 @@ void bind_output(excmg_handle *h, double *out, const double *avoid) {
   const Grid &d = h->lo.gdense;
   const long long nodes = d.nodes();
   if (!out || h->xfin) return;
-  if (avoid && out < avoid + nodes && avoid < out + nodes) return;
+  if (avoid && overlap(out, nodes, avoid, nodes)) return;
   const long long lead = (long long)(((128 - ((uintptr_t)out & 127)) & 127) / sizeof(double));
   for (int a = 16; a >= 1; a /= 2) {
     Grid x;
@@ -747,7 +762,8 @@ int cg_ir(excmg_handle *h, int l, const RhsSrc &rs, bool finest, int *iters, int
 // at most kSmallCg unknowns.
 // The outcome of a one-launch solve of grid l from its CG state hs: iterations and relative residual into the stats,
 // and its status.
-int small_cg_outcome(const CgState &hs, int l, bool exact, int *iters, double *relres, excmg_stats *st) {
+template <typename State>
+int small_cg_outcome(const State &hs, int l, bool exact, int *iters, double *relres, excmg_stats *st) {
   if (exact && st && l < 2) st->dsolve_iters[l] = hs.iter;
   *iters = exact ? 0 : hs.iter;
   *relres = hs.bnorm2 > 0.0 ? sqrt(hs.rho / hs.bnorm2) : 0.0;
@@ -755,9 +771,8 @@ int small_cg_outcome(const CgState &hs, int l, bool exact, int *iters, double *r
   return hs.status;
 }
 
-// defer: nothing on the host waits for this grid's outcome (it is not the finest): its state is copied on the device
-// to the grid's slot of defer_dev, which the cascade reads once at its end, so the stream runs on to the next grid
-// without a round trip to the host.
+// defer: nothing on the host waits for this grid's outcome: it goes to the grid's outcome slot, which the cascade reads
+// once at its end, so the stream runs on to the next grid without a round trip to the host.
 int small_cg(excmg_handle *h, int l, const RhsSrc &rs, bool exact, bool finest, int *iters, double *relres,
              excmg_stats *st, bool defer = false) {
   Level &lv = h->lo.lev[l];
@@ -771,7 +786,7 @@ int small_cg(excmg_handle *h, int l, const RhsSrc &rs, bool exact, bool finest, 
   int e = last_error();
   if (e) return e;
   if (defer && !hist_on) {
-    launch_publish(h->cs, h->defer_dev + (size_t)l * kStateHead, kStateHead, h->stream);
+    launch_outcome(h->cs, outcome_slot(h, l), h->stream);
     *iters = 0;
     *relres = 0.0;
     return last_error();
@@ -832,24 +847,33 @@ struct ResidentCall {
 // the sweeps).
 constexpr int kGaveUp = -1001;
 
-// The resident CG of grid l from the current u, in one launch (defer: as small_cg).
-int resident_cg(excmg_handle *h, int l, const RhsSrc &rs, bool finest, int *iters, double *relres, excmg_stats *st,
-                bool defer) {
-  Level &lv = h->lo.lev[l];
-  const int hist_on = (finest && st && (h->p.flags & EXCMG_WANT_HISTORY)) ? 1 : 0;
+// Whether the resident CG leaves grid l's outcome to the cascade's end: always, but for a history to read.
+bool resident_defers(const excmg_handle *h, int l, const excmg_stats *st) {
+  return l < h->lo.L - 1 || !(st && (h->p.flags & EXCMG_WANT_HISTORY));
+}
+
+Resident resident_args(excmg_handle *h, int l, const RhsSrc &rs, const excmg_stats *st) {
+  const Level &lv = h->lo.lev[l];
   Resident a;
   a.g = lv.g;
   a.u = lv.u;
   a.rs = rs;
   a.st = lv.st;
   a.cs = h->cs;
+  a.out = resident_defers(h, l, st) ? outcome_slot(h, l) : nullptr;
   a.scratch = h->p1;
   a.W0 = h->r;
   a.W1 = h->p0;
   a.tol = grid_tol(h->p, l, h->lo.L);
   a.cap = grid_cap(h, l);
-  a.hist_on = hist_on;
+  a.hist_on = resident_defers(h, l, st) ? 0 : 1;
   a.plan = lv.res;
+  return a;
+}
+
+// The resident CG of grid l from the current u, in one launch (the grid's initial guess has set its slots).
+int resident_cg(excmg_handle *h, int l, const RhsSrc &rs, int *iters, double *relres, excmg_stats *st) {
+  const Resident a = resident_args(h, l, rs, st);
   {
     Tick t(h, EXCMG_K_CG_A, l, kResidentTick);
     ResidentTurn &turn = g_resident[h->device];
@@ -859,23 +883,45 @@ int resident_cg(excmg_handle *h, int l, const RhsSrc &rs, bool finest, int *iter
     launch_resident(a, h->stream);
   }
   int e = last_error();
-  if (e) return e;
-  if (defer) {
-    launch_publish(h->cs, h->defer_dev + (size_t)l * kStateHead, kStateHead, h->stream);
-    *iters = 0;
-    *relres = 0.0;
-    return last_error();
-  }
+  *iters = 0;
+  *relres = 0.0;
+  if (e || a.out) return e;
   CgState hs;
-  e = hist_on ? read_hist(h, &hs, h->cs) : read_state(h, &hs, h->cs);
+  e = read_hist(h, &hs, h->cs);
   if (e) return e;
   if (hs.abort) return kGaveUp;
-  if (hist_on) {
-    const int n = hs.iter + 1 < EXCMG_MAX_HISTORY ? hs.iter + 1 : EXCMG_MAX_HISTORY;
-    st->history_len = n;
-    for (int q = 0; q < n; ++q) st->history[q] = hs.hist[q];
-  }
+  const int n = hs.iter + 1 < EXCMG_MAX_HISTORY ? hs.iter + 1 : EXCMG_MAX_HISTORY;
+  st->history_len = n;
+  for (int q = 0; q < n; ++q) st->history[q] = hs.hist[q];
   return small_cg_outcome(hs, l, false, iters, relres, st);
+}
+
+// DSOLVE of grid l (0 or 1) by sine transforms, with its boundary values; defer: as small_cg.
+int direct_solve(excmg_handle *h, int l, const RhsSrc &rs, const double *gdat, bool defer, double *relres,
+                 excmg_stats *st) {
+  Level &lv = h->lo.lev[l];
+  Direct a;
+  a.g = lv.g;
+  a.u = lv.u;
+  a.rs = rs;
+  a.gdat = gdat;
+  a.st = lv.st;
+  a.cs = h->cs;
+  a.out = defer ? outcome_slot(h, l) : nullptr;
+  a.A = h->r;
+  a.B = h->p0;
+  a.parts = h->partials;
+  {
+    Tick t(h, EXCMG_K_DSOLVE, l);
+    launch_direct(a, h->stream);
+  }
+  int e = last_error();
+  *relres = 0.0;
+  if (e || defer) return e;
+  CgState hs;
+  e = read_state(h, &hs, h->cs);
+  int iters = 0;
+  return e ? e : small_cg_outcome(hs, l, true, &iters, relres, st);
 }
 
 // Kernel timing on or off; the event pool is created the first time it is turned on.
@@ -970,7 +1016,10 @@ void bind_workspace(excmg_handle *h) {
 }
 
 // The cascade shared by the solve and the adjoint.  mode 0: level data from (f, g); mode 1: from G, zero boundary.
-int cascade(excmg_handle *h, int mode, const double *f, const double *g, excmg_stats *st, LevelIters *li) {
+// finish: launches what follows on the finest grid's solution; called before the host waits for the outcomes.
+template <typename Finish>
+int cascade(excmg_handle *h, int mode, const double *f, const double *g, excmg_stats *st, LevelIters *li,
+            Finish &&finish) {
   Layout &lo = h->lo;
   const int L = lo.L;
   const hipStream_t s = h->stream;
@@ -982,13 +1031,17 @@ int cascade(excmg_handle *h, int mode, const double *f, const double *g, excmg_s
     int nd = 0;
     for (int l = 0; l < upto; ++l) nd = deferred[l] ? l + 1 : nd;
     if (nd == 0) return EXCMG_OK;
-    std::vector<char> buf((size_t)nd * kStateHead);
-    int e = read_record(h, buf.data(), h->defer_dev, buf.size());
-    if (e) return e;
+    Outcome buf[EXCMG_MAX_LEVELS];
+    int e = EXCMG_OK;
+    if (h->noalloc) {
+      if ((e = read_record(h, buf, h->defer_dev, nd * sizeof(Outcome)))) return e;
+    } else {
+      HIPCHECK(hipStreamSynchronize(s));
+      memcpy(buf, (const char *)h->pin_host + kPinOutcomes, nd * sizeof(Outcome));
+    }
     for (int l = 0; l < nd; ++l) {
       if (!deferred[l]) continue;
-      CgState hs;
-      memcpy(&hs, buf.data() + (size_t)l * kStateHead, kStateHead);
+      const Outcome &hs = buf[l];
       if (hs.abort) return kGaveUp;
       const bool exact = l <= 1;
       int it = 0;
@@ -1031,7 +1084,14 @@ int cascade(excmg_handle *h, int mode, const double *f, const double *g, excmg_s
     int it = 0, outer = 0, dit = 0;
     double rr = 0.0;
     h->two_pairs = 0;
-    if (l <= 1) {
+    if (l <= 1 && dst_fits(lv.g)) {
+      deferred[l] = l < L - 1;
+      e = direct_solve(h, l, rs, mode == 0 ? g : nullptr, deferred[l], &rr, st);
+      if (e && e != EXCMG_ERR_NOCONV) {
+        const int d = resolve(l);  // an error of an earlier grid comes first
+        return d ? d : e;
+      }
+    } else if (l <= 1) {
       {
         Tick t(h, EXCMG_K_OTHER, l);
         launch_set_boundary(lo.gdense, mode == 0 ? g : nullptr, lv.stride, lv.g, lv.u, 1, s);
@@ -1051,16 +1111,18 @@ int cascade(excmg_handle *h, int mode, const double *f, const double *g, excmg_s
         return d ? d : e;
       }
     } else {
+      const bool resident = lv.res.threads && !h->apart;
       {
         Tick t(h, EXCMG_K_EXP_FINITE, l);
         launch_initial_guess(guess_kind(h->p.flags), lo.lev[l - 1].g, lo.lev[l - 1].u, lo.lev[l - 2].g,
-                             lo.lev[l - 2].u, lo.gdense, mode == 0 ? g : nullptr, lv.stride, lv.g, lv.u, s);
+                             lo.lev[l - 2].u, lo.gdense, mode == 0 ? g : nullptr, lv.stride, lv.g, lv.u,
+                             resident ? resident_init(resident_args(h, l, rs, st)) : ResidentInit{}, s);
       }
       e = last_error();
       if (e) return e;
-      if (lv.res.threads && !h->apart) {
-        deferred[l] = l < L - 1;
-        e = resident_cg(h, l, rs, l == L - 1, &it, &rr, st, deferred[l]);
+      if (resident) {
+        deferred[l] = resident_defers(h, l, st);
+        e = resident_cg(h, l, rs, &it, &rr, st);
       } else if (!swept(lo, l)) {
         deferred[l] = l < L - 1;
         e = small_cg(h, l, rs, false, l == L - 1, &it, &rr, st, deferred[l]);
@@ -1086,7 +1148,9 @@ int cascade(excmg_handle *h, int mode, const double *f, const double *g, excmg_s
     }
   }
   if (h->lev_ev[L]) HIPCHECK(hipEventRecord(h->lev_ev[L], s));
-  const int e = resolve(L);
+  finish();
+  int e = last_error();
+  if (!e) e = resolve(L);
   return e ? e : final_status;
 }
 
@@ -1096,9 +1160,11 @@ void clear_stats(excmg_stats *st) {
 
 // The cascade, once more without the resident CG if a workgroup of it gave up waiting for the others (which takes
 // another process holding CUs for about a second).
-int run_cascade(excmg_handle *h, int mode, const double *f, const double *g, excmg_stats *st, LevelIters *li) {
+template <typename Finish>
+int run_cascade(excmg_handle *h, int mode, const double *f, const double *g, excmg_stats *st, LevelIters *li,
+                Finish &&finish) {
   ResidentCall call{h};
-  int e = cascade(h, mode, f, g, st, li);
+  int e = cascade(h, mode, f, g, st, li, finish);
   if (e != kGaveUp) return e;
   HIPCHECK(hipStreamSynchronize(h->stream));
   clear_stats(st);
@@ -1106,7 +1172,7 @@ int run_cascade(excmg_handle *h, int mode, const double *f, const double *g, exc
   if (li) *li = LevelIters{};
   launch_clear_state(h->cs, h->cs2, h->stream);
   h->apart = true;
-  e = cascade(h, mode, f, g, st, li);
+  e = cascade(h, mode, f, g, st, li, finish);
   h->apart = false;
   return e;
 }
@@ -1761,7 +1827,7 @@ int excmg_setup(const excmg_problem *p, void *workspace, size_t bytes, void *hip
       return EXCMG_ERR_HIP;
     }
   }
-  if (ensure_pinned(h, sizeof(CgState)) != EXCMG_OK ||
+  if (ensure_pinned(h, kPinBytes) != EXCMG_OK ||
       hipStreamCreateWithFlags(&h->cap, hipStreamNonBlocking) != hipSuccess) {
     delete h;
     return EXCMG_ERR_HIP;
@@ -1822,22 +1888,35 @@ int solve_on(excmg_handle *h, const double *f, const double *g, double *u, doubl
   LevelIters li;
   memset(li.iters, 0, sizeof(li.iters));
   memset(li.launches, 0, sizeof(li.launches));
-  OutputBinding binding{h};
-  bind_output(h, u, nullptr);  // (f and g are last read by the finest grid's residual, before the sweeps)
-  const int status = run_cascade(h, 0, f, g, st, h->noalloc ? nullptr : &li);
-  if (status != EXCMG_OK && status != EXCMG_ERR_NOCONV) return status;
   Layout &lo = h->lo;
   const Level &fin = lo.lev[lo.L - 1];
-  if (u_ext) {  // EXP_true also writes u to the caller's array from the same read of u_h
-    Tick t(h, EXCMG_K_EXP_TRUE, lo.L - 1);
-    launch_exp_true(fin.g, fin.u, lo.lev[lo.L - 2].g, lo.lev[lo.L - 2].u, lo.gdense, u_ext, u, h->stream);
-  } else {
-    Tick t(h, EXCMG_K_OTHER, lo.L - 1);
-    launch_copy(fin.g, fin.u, lo.gdense, u, h->stream);
+  // An output over f or g is written only once the cascade has ended well: one that starts over reads them again.
+  const long long nodes = lo.gdense.nodes();
+  auto over = [&](const double *in) {
+    return overlap(u, nodes, in, nodes) || (u_ext && overlap(u_ext, nodes, in, nodes));
+  };
+  const bool late = over(f) || over(g);
+  OutputBinding binding{h};
+  if (!late) bind_output(h, u, nullptr);
+  auto finish = [&]() {
+    if (u_ext) {  // EXP_true also writes u to the caller's array from the same read of u_h
+      Tick t(h, EXCMG_K_EXP_TRUE, lo.L - 1);
+      launch_exp_true(fin.g, fin.u, lo.lev[lo.L - 2].g, lo.lev[lo.L - 2].u, lo.gdense, u_ext, u, h->stream);
+    } else {
+      Tick t(h, EXCMG_K_OTHER, lo.L - 1);
+      launch_copy(fin.g, fin.u, lo.gdense, u, h->stream);
+    }
+  };
+  const int status = run_cascade(h, 0, f, g, st, h->noalloc ? nullptr : &li, [&]() {
+    if (!late) finish();
+  });
+  int e = status != EXCMG_OK && status != EXCMG_ERR_NOCONV ? status : EXCMG_OK;
+  if (!e && late) {
+    finish();
+    e = last_error();
   }
-  int e = last_error();
+  HIPCHECK(hipStreamSynchronize(h->stream));  // also on an error: nothing of the call is left running
   if (e) return e;
-  HIPCHECK(hipStreamSynchronize(h->stream));
   fill_level_stats(h, st);
   e = collect_timing(h, st, li);
   if (e) return e;
@@ -1884,15 +1963,26 @@ int excmg_adjoint(excmg_handle *h, const double *G, double *dLdf, double *dLdg, 
   OutputBinding binding{h};
   bind_output(h, dLdf, G);
   bind_output(h, dLdg, G);
-  const int status = run_cascade(h, 1, G, nullptr, st, &li);
-  if (status != EXCMG_OK && status != EXCMG_ERR_NOCONV) return status;
   Layout &lo = h->lo;
   const Level &fin = lo.lev[lo.L - 1];
-  launch_adjoint_transposes(fin.g, fin.u, lo.gdense, G, dLdf, dLdg, fin.h[0], fin.h[1], fin.h[2], h->stream);
-  if (lambda_out) launch_copy(fin.g, fin.u, lo.gdense, lambda_out, h->stream);
-  int e = last_error();
+  // (an output over G: as in solve_on)
+  const long long nodes = lo.gdense.nodes();
+  auto over = [&](const double *out) { return out && overlap(out, nodes, G, nodes); };
+  const bool late = over(dLdf) || over(dLdg) || over(lambda_out);
+  auto finish = [&]() {
+    launch_adjoint_transposes(fin.g, fin.u, lo.gdense, G, dLdf, dLdg, fin.h[0], fin.h[1], fin.h[2], h->stream);
+    if (lambda_out) launch_copy(fin.g, fin.u, lo.gdense, lambda_out, h->stream);
+  };
+  const int status = run_cascade(h, 1, G, nullptr, st, &li, [&]() {
+    if (!late) finish();
+  });
+  int e = status != EXCMG_OK && status != EXCMG_ERR_NOCONV ? status : EXCMG_OK;
+  if (!e && late) {
+    finish();
+    e = last_error();
+  }
+  HIPCHECK(hipStreamSynchronize(h->stream));  // also on an error: nothing of the call is left running
   if (e) return e;
-  HIPCHECK(hipStreamSynchronize(h->stream));
   fill_level_stats(h, st);
   e = collect_timing(h, st, li);
   if (e) return e;
@@ -2219,7 +2309,7 @@ int excmg_op_exp_finite(const int32_t n[3], const double *u2h, const double *u4h
   const Grid gw = dense_grid(n[0], n[1], n[2]);
   const Grid g2 = dense_grid(n[0] / 2, n[1] / 2, n[2] / 2);
   const Grid g4 = dense_grid(n[0] / 4, n[1] / 4, n[2] / 4);
-  launch_initial_guess(kGuessQuartic, g2, u2h, g4, u4h, gw, g, 1, gw, w, s);
+  launch_initial_guess(kGuessQuartic, g2, u2h, g4, u4h, gw, g, 1, gw, w, ResidentInit{}, s);
   int e = last_error();
   if (e) return e;
   HIPCHECK(hipStreamSynchronize(s));
@@ -2235,7 +2325,7 @@ int excmg_op_initial_guess(int32_t kind, const int32_t n[3], const double *u2h, 
   const Grid gw = dense_grid(n[0], n[1], n[2]);
   const Grid g2 = dense_grid(n[0] / 2, n[1] / 2, n[2] / 2);
   const Grid g4 = dense_grid(n[0] / 4, n[1] / 4, n[2] / 4);
-  launch_initial_guess(kind, g2, u2h, g4, u4h, gw, g, 1, gw, w, s);
+  launch_initial_guess(kind, g2, u2h, g4, u4h, gw, g, 1, gw, w, ResidentInit{}, s);
   int e = last_error();
   if (e) return e;
   HIPCHECK(hipStreamSynchronize(s));

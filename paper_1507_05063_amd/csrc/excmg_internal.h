@@ -240,6 +240,30 @@ void launch_probe_mix_nt(const double *a, double *b, double *c, long long n, hip
 void launch_probe_sweep(int mode, int u, bool nt, bool chunk, int wg_per_cu, const double *a, double *b, double *c,
                         long long n, double *sink, hipStream_t st);
 
+// a slot of the resident CG's meetings that has not been written: a quiet NaN with a payload of its own
+constexpr unsigned long long kMissingSlot = 0x7ff8dead0badf00dull;
+
+// What a grid solved in one launch leaves for the host to read after the cascade.
+struct Outcome {
+  double rho, rho0, bnorm2;
+  int iter, status;
+  int abort;  // the resident CG gave up waiting (nothing was written)
+};
+
+// The direct solve by sine transforms (kernels_direct.hip), with u's boundary values from gdat (null: 0) and the
+// outcome also into out (nullable).  A, B: work arrays in the grid's layout; parts: 3 per plane.
+struct Direct {
+  Grid g;
+  double *u;
+  RhsSrc rs;
+  const double *gdat;
+  Stencil st;
+  CgState *cs;
+  Outcome *out;
+  double *A, *B, *parts;
+};
+void launch_direct(const Direct &a, hipStream_t st);
+
 // The resident CG (kernels_resident.hip): a brick shape on gx x gy x gz workgroups
 struct ResidentPlan {
   int brick, gx, gy, gz, threads;  // threads 0: the grid does not fit
@@ -252,13 +276,32 @@ struct Resident {
   RhsSrc rs;
   Stencil st;
   CgState *cs;
+  Outcome *out;     // (nullable)
   double *scratch;  // the slots of the meetings and the packed x faces: an array in the grid's layout holds them
   double *W0, *W1;  // published layers of w, in the grid's layout
   double tol;
   int cap, hist_on;
   ResidentPlan plan;
 };
+// before launch_resident: the slots it meets by, and no give-up recorded
+struct ResidentInit {
+  double *slots;
+  int n;  // 0: nothing to do
+  CgState *cs;
+  Outcome *out;
+};
+ResidentInit resident_init(const Resident &a);
+void launch_resident_init(const ResidentInit &i, hipStream_t st);
 void launch_resident(const Resident &a, hipStream_t st);
+// cs's outcome into out
+void launch_outcome(const CgState *cs, Outcome *out, hipStream_t st);
+__device__ __forceinline__ void resident_init_block(const ResidentInit &i) {
+  for (int q = threadIdx.x; q < i.n; q += blockDim.x) i.slots[q] = __longlong_as_double((long long)kMissingSlot);
+  if (threadIdx.x == 0 && i.n > 0) {
+    i.cs->abort = 0;
+    if (i.out) i.out->abort = 0;
+  }
+}
 
 // Vectors of the two-step sweeps (x in a layout gx of its own, the others in the sweep's)
 template <typename T>
@@ -334,8 +377,10 @@ void launch_set_boundary(const Grid &gg, const double *g, int stride, const Grid
 // Initial guess of a grid from the two coarser solutions: kGuessQuartic = EXP_finite (the paper's), kGuessQuadratic =
 // the same extrapolation with tri-quadratic interpolation, kGuessLinear = trilinear interpolation of u2 alone.
 enum GuessKind { kGuessQuartic = 0, kGuessQuadratic = 1, kGuessLinear = 2 };
+// init (n 0: none): what the resident CG that follows on the grid needs
 void launch_initial_guess(int kind, const Grid &g2, const double *u2, const Grid &g4, const double *u4,
-                          const Grid &gg, const double *g, int stride, const Grid &gw, double *w, hipStream_t st);
+                          const Grid &gg, const double *g, int stride, const Grid &gw, double *w,
+                          const ResidentInit &init, hipStream_t st);
 // ut (grid gt) = EXP_true(uh (grid gh), u2 (grid g2))
 void launch_exp_true(const Grid &gh, const double *uh, const Grid &g2, const double *u2, const Grid &gt, double *ut,
                      double *ucopy, hipStream_t st);

@@ -32,7 +32,7 @@ namespace excmg {
 namespace {
 
 constexpr int kSpins = 1 << 20;             // looks at the slots before a workgroup gives up (about a second)
-constexpr unsigned long long kMissing = 0x7ff8dead0badf00dull;  // a quiet NaN with a payload of its own
+constexpr unsigned long long kMissing = kMissingSlot;
 
 __device__ __forceinline__ void put(double *p, double v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -48,9 +48,15 @@ __device__ __forceinline__ double uniform(double v) {
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
-__global__ void resident_init_kernel(double *slots, int n, CgState *cs) {
-  for (int q = threadIdx.x; q < n; q += blockDim.x) slots[q] = __longlong_as_double((long long)kMissing);
-  if (threadIdx.x == 0) cs->abort = 0;
+__global__ void resident_init_kernel(ResidentInit i) { resident_init_block(i); }
+
+__global__ void outcome_kernel(const CgState *cs, Outcome *out) {
+  out->rho = cs->rho;
+  out->rho0 = cs->rho0;
+  out->bnorm2 = cs->bnorm2;
+  out->iter = cs->iter;
+  out->status = cs->status;
+  out->abort = 0;
 }
 
 // v of another lane of the wave by a DPP move (0 where the move has no source, or in rows outside the mask)
@@ -390,7 +396,10 @@ __global__ __launch_bounds__(BX * BY * ZS) void resident_cg_kernel(Resident a, d
     publish(k & 1, w);
   }
   if (!here) {
-    if (tid == 0) __hip_atomic_store(&cs->abort, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == 0) {
+      __hip_atomic_store(&cs->abort, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (a.out) a.out->abort = 1;
+    }
     return;
   }
 #pragma unroll
@@ -404,6 +413,13 @@ __global__ __launch_bounds__(BX * BY * ZS) void resident_cg_kernel(Resident a, d
     cs->stop2 = stop2;
     cs->status = status;
     cs->done = 1;
+    if (a.out) {
+      a.out->rho = gamma;
+      a.out->rho0 = rho0;
+      a.out->bnorm2 = bb;
+      a.out->iter = k;
+      a.out->status = status;
+    }
   }
 }
 
@@ -446,13 +462,20 @@ ResidentPlan resident_plan(const Grid &g, int blocks) {
   return best;
 }
 
+ResidentInit resident_init(const Resident &a) {
+  const int nb = a.plan.gx * a.plan.gy * a.plan.gz;
+  return {a.scratch, 3 * set_slots((nb + kGroup - 1) / kGroup), a.cs, a.out};
+}
+
+void launch_resident_init(const ResidentInit &i, hipStream_t st) { resident_init_kernel<<<1, 256, 0, st>>>(i); }
+
+void launch_outcome(const CgState *cs, Outcome *out, hipStream_t st) { outcome_kernel<<<1, 1, 0, st>>>(cs, out); }
+
 void launch_resident(const Resident &a, hipStream_t st) {
   const ResidentPlan &p = a.plan;
   const int nb = p.gx * p.gy * p.gz;
-  const int slots = 3 * set_slots((nb + kGroup - 1) / kGroup);
-  resident_init_kernel<<<1, 256, 0, st>>>(a.scratch, slots, a.cs);
   with_brick(p.brick, [&](auto, auto *kernel) {
-    kernel<<<nb, p.threads, p.lds, st>>>(a, a.u, a.W0, a.W1, a.scratch + slots, a.scratch, a.cs);
+    kernel<<<nb, p.threads, p.lds, st>>>(a, a.u, a.W0, a.W1, a.scratch + resident_init(a).n, a.scratch, a.cs);
   });
 }
 

@@ -307,7 +307,8 @@ template <bool QUAD>
 __global__ __launch_bounds__(ET) __attribute__((amdgpu_waves_per_eu(7, 7))) void exp_finite_kernel(Grid g2, const double *__restrict__ u2, Grid g4,
                                                         const double *__restrict__ u4, Grid gg,
                                                         const double *__restrict__ gdat, int s, Grid gw,
-                                                        double *__restrict__ w) {
+                                                        double *__restrict__ w, ResidentInit init) {
+  if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0) resident_init_block(init);
   // w is read again right away by the residual sweep: streaming stores only where it cannot stay in the caches
   exp_finite_block<QUAD>(g2, u2, g4, u4, gg, gdat, s, gw, w, blockIdx.x, blockIdx.y, blockIdx.z,
                          gw.interior() >= (1LL << 23));
@@ -527,15 +528,17 @@ void launch_set_boundary(const Grid &gg, const double *g, int stride, const Grid
 }
 
 void launch_initial_guess(int kind, const Grid &g2, const double *u2, const Grid &g4, const double *u4,
-                          const Grid &gg, const double *g, int stride, const Grid &gw, double *w, hipStream_t st) {
+                          const Grid &gg, const double *g, int stride, const Grid &gw, double *w,
+                          const ResidentInit &init, hipStream_t st) {
   if (kind == kGuessLinear) {
+    if (init.n > 0) launch_resident_init(init, st);
     prolong_linear_kernel<<<node_grid(gw, 256), 256, 0, st>>>(g2, u2, gg, g, stride, gw, w);
     return;
   }
   const int ncx = gw.nx / 8, ncy = gw.ny / 8, ncz = gw.nz / 8;
   dim3 grid((ncx + CXN - 1) / CXN, ncy, ncz);
-  if (kind == kGuessQuadratic) exp_finite_kernel<true><<<grid, ET, 0, st>>>(g2, u2, g4, u4, gg, g, stride, gw, w);
-  else exp_finite_kernel<false><<<grid, ET, 0, st>>>(g2, u2, g4, u4, gg, g, stride, gw, w);
+  if (kind == kGuessQuadratic) exp_finite_kernel<true><<<grid, ET, 0, st>>>(g2, u2, g4, u4, gg, g, stride, gw, w, init);
+  else exp_finite_kernel<false><<<grid, ET, 0, st>>>(g2, u2, g4, u4, gg, g, stride, gw, w, init);
 }
 
 void launch_exp_true(const Grid &gh, const double *uh, const Grid &g2, const double *u2, const Grid &gt, double *ut,
