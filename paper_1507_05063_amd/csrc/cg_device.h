@@ -1,10 +1,12 @@
-// Device helpers shared by the CG sweep kernels (kernels_cg.hip, kernels_two.hip).
+// Device helpers shared by the CG sweep kernels and of the one-launch solves.
 #pragma once
 
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
 #include <utility>
+
+#include "excmg_internal.h"
 
 namespace excmg {
 
@@ -59,6 +61,47 @@ template <typename T>
 __device__ __forceinline__ T *at_byte(T *plane, unsigned off) {
   return reinterpret_cast<T *>(reinterpret_cast<std::conditional_t<std::is_const_v<T>, const char, char> *>(plane) +
                                off);
+}
+
+// p, known to point to global memory (the compiler cannot tell for a pointer that is itself read from memory, and takes
+// the slower flat instructions)
+template <typename T>
+__device__ __forceinline__ T *as_global(T *p) {
+  return (T *)(__attribute__((address_space(1))) T *)p;
+}
+
+// entry e of a batched launch; nothing writes the tables while a kernel runs, so its fields are read as constants
+// (scalar loads)
+__device__ __forceinline__ const BatchEntry &entry_at(const BatchList &L, int e) {
+  typedef const BatchEntry *P;
+  const P p = *(const P *)(__attribute__((address_space(4))) const P *)(L.ent + e);
+  return *(const BatchEntry *)(__attribute__((address_space(4))) const BatchEntry *)p;
+}
+
+// entry of flattened workgroup b: the largest e with pre[e] <= b (entries with no workgroups have pre[e] = pre[e+1])
+__device__ __forceinline__ int find_entry(const int *pre, int n, int b) {
+  int lo = 0, hi = n;
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (pre[mid] <= b) lo = mid;
+    else hi = mid;
+  }
+  return lo;
+}
+
+// copy of a CG state's scalars for the host; the finest grid's completion time is stamped once
+__device__ __forceinline__ void mirror(const BatchEntry &E, const CgState *cs, BatchStatus *stat, int slot, bool final_state) {
+  BatchMirror &m = stat[E.problem].m[slot];
+  m.done = cs->done;
+  m.iter = cs->iter;
+  m.status = cs->status;
+  m.abort = cs->abort;
+  m.rho = cs->rho;
+  m.bnorm2 = cs->bnorm2;
+  m.rho0 = cs->rho0;
+  m.stop2 = cs->stop2;
+  if (final_state && E.finest && cs->done && stat[E.problem].t_done == 0)
+    stat[E.problem].t_done = (long long)wall_clock64();
 }
 
 }  // namespace

@@ -1298,29 +1298,18 @@ void batch_entry(excmg_handle *h, int problem, int l, const double *f, const dou
 // a problem's place in its cascade
 enum BatchPhase { kPhStart, kPhSmall, kPhIter64, kPhIter32, kPhOuter, kPhCopy, kPhDone };
 
-// A round's CG iterations: it rounds of one iteration of the FP64 entries (the first nb64 rounds) and of the FP32 inner
-// solves (the first nb32), in a graph replayed from the first handle's cache when the round has the launch shape of
-// an earlier one (the same workspace, iteration counts and, per list, numbers of entries and workgroups; the lists
-// themselves are read from the batch workspace when the kernels run), else captured and instantiated; directly
-// launched under EXCMG_NO_GRAPHS or for a single iteration.
+// The launches of a round's CG: launch_all(stream), in a graph replayed from the first handle's cache when the round has
+// the launch shape (key) of an earlier one - the lists themselves are read from the batch workspace when the kernels
+// run - else captured and instantiated; directly launched under EXCMG_NO_GRAPHS.
 constexpr size_t kBatchGraphCache = 1024;
 
-int batch_iterations(excmg_handle *h0, const char *ws, int it, int nb64, int nb32, const BatchList (&l64)[2],
-                     const BatchList (&l32)[2], BatchStatus *stat) {
+template <typename F>
+int batch_replay(excmg_handle *h0, const std::vector<long long> &key, F &&launch_all) {
   const hipStream_t s = h0->stream;
-  auto launch_all = [&](hipStream_t st) {
-    for (int q = 0; q < it; ++q) {
-      if (q < nb64) launch_b_iteration(0, h0->bty[0], h0->bdepth[0], l64[0], l64[1], stat, st);
-      if (q < nb32) launch_b_iteration(1, h0->bty[1], h0->bdepth[1], l32[0], l32[1], stat, st);
-    }
-  };
-  if (it <= 1 || (h0->p.flags & EXCMG_NO_GRAPHS) || h0->noalloc) {
+  if ((h0->p.flags & EXCMG_NO_GRAPHS) || h0->noalloc) {
     launch_all(s);
     return last_error();
   }
-  const std::vector<long long> key = {(long long)(uintptr_t)ws, h0->bty[0], h0->bty[1], h0->bdepth[0], h0->bdepth[1],
-                                      it, nb64, nb32, l64[0].n, l64[0].total, l64[1].total,
-                                      l32[0].n, l32[0].total, l32[1].total};
   const long long now = h0->bgraph_hits + h0->bgraph_misses;
   for (auto &bg : h0->bgraphs)
     if (bg.key == key) {
@@ -1351,10 +1340,85 @@ int batch_iterations(excmg_handle *h0, const char *ws, int it, int nb64, int nb3
   return EXCMG_OK;
 }
 
+// it rounds of one iteration of the FP64 entries (the first nb64 rounds) and of the FP32 inner solves (the first nb32)
+int batch_iterations(excmg_handle *h0, const char *ws, int it, int nb64, int nb32, const BatchList (&l64)[2],
+                     const BatchList (&l32)[2], BatchStatus *stat) {
+  auto launch_all = [&](hipStream_t st) {
+    for (int q = 0; q < it; ++q) {
+      if (q < nb64) launch_b_iteration(0, h0->bty[0], h0->bdepth[0], l64[0], l64[1], stat, st);
+      if (q < nb32) launch_b_iteration(1, h0->bty[1], h0->bdepth[1], l32[0], l32[1], stat, st);
+    }
+  };
+  if (it <= 1) {
+    launch_all(h0->stream);
+    return last_error();
+  }
+  return batch_replay(h0, {(long long)(uintptr_t)ws, h0->bty[0], h0->bty[1], h0->bdepth[0], h0->bdepth[1], it, nb64,
+                           nb32, l64[0].n, l64[0].total, l64[1].total, l32[0].n, l32[0].total, l32[1].total},
+                      launch_all);
+}
+
+// The resident CG in a batch.  A launch holds as many grids, in bricks of one kind, as the CUs take workgroups.
+struct ResidentPack {
+  int brick, blocks;
+  std::vector<int> problems;
+};
+
+// The grids gs (of the problems ps) in launches.  Small bricks iterate fastest, large ones put more grids into a launch:
+// for each kind of brick as the smallest one allowed (a grid that needs more than `cus` of it takes the next), the
+// launches are filled largest grid first, and the kind whose launches together take the least time an iteration is
+// taken.  24 problems of 32 to 64 cells an axis relax their finest grids in three launches of 0.45 ms (2.2 ms the whole
+// batch), where the flattened sweeps, four launches an iteration, took 6 ms (9.7 ms the whole batch).
+std::vector<ResidentPack> pack_residents(const std::vector<int> &ps, const std::vector<Grid> &gs, int cus) {
+  std::vector<ResidentPack> best;
+  double least = 1e300;
+  const int n = (int)ps.size();
+  for (int least_brick = 0; least_brick < kResidentBricks; ++least_brick) {
+    std::vector<int> brick(n), nb(n), order(n);
+    for (int q = 0; q < n; ++q) {
+      order[q] = q;
+      auto fits = [&](int k) {
+        const int v = brick_blocks(gs[q], k);
+        if (v == 0 || v > cus) return false;
+        brick[q] = k;
+        nb[q] = v;
+        return true;
+      };
+      bool found = false;
+      for (int k = least_brick; k < kResidentBricks && !found; ++k) found = fits(k);
+      for (int k = least_brick - 1; k >= 0 && !found; --k) found = fits(k);
+    }
+    std::sort(order.begin(), order.end(), [&](int a, int b) { return nb[a] != nb[b] ? nb[a] > nb[b] : a < b; });
+    std::vector<ResidentPack> packs;
+    double t = 0.0;
+    for (int q : order) {
+      ResidentPack *p = nullptr;
+      for (auto &c : packs)
+        if (!p && c.brick == brick[q] && c.blocks + nb[q] <= cus) p = &c;
+      if (!p) {
+        t += brick_time(brick[q]);
+        packs.push_back({brick[q], 0, {}});
+        p = &packs.back();
+      }
+      p->blocks += nb[q];
+      p->problems.push_back(ps[q]);
+    }
+    if (t < least) {
+      least = t;
+      best = std::move(packs);
+    }
+  }
+  return best;
+}
+
 int batched_solve(excmg_handle *const *hs, int count, const double *const *f, const double *const *g,
                   double *const *u, char *ws, excmg_stats *stats, double *ms_per_problem) {
   const hipStream_t s = hs[0]->stream;
   const auto t_host = std::chrono::steady_clock::now();
+  ResidentCall call{hs[0]};
+  int cus = 0;
+  HIPCHECK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, hs[0]->device));
+  cus = cus < 256 ? cus : 256;
   int S = 0;
   for (int b = 0; b < count; ++b) S = hs[b]->lo.L > S ? hs[b]->lo.L : S;
   const size_t stat_bytes = align256(sizeof(BatchStatus) * (size_t)count);
@@ -1424,6 +1488,10 @@ int batched_solve(excmg_handle *const *hs, int count, const double *const *f, co
         for (int d = 0; d < 3; ++d) stats[b].n[l][d] = hs[b]->lo.lev[l].n[d];
     }
   std::vector<int> lev(count, 0), ph(count, kPhStart), outer(count, 0), inner(count, 0), fresh(count, 0);
+  // problems on a grid of one launch this round: direct solves (small, larger), the one-workgroup CG, the resident CG
+  std::vector<int> dsmall, dlarge, small, res;
+  std::vector<Grid> res_grid;
+  std::vector<char> apart(count, 0);  // a workgroup of the resident CG gave up waiting: this problem runs without it
   int final_status = EXCMG_OK, remaining = count;
   // a problem's grid is finished: record it, then start its next grid (or copy it out)
   auto finish_grid = [&](int b) -> int {
@@ -1456,18 +1524,36 @@ int batched_solve(excmg_handle *const *hs, int count, const double *const *f, co
       hl[k].n = 0;
       hl[k].preA[0] = hl[k].preB[0] = 0;
     }
-    int lds = 0;
+    dsmall.clear();
+    dlarge.clear();
+    small.clear();
+    res.clear();
+    res_grid.clear();
+    int lds = 0, unknowns = 0, scells[3] = {}, lcells[3] = {};
     for (int b = 0; b < count; ++b) {
       const int l = lev[b];
       fresh[b] = 0;
       switch (ph[b]) {
         case kPhStart: {
           const int kind = batch_kind(hs[b], l);
+          const Level &lv = hs[b]->lo.lev[l];
+          if (kind == kBSmall && l <= 1 && dst_fits(lv.g)) {
+            const bool one = direct_small(lv.g);
+            (one ? dsmall : dlarge).push_back(b);
+            for (int d = 0; d < 3; ++d) (one ? scells : lcells)[d] = std::max((one ? scells : lcells)[d], lv.n[d]);
+            if (one) unknowns = std::max(unknowns, (int)lv.g.interior());
+            ph[b] = kPhSmall;
+            break;
+          }
           if (l <= 1) add(kListSetB, l, b, nblk(l, b, kLSetB), 0, 0);
           else add(kListExp, l, b, nblk(l, b, kLExp), 0, 0);
-          if (kind == kBSmall) {
-            add(kListSmall, l, b, 0, 0, 0);
-            const int v = b_small_lds_nodes(hs[b]->lo.lev[l].g);
+          if (lv.res.threads && !apart[b] && s != hipStreamPerThread) {
+            res.push_back(b);
+            res_grid.push_back(lv.g);
+            ph[b] = kPhSmall;
+          } else if (kind == kBSmall) {
+            small.push_back(b);
+            const int v = b_small_lds_nodes(lv.g);
             lds = v > lds ? v : lds;
             ph[b] = kPhSmall;
           } else if (kind == kBCg64) {
@@ -1509,6 +1595,12 @@ int batched_solve(excmg_handle *const *hs, int count, const double *const *f, co
           break;
       }
     }
+    // one list for all of them, a launch each for a part of it
+    for (const auto *v : {&dsmall, &dlarge, &small})
+      for (int b : *v) add(kListSmall, lev[b], b, 0, 0, 0);
+    const std::vector<ResidentPack> packs = pack_residents(res, res_grid, cus);
+    for (const auto &p : packs)
+      for (int b : p.problems) add(kListSmall, lev[b], b, brick_blocks(hs[b]->lo.lev[lev[b]].g, p.brick), 0, 0);
     HIPCHECK(hipMemcpyAsync(lists_dev, lists_host, (size_t)kListKinds * lb, hipMemcpyHostToDevice, s));
     for (int k = 0; k < kListKinds; ++k)
       for (int q = 0; q < 2; ++q) {
@@ -1518,7 +1610,37 @@ int batched_solve(excmg_handle *const *hs, int count, const double *const *f, co
     launch_b_copy(dl[kListCopy][0], s);
     launch_b_set_boundary(dl[kListSetB][0], s);
     launch_b_exp_finite(dl[kListExp][0], s);
-    launch_b_small_cg(dl[kListSmall][0], lds, stat, s);
+    int at = 0;  // the part of the list taken
+    auto part = [&](size_t n, int total) {
+      BatchList p = dl[kListSmall][0];
+      p.ent += at;
+      p.pre += at;
+      p.n = (int)n;
+      p.total = total;
+      at += (int)n;
+      return p;
+    };
+    launch_b_direct_small(part(dsmall.size(), 0), unknowns, scells, stat, s);
+    launch_b_direct(part(dlarge.size(), 0), lcells, stat, s);
+    launch_b_small_cg(part(small.size(), 0), lds, stat, s);
+    if (!packs.empty()) {
+      std::vector<long long> key = {(long long)(uintptr_t)ws, -1, at};
+      for (const auto &p : packs) key.insert(key.end(), {p.brick, p.blocks, (long long)p.problems.size()});
+      ResidentTurn &turn = g_resident[hs[0]->device];
+      std::lock_guard<std::mutex> lock(turn.mu);
+      if (turn.last && turn.last != hs[0]) HIPCHECK(hipStreamSynchronize(turn.last->stream));
+      turn.last = hs[0];
+      const int from = at;
+      e = batch_replay(hs[0], key, [&](hipStream_t st) {
+        at = from;
+        const BatchList all = part(res.size(), 0);
+        launch_b_resident_init(all, st);
+        at = from;
+        for (const auto &p : packs) launch_b_resident(p.brick, part(p.problems.size(), p.blocks), st);
+        launch_b_mirror(all, stat, st);
+      });
+      if (e) return e;
+    }
     launch_b_boundary_terms(dl[kListBterm][0], s);
     launch_b_residual(dl[kListR64][0], stat, s);
     launch_b_add_correction(dl[kListCorr][0], s);
@@ -1529,6 +1651,11 @@ int batched_solve(excmg_handle *const *hs, int count, const double *const *f, co
     // move every problem on, and size the next round's iteration batches from the residual decay seen so far
     nb64 = nb32 = 1;
     bool any64 = false, any32 = false;
+    for (int b : res)
+      if (hstat[b].m[0].abort) {
+        apart[b] = 1;
+        ph[b] = kPhStart;
+      }
     for (int b = 0; b < count; ++b) {
       switch (ph[b]) {
         case kPhSmall:

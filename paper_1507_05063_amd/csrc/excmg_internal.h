@@ -29,8 +29,8 @@ struct Grid {
   __host__ __device__ long long nodes() const { return (long long)(nx + 1) * (ny + 1) * (nz + 1); }
 };
 
-// DSOLVE (the exact solve of the two coarsest grids, Algorithm 1) by sine transforms in one workgroup: grids of at
-// most kDstMax cells per axis.  Larger direct-solve grids are solved by CG to a relative residual of kDsolveTol (one
+// DSOLVE (the exact solve of the two coarsest grids, Algorithm 1) by sine transforms: grids of at most kDstMax
+// cells per axis.  Larger direct-solve grids are solved by CG to a relative residual of kDsolveTol (one
 // workgroup up to kSmallCg unknowns, else the multi-workgroup sweeps), which reports EXCMG_ERR_NOCONV if its
 // iteration cap is reached first.
 constexpr int kDstMax = 64;
@@ -251,7 +251,7 @@ struct Outcome {
 };
 
 // The direct solve by sine transforms (kernels_direct.hip), with u's boundary values from gdat (null: 0) and the
-// outcome also into out (nullable).  A, B: work arrays in the grid's layout; parts: 3 per plane.
+// outcome also into out (nullable).  A, B: work arrays in the grid's layout; parts: 3 per plane of partial sums.
 struct Direct {
   Grid g;
   double *u;
@@ -409,7 +409,8 @@ enum BatchLaunch {
 };
 
 struct BatchMirror {  // copy of one CG state's scalars, for the host
-  int done, iter, status, pad;
+  int done, iter, status;
+  int abort;  // the resident CG gave up waiting (the grid is as it was)
   double rho, bnorm2, rho0, stop2;
 };
 
@@ -459,6 +460,20 @@ void launch_b_set_boundary(const BatchList &L, hipStream_t st);
 void launch_b_exp_finite(const BatchList &L, hipStream_t st);
 void launch_b_small_cg(const BatchList &L, int lds_nodes, BatchStatus *stat, hipStream_t st);
 int b_small_lds_nodes(const Grid &g);  // LDS (doubles) the small-grid CG of this grid uses, 0 if it does not fit
+// direct solves by sine transforms (with the boundary values; parts as in Direct): small ones, direct_small(g), then
+// the others of at most `cells` cells an axis
+bool direct_small(const Grid &g);
+void launch_b_direct_small(const BatchList &L, int unknowns, const int cells[3], BatchStatus *stat, hipStream_t st);
+void launch_b_direct(const BatchList &L, const int cells[3], BatchStatus *stat, hipStream_t st);
+// the resident CG of the entries of L, each in one of the bricks numbered `brick`, with brick_blocks workgroups (all of
+// them at most as many as CUs), after launch_b_resident_init for them; then launch_b_mirror
+constexpr int kResidentBricks = 4;
+int brick_blocks(const Grid &g, int brick);  // 0: this brick does not suit the grid
+double brick_time(int brick);                // of an iteration of a launch that fills the chip, relative
+void launch_b_resident_init(const BatchList &L, hipStream_t st);
+void launch_b_resident(int brick, const BatchList &L, hipStream_t st);
+// the CG states of L's entries into stat
+void launch_b_mirror(const BatchList &L, BatchStatus *stat, hipStream_t st);
 void launch_b_boundary_terms(const BatchList &L, hipStream_t st);
 void launch_b_residual(const BatchList &L, BatchStatus *stat, hipStream_t st);       // + the reduction
 void launch_b_residual_cast(const BatchList &L, BatchStatus *stat, hipStream_t st);  // + the reduction

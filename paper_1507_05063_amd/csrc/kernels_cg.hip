@@ -1238,110 +1238,6 @@ __device__ void small_cg_lds_body(const Grid &gu, double *u, const RhsSrc &rs, c
   }
 }
 
-// ----------------------------------------------------------------------------------------- direct solve by sines
-//
-// With zero Dirichlet data, M (the 19-point operator on the interior) is diagonalised by the products of DST-I
-// vectors s_p(i) = sin(pi p i / N), p, i = 1..N-1 per axis: M S = S diag(lambda) with
-//   lambda_pqr = c0 + 2 cx Cx + 2 cy Cy + 2 cz Cz + 4 cxy Cx Cy + 4 cxz Cx Cz + 4 cyz Cy Cz,  Cx = cos(pi p / Nx), ...
-// (c* the stencil's coefficients), and S^2 = (Nx Ny Nz / 8) I.  So M^-1 b = (8 / (Nx Ny Nz)) S diag(1/lambda) S b: three
-// one-dimensional sine transforms, a division, three more.  This is DSOLVE of Algorithm 1 as an exact direct solve
-// (to rounding), in one workgroup, for grids of at most kDstMax cells per axis; the transforms are dense
-// (N-1) x (N-1) products along each axis through the work arrays A and B (the grid's layout), with the sine table of
-// the current axis in LDS.
-
-__device__ void dst_solve_body(const Grid &gu, double *u, const RhsSrc &rs, const Stencil &st, CgState *cs,
-                               double *A, double *B) {
-  __shared__ double tab[(kDstMax - 1) * (kDstMax - 1)];
-  __shared__ double cosv[3][kDstMax];
-  __shared__ double sh[DT / 64];
-  const int n1[3] = {gu.nx - 1, gu.ny - 1, gu.nz - 1};
-  const int N[3] = {gu.nx, gu.ny, gu.nz};
-  const int n = n1[0] * n1[1] * n1[2];
-  auto coords = [&](int m, int &i, int &j, int &k) {
-    i = 1 + m % n1[0];
-    const int t = m / n1[0];
-    j = 1 + t % n1[1];
-    k = 1 + t / n1[1];
-  };
-  // A = b (formed from the level data), and the cosines of every axis
-  double b2 = 0.0;
-  for (int m = threadIdx.x; m < n; m += DT) {
-    int i, j, k;
-    coords(m, i, j, k);
-    double rf;
-    const double bv = rhs_at<true>(rs, gu.nx, gu.ny, gu.nz, i, j, k, rf);
-    A[gu.at(i, j, k)] = bv;
-    b2 += stop_norm_term(rs, bv, rf);
-  }
-  for (int e = threadIdx.x; e < 3 * kDstMax; e += DT) {
-    const int d = e / kDstMax, p = e % kDstMax;
-    cosv[d][p] = (p >= 1 && p < N[d]) ? cospi((double)p / N[d]) : 0.0;
-  }
-  // one transform along axis d: dst(.., i, ..) = sum_i' sin(pi i i' / N_d) src(.., i', ..)
-  auto transform = [&](int d, const double *src, double *dst) {
-    const int L = n1[d];
-    __syncthreads();  // src complete; the previous table no longer read
-    for (int e = threadIdx.x; e < L * L; e += DT) {
-      const int p = e / L + 1, q = e % L + 1;
-      tab[e] = sinpi((double)((p * q) % (2 * N[d])) / N[d]);
-    }
-    __syncthreads();
-    const long long stride = d == 0 ? 1 : (d == 1 ? gu.sy : gu.sz);
-    for (int m = threadIdx.x; m < n; m += DT) {
-      int i, j, k;
-      coords(m, i, j, k);
-      const int t = d == 0 ? i : (d == 1 ? j : k);
-      const long long base = gu.at(i, j, k) - (long long)t * stride;  // the line's node 0
-      const double *row = tab + (t - 1) * L;
-      double v = 0.0;
-      for (int q = 1; q <= L; ++q) v += row[q - 1] * src[base + (long long)q * stride];
-      dst[gu.at(i, j, k)] = v;
-    }
-  };
-  transform(0, A, B);
-  transform(1, B, A);
-  transform(2, A, B);
-  // divide by the eigenvalues (with the scale of the inverse transform)
-  __syncthreads();
-  const double scale = 8.0 / ((double)N[0] * N[1] * N[2]);
-  for (int m = threadIdx.x; m < n; m += DT) {
-    int i, j, k;
-    coords(m, i, j, k);
-    const double Cx = cosv[0][i], Cy = cosv[1][j], Cz = cosv[2][k];
-    const double lam = st.c0 + 2.0 * (st.cx * Cx + st.cy * Cy + st.cz * Cz) +
-                       4.0 * (st.cxy * Cx * Cy + st.cxz * Cx * Cz + st.cyz * Cy * Cz);
-    B[gu.at(i, j, k)] *= scale / lam;
-  }
-  transform(0, B, A);
-  transform(1, A, B);
-  transform(2, B, A);
-  __syncthreads();
-  for (int m = threadIdx.x; m < n; m += DT) {
-    int i, j, k;
-    coords(m, i, j, k);
-    u[gu.at(i, j, k)] = A[gu.at(i, j, k)];
-  }
-  __syncthreads();
-  // residual of the solve, for the record
-  double r2 = 0.0;
-  for (int m = threadIdx.x; m < n; m += DT) {
-    int i, j, k;
-    coords(m, i, j, k);
-    const double rv = rhs_at<true>(rs, gu.nx, gu.ny, gu.nz, i, j, k) - stencil_direct(gu, u, i, j, k, st);
-    r2 += rv * rv;
-  }
-  const double rho = dsum(r2, sh);
-  const double bnorm2 = dsum(b2, sh) + cs->gbnd2;
-  if (threadIdx.x == 0) {
-    cs->iter = 0;
-    cs->rho = rho;
-    cs->rho0 = rho;
-    cs->bnorm2 = bnorm2;
-    cs->status = (isfinite(rho) && isfinite(bnorm2)) ? 0 : EXCMG_ERR_BREAKDOWN;
-    cs->done = 1;
-  }
-}
-
 __host__ __device__ inline bool small_fits_lds(const Grid &g) {
   return small_lds_nodes(g) <= kSmallLdsMax && g.interior() <= (long long)SK * DT;
 }
@@ -1350,9 +1246,7 @@ __global__ __launch_bounds__(DT) void small_cg_kernel(Grid gu, double *u, RhsSrc
                                                       double *q, Stencil st, CgState *cs, double tol, int cap,
                                                       int exact, int hist_on) {
   extern __shared__ double lds_p[];
-  if (exact && dst_fits(gu))
-    dst_solve_body(gu, u, rs, st, cs, r, p);
-  else if (small_fits_lds(gu))
+  if (small_fits_lds(gu))
     small_cg_lds_body(gu, u, rs, gw, r, st, cs, tol, cap, exact, hist_on, lds_p);
   else
     small_cg_body(gu, u, rs, gw, r, p, q, st, cs, tol, cap, exact, hist_on);
@@ -1361,31 +1255,6 @@ __global__ __launch_bounds__(DT) void small_cg_kernel(Grid gu, double *u, RhsSrc
 // ---------------------------------------------------------------------------------------------------- batched form
 //
 // The same sweeps, reductions and small-grid CG over a table of problems (one entry per problem; see BatchEntry).
-
-// entry of flattened workgroup b: the largest e with pre[e] <= b (entries with no workgroups have pre[e] = pre[e+1])
-__device__ __forceinline__ int find_entry(const int *pre, int n, int b) {
-  int lo = 0, hi = n;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (pre[mid] <= b) lo = mid;
-    else hi = mid;
-  }
-  return lo;
-}
-
-// copy of a CG state's scalars for the host; the finest grid's completion time is stamped once
-__device__ void mirror(const BatchEntry &E, const CgState *cs, BatchStatus *stat, int slot, bool final_state) {
-  BatchMirror &m = stat[E.problem].m[slot];
-  m.done = cs->done;
-  m.iter = cs->iter;
-  m.status = cs->status;
-  m.rho = cs->rho;
-  m.bnorm2 = cs->bnorm2;
-  m.rho0 = cs->rho0;
-  m.stop2 = cs->stop2;
-  if (final_state && E.finest && cs->done && stat[E.problem].t_done == 0)
-    stat[E.problem].t_done = (long long)wall_clock64();
-}
 
 __global__ void b_init_kernel(BatchStatus *stat, int count, long long *t0) {
   const int q = blockIdx.x * blockDim.x + threadIdx.x;
@@ -1401,9 +1270,7 @@ __global__ __launch_bounds__(DT) void b_small_cg_kernel(BatchList L, BatchStatus
   extern __shared__ double lds_p[];
   const BatchEntry &E = *L.ent[blockIdx.x];
   const int cap = E.cap;  // grids 0 and 1: the direct solve's cap
-  if (E.exact && dst_fits(E.g))
-    dst_solve_body(E.g, E.u, E.rs, E.st, E.cs, E.r, E.p0);
-  else if (small_fits_lds(E.g) && small_lds_nodes(E.g) <= lds_nodes)
+  if (small_fits_lds(E.g) && small_lds_nodes(E.g) <= lds_nodes)
     small_cg_lds_body(E.g, E.u, E.rs, E.g, E.r, E.st, E.cs, E.tol, cap, E.exact, 0, lds_p);
   else
     small_cg_body(E.g, E.u, E.rs, E.g, E.r, E.p0, E.p1, E.st, E.cs, E.tol, cap, E.exact, 0);
@@ -1762,8 +1629,7 @@ void launch_small_cg(const Grid &gu, double *u, const RhsSrc &rs, const Grid &gw
                      const Stencil &s, CgState *cs, double tol, int max_iters, int exact, int hist_on,
                      hipStream_t st) {
   const int cap = exact ? dsolve_cap(gu.interior()) : max_iters;
-  const size_t lds = (!(exact && dst_fits(gu)) && small_fits_lds(gu)) ? (size_t)small_lds_nodes(gu) * sizeof(double)
-                                                                        : 0;
+  const size_t lds = small_fits_lds(gu) ? (size_t)small_lds_nodes(gu) * sizeof(double) : 0;
   small_cg_kernel<<<1, DT, lds, st>>>(gu, u, rs, gw, r, p, q, s, cs, tol, cap, exact, hist_on);
 }
 

@@ -61,7 +61,7 @@ __device__ __forceinline__ double dirichlet(const Direct &a, int i, int j, int k
   return a.gdat ? a.gdat[a.rs.gf.at(i * a.rs.s, j * a.rs.s, k * a.rs.s)] : 0.0;
 }
 
-__global__ __launch_bounds__(kDirectSmall) void direct_small_kernel(Direct a) {
+__device__ __forceinline__ void direct_small_body(const Direct &a) {
   extern __shared__ double lds[];
   __shared__ double sh[2][kDirectSmall / 64];
   const Grid g = a.g;
@@ -174,11 +174,11 @@ __device__ __forceinline__ double plane_sum(double v, double *sh) {
 
 // plane k: u's boundary values, b (kept in B), its transforms along x and y into A, and the plane's part of the
 // stopping norm
-__global__ __launch_bounds__(DP) void direct_forward_kernel(Direct a) {
+__device__ __forceinline__ void direct_forward_body(const Direct &a, int bid) {
   extern __shared__ double lds[];
   __shared__ double sh[DP / 64];
   const Grid g = a.g;
-  const int k = blockIdx.x, Lx = g.nx - 1, Ly = g.ny - 1, np = Lx * Ly;
+  const int k = bid, Lx = g.nx - 1, Ly = g.ny - 1, np = Lx * Ly;
   const bool end = k == 0 || k == g.nz;
   for (int e = threadIdx.x; e < (g.nx + 1) * (g.ny + 1); e += DP) {
     const int x = e % (g.nx + 1), y = e / (g.nx + 1);
@@ -208,12 +208,12 @@ constexpr int DC = 64, DCT = 512;  // columns and threads of a column workgroup
 constexpr int kDck = ((kDstMax - 1) * DC + DCT - 1) / DCT;
 
 // 64 columns: the transform along z, the division by the eigenvalues, the transform back
-__global__ __launch_bounds__(DCT) void direct_columns_kernel(Direct a) {
+__device__ __forceinline__ void direct_columns_body(const Direct &a, int bid) {
   extern __shared__ double lds[];
   const Grid g = a.g;
   const int Lx = g.nx - 1, Ly = g.ny - 1, Lz = g.nz - 1, nc = Lx * Ly;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int c = min(blockIdx.x * DC + lane, nc - 1), i = 1 + c % Lx, j = 1 + c / Lx;  // lanes past the last repeat it
+  const int c = min(bid * DC + lane, nc - 1), i = 1 + c % Lx, j = 1 + c / Lx;  // lanes past the last repeat it
   double *P = lds, *S = P + Lz * DC, *half = S + Lz * Lz;
   for (int k = w; k < Lz; k += DCT / 64) P[k * DC + lane] = a.A[g.at(i, j, k + 1)];
   sine_table(S, half, g.nz, DCT);
@@ -239,15 +239,15 @@ __global__ __launch_bounds__(DCT) void direct_columns_kernel(Direct a) {
     }
     __syncthreads();
   }
-  if (blockIdx.x * DC + lane < nc)
+  if (bid * DC + lane < nc)
     for (int k = w; k < Lz; k += DCT / 64) a.A[g.at(i, j, k + 1)] = P[k * DC + lane];
 }
 
 // plane k: the transforms along y and x back, into u
-__global__ __launch_bounds__(DP) void direct_backward_kernel(Direct a) {
+__device__ __forceinline__ void direct_backward_body(const Direct &a, int bid) {
   extern __shared__ double lds[];
   const Grid g = a.g;
-  const int k = 1 + blockIdx.x, Lx = g.nx - 1, Ly = g.ny - 1, np = Lx * Ly;
+  const int k = 1 + bid, Lx = g.nx - 1, Ly = g.ny - 1, np = Lx * Ly;
   double *P = lds, *S = P + np, *half = S + max(Lx * Lx, Ly * Ly);
   for (int e = threadIdx.x; e < np; e += DP) P[e] = a.A[g.at(1 + e % Lx, 1 + e / Lx, k)];
   sine_table(S, half, g.ny, DP);
@@ -258,9 +258,9 @@ __global__ __launch_bounds__(DP) void direct_backward_kernel(Direct a) {
 }
 
 // the residual b - M u of plane k; the last workgroup records the outcome
-__global__ __launch_bounds__(DP) void direct_residual_kernel(Direct a) {
+__device__ __forceinline__ void direct_residual_body(const Direct &a, int bid) {
   const Grid g = a.g;
-  const int k = 1 + blockIdx.x, Lx = g.nx - 1, np = Lx * (g.ny - 1);
+  const int k = 1 + bid, Lx = g.nx - 1, np = Lx * (g.ny - 1);
   const Stencil &s = a.st;
   double v[2] = {0.0, threadIdx.x == 0 ? a.parts[2 * (g.nz - 1) + k - 1] : 0.0}, tot[2];
   for (int e = threadIdx.x; e < np; e += DP) {
@@ -277,26 +277,105 @@ __global__ __launch_bounds__(DP) void direct_residual_kernel(Direct a) {
     const double r = a.B[g.at(i, j, k)] - m;
     v[0] += r * r;
   }
-  if (last_sums<2, DP>(v, a.parts, &a.cs->count, blockIdx.x, gridDim.x, tot) && threadIdx.x == 0)
+  if (last_sums<2, DP>(v, a.parts, &a.cs->count, bid, g.nz - 1, tot) && threadIdx.x == 0)
     direct_outcome(a, tot[0], tot[1]);
 }
 
+// entry e of a batch
+__device__ __forceinline__ Direct direct_of(const BatchList &L, int e) {
+  const BatchEntry &E = entry_at(L, e);
+  Direct a;
+  a.g = E.g;
+  a.u = as_global(E.u);
+  a.rs = E.rs;
+  a.rs.f = as_global(E.rs.f);
+  a.rs.g = as_global(E.rs.g);
+  a.gdat = as_global(E.gb);
+  a.st = E.st;
+  a.cs = as_global(E.cs);
+  a.out = nullptr;
+  a.A = as_global(E.r);
+  a.B = as_global(E.p0);
+  a.parts = as_global(E.parts);
+  return a;
+}
+
+__global__ __launch_bounds__(kDirectSmall) void direct_small_kernel(Direct a) { direct_small_body(a); }
+__global__ __launch_bounds__(DP) void direct_forward_kernel(Direct a) { direct_forward_body(a, blockIdx.x); }
+__global__ __launch_bounds__(DCT) void direct_columns_kernel(Direct a) { direct_columns_body(a, blockIdx.x); }
+__global__ __launch_bounds__(DP) void direct_backward_kernel(Direct a) { direct_backward_body(a, blockIdx.x); }
+__global__ __launch_bounds__(DP) void direct_residual_kernel(Direct a) { direct_residual_body(a, blockIdx.x); }
+
+// one grid to a y of the launch; x covers the largest grid
+__global__ __launch_bounds__(kDirectSmall) void b_direct_small_kernel(BatchList L) {
+  direct_small_body(direct_of(L, blockIdx.x));
+}
+__global__ __launch_bounds__(DP) void b_direct_forward_kernel(BatchList L) {
+  const Direct a = direct_of(L, blockIdx.y);
+  if ((int)blockIdx.x <= a.g.nz) direct_forward_body(a, blockIdx.x);
+}
+__global__ __launch_bounds__(DCT) void b_direct_columns_kernel(BatchList L) {
+  const Direct a = direct_of(L, blockIdx.y);
+  if ((int)blockIdx.x * DC < (a.g.nx - 1) * (a.g.ny - 1)) direct_columns_body(a, blockIdx.x);
+}
+__global__ __launch_bounds__(DP) void b_direct_backward_kernel(BatchList L) {
+  const Direct a = direct_of(L, blockIdx.y);
+  if ((int)blockIdx.x < a.g.nz - 1) direct_backward_body(a, blockIdx.x);
+}
+__global__ __launch_bounds__(DP) void b_direct_residual_kernel(BatchList L) {
+  const Direct a = direct_of(L, blockIdx.y);
+  if ((int)blockIdx.x < a.g.nz - 1) direct_residual_body(a, blockIdx.x);
+}
+
+// LDS of the kernels for grids of at most the given unknowns and cells
+size_t small_lds(int n, int nx, int ny, int nz) {
+  const int Lx = nx - 1, Ly = ny - 1, Lz = nz - 1;
+  return (size_t)(n + Lx * Lx + Ly * Ly + Lz * Lz + 2 * std::max(nx, std::max(ny, nz))) * sizeof(double);
+}
+size_t plane_lds(int nx, int ny) {
+  const int Lx = nx - 1, Ly = ny - 1;
+  return (size_t)(Lx * Ly + std::max(Lx * Lx, Ly * Ly) + 2 * std::max(nx, ny)) * sizeof(double);
+}
+size_t column_lds(int nz) { return (size_t)((nz - 1) * DC + (nz - 1) * (nz - 1) + 2 * nz) * sizeof(double); }
+
 }  // namespace
+
+bool direct_small(const Grid &g) { return g.interior() <= kDirectSmall; }
 
 void launch_direct(const Direct &a, hipStream_t st) {
   const Grid &g = a.g;
-  const int Lx = g.nx - 1, Ly = g.ny - 1, Lz = g.nz - 1, n = Lx * Ly * Lz;
-  const auto bytes = [](int doubles) { return (size_t)doubles * sizeof(double); };
-  if (n <= kDirectSmall) {
-    const int half = 2 * std::max(g.nx, std::max(g.ny, g.nz));
-    direct_small_kernel<<<1, (n + 63) / 64 * 64, bytes(n + Lx * Lx + Ly * Ly + Lz * Lz + half), st>>>(a);
+  const int nc = (g.nx - 1) * (g.ny - 1), Lz = g.nz - 1;
+  if (direct_small(g)) {
+    direct_small_kernel<<<1, (nc * Lz + 63) / 64 * 64, small_lds(nc * Lz, g.nx, g.ny, g.nz), st>>>(a);
     return;
   }
-  const size_t plane = bytes(Lx * Ly + std::max(Lx * Lx, Ly * Ly) + 2 * std::max(g.nx, g.ny));
+  const size_t plane = plane_lds(g.nx, g.ny);
   direct_forward_kernel<<<g.nz + 1, DP, plane, st>>>(a);
-  direct_columns_kernel<<<(Lx * Ly + DC - 1) / DC, DCT, bytes(Lz * DC + Lz * Lz + 2 * g.nz), st>>>(a);
+  direct_columns_kernel<<<(nc + DC - 1) / DC, DCT, column_lds(g.nz), st>>>(a);
   direct_backward_kernel<<<Lz, DP, plane, st>>>(a);
   direct_residual_kernel<<<Lz, DP, 0, st>>>(a);
+}
+
+void launch_b_direct_small(const BatchList &L, int unknowns, const int cells[3], BatchStatus *stat, hipStream_t st) {
+  if (L.n == 0) return;
+  const size_t lds = small_lds(unknowns, cells[0], cells[1], cells[2]);
+  b_direct_small_kernel<<<L.n, (unknowns + 63) / 64 * 64, lds, st>>>(L);
+  launch_b_mirror(L, stat, st);
+}
+
+void launch_b_direct(const BatchList &L, const int cells[3], BatchStatus *stat, hipStream_t st) {
+  const int nc = (cells[0] - 1) * (cells[1] - 1), Lz = cells[2] - 1;
+  const size_t plane = plane_lds(cells[0], cells[1]);
+  for (int e = 0; e < L.n; e += 65535) {  // (the limit of y)
+    BatchList part = L;
+    part.ent += e;
+    part.n = std::min(L.n - e, 65535);
+    b_direct_forward_kernel<<<dim3(Lz + 2, part.n), DP, plane, st>>>(part);
+    b_direct_columns_kernel<<<dim3((nc + DC - 1) / DC, part.n), DCT, column_lds(cells[2]), st>>>(part);
+    b_direct_backward_kernel<<<dim3(Lz, part.n), DP, plane, st>>>(part);
+    b_direct_residual_kernel<<<dim3(Lz, part.n), DP, 0, st>>>(part);
+  }
+  launch_b_mirror(L, stat, st);
 }
 
 }  // namespace excmg

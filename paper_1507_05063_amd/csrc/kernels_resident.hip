@@ -94,6 +94,8 @@ struct Meeting {
 // A set of slots: per group of 32 workgroups 32 slots of a and 32 of b, then one line of the groups' sums.
 constexpr int kGroup = 32, kGroups = 8;
 __host__ __device__ constexpr int set_slots(int groups) { return 2 * kGroup * groups + 2 * kGroups; }
+// the three sets of nb workgroups
+__host__ __device__ constexpr int slots_of(int nb) { return 3 * set_slots((nb + kGroup - 1) / kGroup); }
 
 // Reads slot p of every lane that has one until none is missing (0 in the other lanes); there: whether that happened.
 __device__ __forceinline__ double await(const double *p, bool mine, bool &there) {
@@ -111,7 +113,7 @@ __device__ __forceinline__ double await(const double *p, bool mine, bool &there)
 // adds up its group, and read the groups' sums (256 workgroups that all read 512 slots get in one another's way: 3.6 us
 // a meeting, against 1.2 us among four).
 template <int NW>
-__device__ __forceinline__ bool meet(double &a, double &b, double *slots, int seq, int nb, Meeting<NW> &m) {
+__device__ __forceinline__ bool meet(double &a, double &b, double *slots, int seq, int bid, int nb, Meeting<NW> &m) {
   const int groups = (nb + kGroup - 1) / kGroup;
   __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");  // what this thread has published has arrived
   a = wave_sum63(a);
@@ -124,9 +126,9 @@ __device__ __forceinline__ bool meet(double &a, double &b, double *slots, int se
   __syncthreads();
   if (w == 0) {
     const int now = (seq % 3) * set_slots(groups), before = ((seq + 2) % 3) * set_slots(groups);
-    const int group = blockIdx.x / kGroup, line = 2 * kGroup * groups;
-    const bool writer = lane == 15 || lane == 31, leader = groups == 1 || blockIdx.x % kGroup == 0;
-    const int own = 2 * kGroup * group + (lane >> 4) * kGroup + blockIdx.x % kGroup;
+    const int group = bid / kGroup, line = 2 * kGroup * groups;
+    const bool writer = lane == 15 || lane == 31, leader = groups == 1 || bid % kGroup == 0;
+    const int own = 2 * kGroup * group + (lane >> 4) * kGroup + bid % kGroup;
     double x = row_sum(lane < 32 && (lane & 15) < NW ? m.mine[lane >> 4][lane & 15] : 0.0);
     if (!(x == x)) x = __longlong_as_double(0x7ff8000000000000ll);  // any NaN is the plain one
     if (writer) put(&slots[now + own], x);
@@ -176,8 +178,8 @@ struct Brick {
 };
 
 template <int BX, int BY, int ZS, int ZR>
-__global__ __launch_bounds__(BX * BY * ZS) void resident_cg_kernel(Resident a, double *u_, double *W0, double *W1, double *WX, double *slots,
-                                                                    CgState *cs) {
+__device__ __forceinline__ void resident_cg(const Resident &a, double *u_, double *W0, double *W1, double *WX,
+                                            double *slots, CgState *cs, int gx, int gy, int bid, int nb) {
   using B = Brick<BX, BY, ZS, ZR>;
   constexpr int BZ = B::BZ, PX = B::PX, PY = B::PY, plane = B::Plane, HM = B::HM, nt = B::NT, XF = B::Xf;
   extern __shared__ double R[];  // r on the brick and its neighbours' layer
@@ -185,9 +187,8 @@ __global__ __launch_bounds__(BX * BY * ZS) void resident_cg_kernel(Resident a, d
   __shared__ Meeting<nt / 64> meeting;
   const Grid g = a.g;
   const int tid = threadIdx.x;
-  const int nb = gridDim.x;
-  const int wx = blockIdx.x % a.plan.gx, wr = blockIdx.x / a.plan.gx;
-  const int i0 = 1 + wx * BX, j0 = 1 + (wr % a.plan.gy) * BY, k0 = 1 + (wr / a.plan.gy) * BZ;
+  const int wx = bid % gx, wr = bid / gx;
+  const int i0 = 1 + wx * BX, j0 = 1 + (wr % gy) * BY, k0 = 1 + (wr / gy) * BZ;
   auto interior = [&](int i, int j, int k) {
     return i >= 1 && j >= 1 && k >= 1 && i < g.nx && j < g.ny && k < g.nz;
   };
@@ -233,7 +234,7 @@ __global__ __launch_bounds__(BX * BY * ZS) void resident_cg_kernel(Resident a, d
         x = e % BX; z = e / BX;
       } else if ((e -= 2 * fy) < 2 * fx) {
         x = e < fx ? -1 : BX;
-        wx = (int)(blockIdx.x + (e < fx ? -1 : 1)) * XF + (e < fx ? fx : -fx) + e;
+        wx = (bid + (e < fx ? -1 : 1)) * XF + (e < fx ? fx : -fx) + e;
         e %= fx;
         y = e % BY; z = e / BY;
       } else if ((e -= 2 * fx) < 4 * BX) {
@@ -292,7 +293,7 @@ __global__ __launch_bounds__(BX * BY * ZS) void resident_cg_kernel(Resident a, d
       if (lx == 0 || lx == BX - 1) FX[(lx != 0 ? XF / 2 : 0) + (lz + q) * BY + ly] = v[q];
     }
     __syncthreads();
-    double *const X = WX + ((odd ? nb : 0) + (int)blockIdx.x) * XF;
+    double *const X = WX + ((odd ? nb : 0) + bid) * XF;
     for (int e = tid; e < XF; e += nt) put(&X[e], FX[e]);
   };
   auto layer = [&](int odd, int m) {
@@ -328,7 +329,7 @@ __global__ __launch_bounds__(BX * BY * ZS) void resident_cg_kernel(Resident a, d
   publish(1, w);
   const double gbnd2 = uniform(cs->gbnd2);
   int seq = 0;
-  bool here = meet(gam, bsum, slots, seq++, nb, meeting);
+  bool here = meet(gam, bsum, slots, seq++, bid, nb, meeting);
   const double rho0 = gam, bb = bsum + gbnd2;
   const double stop2 = a.tol * a.tol * bb;
 #pragma unroll
@@ -342,11 +343,11 @@ __global__ __launch_bounds__(BX * BY * ZS) void resident_cg_kernel(Resident a, d
   double gold = 1.0, aold = 1.0, gamma = rho0;
   int k = 0, status = 0;
   while (here) {
-    here = meet(gam, del, slots, seq++, nb, meeting);
+    here = meet(gam, del, slots, seq++, bid, nb, meeting);
     if (!here) break;
     gamma = gam;
     const double delta = del;
-    if (a.hist_on && blockIdx.x == 0 && tid == 0 && k < EXCMG_MAX_HISTORY)
+    if (a.hist_on && bid == 0 && tid == 0 && k < EXCMG_MAX_HISTORY)
       cs->hist[k] = bb > 0.0 ? sqrt(gamma / bb) : 0.0;
     if (!isfinite(gamma) || !isfinite(bb)) {
       status = EXCMG_ERR_BREAKDOWN;
@@ -405,7 +406,7 @@ __global__ __launch_bounds__(BX * BY * ZS) void resident_cg_kernel(Resident a, d
 #pragma unroll
   for (int q = 0; q < ZR; ++q)
     if (act[q]) *node(u_, q) = B::ULds ? ul[q * nt] : u[B::ULds ? 0 : q];
-  if (blockIdx.x == 0 && tid == 0) {
+  if (bid == 0 && tid == 0) {
     cs->iter = k;
     cs->rho = gamma;
     cs->rho0 = rho0;
@@ -423,48 +424,91 @@ __global__ __launch_bounds__(BX * BY * ZS) void resident_cg_kernel(Resident a, d
   }
 }
 
-// f(Brick) for brick number b
+template <int BX, int BY, int ZS, int ZR>
+__global__ __launch_bounds__(BX * BY * ZS) void resident_cg_kernel(Resident a, double *u, double *W0, double *W1,
+                                                                    double *WX, double *slots, CgState *cs) {
+  resident_cg<BX, BY, ZS, ZR>(a, u, W0, W1, WX, slots, cs, a.plan.gx, a.plan.gy, blockIdx.x, gridDim.x);
+}
+
+// Several grids of a batch in one launch, each on a range of the workgroups.  Their meetings are apart; the launch lasts
+// as long as the grid with the most iterations.  (A full launch of the largest bricks takes 16 us an iteration, 128^3
+// alone 11 us: the ranges do not keep to XCDs.)
+template <int BX, int BY, int ZS, int ZR>
+__global__ __launch_bounds__(BX * BY * ZS) void b_resident_cg_kernel(BatchList L) {
+  const int first = L.pre[0], e = find_entry(L.pre, L.n, first + blockIdx.x);
+  const int start = L.pre[e], nb = L.pre[e + 1] - start;
+  const BatchEntry &E = entry_at(L, e);
+  Resident a;
+  a.g = E.g;
+  a.rs = E.rs;
+  a.rs.f = as_global(E.rs.f);
+  a.rs.g = as_global(E.rs.g);
+  a.st = E.st;
+  a.tol = E.tol;
+  a.cap = E.cap;
+  a.hist_on = 0;
+  a.out = nullptr;
+  double *const scratch = as_global(E.p1);
+  const int gx = (E.g.nx - 1 + BX - 1) / BX, gy = (E.g.ny - 1 + BY - 1) / BY;
+  resident_cg<BX, BY, ZS, ZR>(a, as_global(E.u), as_global(E.r), as_global(E.p0), scratch + slots_of(nb), scratch,
+                              as_global(E.cs), gx, gy, first + blockIdx.x - start, nb);
+}
+
+__global__ void b_resident_init_kernel(BatchList L) {
+  const BatchEntry &E = entry_at(L, blockIdx.x);
+  resident_init_block({E.p1, slots_of(L.pre[blockIdx.x + 1] - L.pre[blockIdx.x]), E.cs, nullptr});
+}
+
+__global__ void b_mirror_kernel(BatchList L, BatchStatus *stat) {
+  const BatchEntry &E = entry_at(L, blockIdx.x);
+  if (threadIdx.x == 0) mirror(E, E.cs, stat, 0, true);
+}
+
+// f(Brick, its kernel, its batched kernel) for brick number b
 template <typename F>
 void with_brick(int b, F &&f) {
+  auto go = [&](auto br, auto *kernel, auto *batched) { f(br, kernel, batched); };
   switch (b) {
-    case 0: f(Brick<16, 8, 4, 2>{}, resident_cg_kernel<16, 8, 4, 2>); break;
-    case 1: f(Brick<16, 16, 2, 4>{}, resident_cg_kernel<16, 16, 2, 4>); break;
-    case 2: f(Brick<32, 16, 1, 8>{}, resident_cg_kernel<32, 16, 1, 8>); break;
-    default: f(Brick<32, 16, 1, 16>{}, resident_cg_kernel<32, 16, 1, 16>); break;
+    case 0: go(Brick<16, 8, 4, 2>{}, resident_cg_kernel<16, 8, 4, 2>, b_resident_cg_kernel<16, 8, 4, 2>); break;
+    case 1: go(Brick<16, 16, 2, 4>{}, resident_cg_kernel<16, 16, 2, 4>, b_resident_cg_kernel<16, 16, 2, 4>); break;
+    case 2: go(Brick<32, 16, 1, 8>{}, resident_cg_kernel<32, 16, 1, 8>, b_resident_cg_kernel<32, 16, 1, 8>); break;
+    default: go(Brick<32, 16, 1, 16>{}, resident_cg_kernel<32, 16, 1, 16>, b_resident_cg_kernel<32, 16, 1, 16>); break;
   }
 }
-constexpr int kBricks = 4;
+
+// the bricks of grid g; none where g's work arrays do not hold the slots and the packed x faces
+template <typename B>
+ResidentPlan bricks_of(const Grid &g, int b) {
+  const int gx = (g.nx - 1 + B::PX - 3) / (B::PX - 2), gy = (g.ny - 1 + B::PY - 3) / (B::PY - 2);
+  const int gz = (g.nz - 1 + B::BZ - 1) / B::BZ;
+  const long long nb = (long long)gx * gy * gz;
+  if (nb > kGroup * kGroups || slots_of((int)nb) + 2 * nb * B::Xf > g.elems) return {};
+  return {b, gx, gy, gz, B::NT, B::Lds};
+}
 
 }  // namespace
-
-// doubles of the slots and the packed x faces of nb workgroups
-template <typename B>
-long long scratch_doubles(long long nb) { return 3LL * set_slots((int)((nb + kGroup - 1) / kGroup)) + 2 * nb * B::Xf; }
 
 // The bricks of a grid, of those that need no more than `blocks` workgroups (one per CU): the work of an iteration
 // grows with the brick (1.0, 1.4, 2.1 and 4.1 us), the meeting with the workgroups (about 0.4 us with every doubling).
 ResidentPlan resident_plan(const Grid &g, int blocks) {
-  static const double work[kBricks] = {1.0, 1.4, 2.1, 4.1};
+  static const double work[kResidentBricks] = {1.0, 1.4, 2.1, 4.1};
   ResidentPlan best = {};
   double least = 1e300;
   if (g.elems >= (1ll << 29)) return best;
-  for (int b = 0; b < kBricks; ++b)
-    with_brick(b, [&](auto br, auto) {
-      using B = decltype(br);
-      const int gx = (g.nx - 1 + B::PX - 3) / (B::PX - 2), gy = (g.ny - 1 + B::PY - 3) / (B::PY - 2);
-      const int gz = (g.nz - 1 + B::BZ - 1) / B::BZ;
-      const long long nb = (long long)gx * gy * gz;
+  for (int b = 0; b < kResidentBricks; ++b)
+    with_brick(b, [&](auto br, auto, auto) {
+      const ResidentPlan p = bricks_of<decltype(br)>(g, b);
+      const int nb = p.gx * p.gy * p.gz;
       const double t = work[b] + 0.4 * log2((double)nb);
-      if (nb > blocks || t >= least || scratch_doubles<B>(nb) > g.elems) return;
+      if (nb == 0 || nb > blocks || t >= least) return;
       least = t;
-      best = {b, gx, gy, gz, B::NT, B::Lds};
+      best = p;
     });
   return best;
 }
 
 ResidentInit resident_init(const Resident &a) {
-  const int nb = a.plan.gx * a.plan.gy * a.plan.gz;
-  return {a.scratch, 3 * set_slots((nb + kGroup - 1) / kGroup), a.cs, a.out};
+  return {a.scratch, slots_of(a.plan.gx * a.plan.gy * a.plan.gz), a.cs, a.out};
 }
 
 void launch_resident_init(const ResidentInit &i, hipStream_t st) { resident_init_kernel<<<1, 256, 0, st>>>(i); }
@@ -474,9 +518,38 @@ void launch_outcome(const CgState *cs, Outcome *out, hipStream_t st) { outcome_k
 void launch_resident(const Resident &a, hipStream_t st) {
   const ResidentPlan &p = a.plan;
   const int nb = p.gx * p.gy * p.gz;
-  with_brick(p.brick, [&](auto, auto *kernel) {
+  with_brick(p.brick, [&](auto, auto *kernel, auto) {
     kernel<<<nb, p.threads, p.lds, st>>>(a, a.u, a.W0, a.W1, a.scratch + resident_init(a).n, a.scratch, a.cs);
   });
+}
+
+int brick_blocks(const Grid &g, int brick) {
+  int n = 0;
+  with_brick(brick, [&](auto br, auto, auto) {
+    const ResidentPlan p = bricks_of<decltype(br)>(g, brick);
+    n = p.gx * p.gy * p.gz;
+  });
+  return n;
+}
+
+double brick_time(int brick) {
+  static const double t[kResidentBricks] = {4.5, 5.1, 6.5, 11.1};
+  return t[brick];
+}
+
+void launch_b_resident_init(const BatchList &L, hipStream_t st) {
+  if (L.n > 0) b_resident_init_kernel<<<L.n, 256, 0, st>>>(L);
+}
+
+void launch_b_resident(int brick, const BatchList &L, hipStream_t st) {
+  with_brick(brick, [&](auto br, auto, auto *kernel) {
+    using B = decltype(br);
+    kernel<<<L.total, B::NT, B::Lds, st>>>(L);
+  });
+}
+
+void launch_b_mirror(const BatchList &L, BatchStatus *stat, hipStream_t st) {
+  if (L.n > 0) b_mirror_kernel<<<L.n, 64, 0, st>>>(L, stat);
 }
 
 }  // namespace excmg
