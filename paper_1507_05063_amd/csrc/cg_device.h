@@ -70,6 +70,12 @@ __device__ __forceinline__ T *as_global(T *p) {
   return (T *)(__attribute__((address_space(1))) T *)p;
 }
 
+template <typename T>
+__device__ __forceinline__ T *at_plane(T *a, unsigned bytes, unsigned k) {
+  using C = std::conditional_t<std::is_const_v<T>, const char, char>;
+  return reinterpret_cast<T *>(reinterpret_cast<C *>(a) + (unsigned long long)bytes * k);
+}
+
 // entry e of a batched launch; nothing writes the tables while a kernel runs, so its fields are read as constants
 // (scalar loads)
 __device__ __forceinline__ const BatchEntry &entry_at(const BatchList &L, int e) {

@@ -276,6 +276,7 @@ struct excmg_handle {
   double *xfin = nullptr;
   Grid gxfin = {};
   int two_pairs = 0;  // pairs of the last two-step solve (kernel timing)
+  bool late = false;  // this call's outputs lie over its inputs: nothing is written there while it may start over
   bool apart = false; // this call relaxes no grid by the resident CG (a workgroup of it gave up waiting)
   // graphs of a batched round's CG iterations (excmg_solve_batched, on the batch's first handle), by launch shape
   struct BatchGraph {
@@ -510,7 +511,10 @@ void bind_output(excmg_handle *h, double *out, const double *avoid) {
 // the binding lasts for the call
 struct OutputBinding {
   excmg_handle *h;
-  ~OutputBinding() { h->xfin = nullptr; }
+  ~OutputBinding() {
+    h->xfin = nullptr;
+    h->late = false;
+  }
 };
 
 // Iterations 2 * pair and 2 * pair + 1 of grid l by the two-step sweeps.
@@ -1061,6 +1065,10 @@ int cascade(excmg_handle *h, int mode, const double *f, const double *g, excmg_s
   };
   for (int l = 0; l < L; ++l) {
     Level &lv = lo.lev[l];
+    if (h->late && l == L - 1) {  // the finest grid's sweeps may keep a vector in the output
+      const int e = resolve(l);
+      if (e) return e;
+    }
     if (h->lev_ev[l]) HIPCHECK(hipEventRecord(h->lev_ev[l], s));
     RhsSrc rs;
     rs.gf = lo.gdense;
@@ -2017,14 +2025,15 @@ int solve_on(excmg_handle *h, const double *f, const double *g, double *u, doubl
   memset(li.launches, 0, sizeof(li.launches));
   Layout &lo = h->lo;
   const Level &fin = lo.lev[lo.L - 1];
-  // An output over f or g is written only once the cascade has ended well: one that starts over reads them again.
+  // An output over f or g is written only once the cascade cannot start over, which reads them again.
   const long long nodes = lo.gdense.nodes();
   auto over = [&](const double *in) {
     return overlap(u, nodes, in, nodes) || (u_ext && overlap(u_ext, nodes, in, nodes));
   };
   const bool late = over(f) || over(g);
+  h->late = late;
   OutputBinding binding{h};
-  if (!late) bind_output(h, u, nullptr);
+  bind_output(h, u, nullptr);  // (f and g are last read by the finest grid's residual, before the sweeps)
   auto finish = [&]() {
     if (u_ext) {  // EXP_true also writes u to the caller's array from the same read of u_h
       Tick t(h, EXCMG_K_EXP_TRUE, lo.L - 1);

@@ -19,9 +19,13 @@ namespace {
 // iteration move 128.  The coefficients of the second iteration come from pass G's sums (two_after_g), which are
 // exact consequences of r1 = r - alpha q and p1 = r1 + beta0 p, so the iterates are CG's; the residual norms that the
 // stopping test and beta use are summed directly in pass U.
-// Measured at 511^3 unknowns in FP64: pass G 0.63 ms, pass U 1.39 ms (4.6 TB/s of its 48 bytes), 2.05 ms a pair, where
-// two iterations of the two-pass form take 3.1 ms; in FP32 1.17 against 2.0 ms; at 255^3 0.27 against 0.38 ms.  Pass G is
-// bound by its LDS reads and FP64 instructions (a step of a workgroup takes 1 us), pass U by HBM.
+// Measured at 511^3 unknowns in FP64: pass G 0.57 ms, pass U 1.39 ms (4.6 TB/s of its 48 bytes), 1.97 ms a pair, where
+// two iterations of the two-pass form take 3.1 ms; in FP32 1.13 against 2.0 ms; at 255^3 0.26 against 0.38 ms.  Pass G is
+// bound by its LDS reads and vector instructions (half of each unit's time in a step, with a barrier between), pass U by
+// HBM.  What does not depend on the data is kept out of the vector instructions for that: masks that a whole wave shares
+// are branches, nodes outside the grid are zeroed once and their threads write to a spare row, and offsets stay 32 bits
+// (98 vector instructions a step and wave instead of 138: pass G 0.63 -> 0.57 ms at 511^3, 106 -> 89 us at 255^3, in
+// FP32 427 -> 355 us).
 //
 // Tile: a wavefront covers one 64-node row segment, each lane two rows (12 LDS reads for two nodes instead of 18),
 // MW such waves the rows of the region where q (or p1) is needed (2 MW rows: the output rows and one more on each
@@ -41,13 +45,20 @@ struct Two {
   static_assert(Ring <= NT, "one ring node per thread at most");
 };
 
-// T: precision; D: planes of loads in flight; FIRST: p = r (no p_old).  P: the policy of the pass: mid(m, k, on, idx,
-// r, p, q) at q's plane k (returns the staged second operand; on: an output node of the tile), fin(m, k, idx, c, t) at
-// an output node of plane k, two planes behind (c: the second operand there, t: M of it);
-// plane, center<S>() for the pass's own loads, place(m, ...) once for the node's place in the pass's other arrays.
+// plane k >= 0 of an array in layout g (a plane is under 2^32 bytes: two scalar multiplications)
+template <typename T>
+__device__ __forceinline__ T *plane_of(T *a, const Grid &g, int k) {
+  return at_plane(a + g.off, (unsigned)(g.sz * (long long)sizeof(T)), (unsigned)k);
+}
+
+// T: precision; D: planes of loads in flight; FIRST: p = r (no p_old).  P: the policy of the pass: mid(m, row, off, k, r,
+// p, q) at q's plane k (row: the tile puts out row m of plane k; returns the staged second operand), fin(m, row, off, k,
+// c, t) two planes behind (c: the second operand there, t: M of it); center<S>() for the pass's own loads, place(m, ...)
+// once for the node's place in the pass's other arrays, lane: whether the thread's column lies in the grid.
 template <typename T, int D, int TY, bool FIRST, typename P>
 __device__ __forceinline__ void march2(const Sweep &sw, const T *rin, const T *pin, const Grid &gp, T beta, P &pol,
-                                       T (*tp)[Two<TY>::PH][Two<TY>::PW], T (*tq)[Two<TY>::QH][Two<TY>::QW], int bid,
+                                       T (*tp)[Two<TY>::PH + 1][Two<TY>::PW],
+                                       T (*tq)[Two<TY>::QH + 2][Two<TY>::QW], int bid,
                                        int nb, bool remap) {
   using W = Two<TY>;
   constexpr int U = D % 2 == 0 ? D : 2 * D;
@@ -66,20 +77,26 @@ __device__ __forceinline__ void march2(const Sweep &sw, const T *rin, const T *p
   const int d = side ? ((sl & 1) ? W::QW - 1 : 0) : lane + 1;
   const int b0 = RP * (side ? sl >> 1 : w);
   const int i = i0 - 1 + d, j = j0 - 1 + b0;
-  bool in[RP], on[RP];
-  unsigned offR[NL], offP[NL], own[RP];
+  // rows of the tile that are output nodes of the grid: the same for a whole wave
+  bool in[RP], row[RP];
+  unsigned offR[NL], offP[NL];
+  int wp[RP], wq[RP];
   const bool xin = i >= 1 && i < g.nx;
   const unsigned ci = clampi(i, 1, g.nx - 1);
 #pragma unroll
   for (int m = 0; m < RP; ++m) {
     in[m] = xin && j + m >= 1 && j + m < g.ny;
-    on[m] = !side && in[m] && b0 + m >= 1 && b0 + m <= W::QH - 2;
+    const int b = RP * w + m;
+    row[m] = !side && b >= 1 && b <= W::QH - 2 && j0 - 1 + b < g.ny;
     const unsigned cj = clampi(j + m, 1, g.ny - 1);
     offR[m] = (cj * (unsigned)g.sy + ci) * (unsigned)sizeof(T);
     offP[m] = (cj * (unsigned)gp.sy + ci) * (unsigned)sizeof(T);
-    own[m] = offR[m];
     pol.place(m, ci, cj);
+    // a node outside the grid is 0 in both buffers for good, and its thread writes to the spare row
+    wp[m] = in[m] ? b0 + 1 + m : W::PH;
+    wq[m] = in[m] ? b0 + 1 + m : W::QH + 1;
   }
+  pol.lane = xin;
   // ring node of p's region
   int ra, rc;
   {
@@ -94,7 +111,10 @@ __device__ __forceinline__ void march2(const Sweep &sw, const T *rin, const T *p
     }
   }
   const int gi = i0 - 2 + rc, gj = j0 - 2 + ra;
-  const bool rin_ok = gi >= 1 && gi < g.nx && gj >= 1 && gj < g.ny;
+  if (!(gi >= 1 && gi < g.nx && gj >= 1 && gj < g.ny)) ra = W::PH;
+  for (int e = tid; e < 2 * (W::PH + 1) * W::PW; e += W::NT) (&tp[0][0][0])[e] = T(0);
+  for (int e = tid; e < 2 * (W::QH + 2) * W::QW; e += W::NT) (&tq[0][0][0])[e] = T(0);
+  __syncthreads();
   {
     const unsigned cj = clampi(gj, 1, g.ny - 1), cx = clampi(gi, 1, g.nx - 1);
     offR[RP] = (cj * (unsigned)g.sy + cx) * (unsigned)sizeof(T);
@@ -102,12 +122,12 @@ __device__ __forceinline__ void march2(const Sweep &sw, const T *rin, const T *p
   }
   T rr[D][NL], pp[D][NL];
   auto fetch = [&](T(&r)[NL], T(&p)[NL], int kk) {
-    const long long kc = clampi(kk, 1, g.nz - 1);
-    const T *rb = rin + (g.off + kc * g.sz);
+    const int kc = clampi(kk, 1, g.nz - 1);
+    const T *rb = plane_of(rin, g, kc);
 #pragma unroll
     for (int m = 0; m < NL; ++m) r[m] = *at_byte(rb, offR[m]);
     if constexpr (!FIRST) {
-      const T *pb = pin + (gp.off + kc * gp.sz);
+      const T *pb = plane_of(pin, gp, kc);
 #pragma unroll
       for (int m = 0; m < NL; ++m) p[m] = *at_byte(pb, offP[m]);
     }
@@ -124,22 +144,33 @@ __device__ __forceinline__ void march2(const Sweep &sw, const T *rin, const T *p
   for (int q = 0; q < D; ++q) fetch(rr[q], pp[q], k0 - 2 + q);
   static_for<D>([&](auto qc) {  // step q's own loads are of plane k0 - 3 + q
     constexpr int q = decltype(qc)::value;
-    pol.template center<q>(own, clampi(k0 - 3 + q, k0, k1 - 1));
+    pol.template center<q>(offR, clampi(k0 - 3 + q, k0, k1 - 1));
   });
-  const int qr0 = max(b0 - 1, 0), qr3 = min(b0 + RP, W::QH - 1);  // LDS rows of the second product (clamped: unused)
   auto body = [&](auto pb, auto pr, int s) {
     const int PB = pb;  // LDS buffer of the step
     constexpr int PR = decltype(pr)::value;  // register set of the step
     const int kp = k0 - 2 + s;
     const bool kin = kp >= 1 && kp < g.nz;
-    T rnew[RP];
+    // the offsets are new to the compiler in every step (and block of it): it would else keep them widened to 64 bits and
+    // add them to the planes' bases in vector registers
+#pragma unroll
+    for (int m = 0; m < NL; ++m) {
+      __asm__ volatile("" : "+v"(offR[m]));
+      if constexpr (!FIRST) __asm__ volatile("" : "+v"(offP[m]));
+    }
+    T rnew[RP], pnew[NL] = {};
+    if (kin) {
+      __asm__ volatile("");  // a branch, not selects
+#pragma unroll
+      for (int m = 0; m < NL; ++m) pnew[m] = val(rr[PR][m], pp[PR][m]);
+    }
 #pragma unroll
     for (int m = 0; m < RP; ++m) {
       rnew[m] = rr[PR][m];
-      tp[PB][b0 + 1 + m][d + 1] = (kin && in[m]) ? val(rr[PR][m], pp[PR][m]) : T(0);
-      tq[PB][b0 + m][d] = qreg[m];
+      tp[PB][wp[m]][d + 1] = pnew[m];
+      tq[PB][wq[m]][d] = qreg[m];
     }
-    tp[PB][ra][rc] = (kin && rin_ok) ? val(rr[PR][RP], pp[PR][RP]) : T(0);
+    tp[PB][ra][rc] = pnew[RP];
     __syncthreads();
     fetch(rr[PR], pp[PR], kp + D);
     {  // q = M p of plane kp - 1 at the own nodes
@@ -159,19 +190,22 @@ __device__ __forceinline__ void march2(const Sweep &sw, const T *rin, const T *p
         const T q = A1[m] + S;
         A1[m] = S1[m] + (c0 * c[m + 1] + cx * x[m + 1] + cy * y + cxy * (x[m] + x[m + 2]));
         S1[m] = S;
-        const T v = pol.template mid<PR>(m, ko && on[m], own[m], k, rown[m], pown[m], q);
-        qreg[m] = (kq && in[m]) ? v : T(0);
+        qreg[m] = pol.template mid<PR>(m, ko && row[m], offR[m], k, rown[m], pown[m], q);
+        if (!kq) {
+          __asm__ volatile("");
+          qreg[m] = T(0);
+        }
         rown[m] = rnew[m];
         pown[m] = c[m + 1];
       }
-      pol.template center<PR>(own, clampi(k + D, k0, k1 - 1));
+      pol.template center<PR>(offR, clampi(k + D, k0, k1 - 1));
     }
     __builtin_amdgcn_sched_barrier(0);  // the second product's LDS reads stay behind the first's (registers)
     if (!side) {  // the second product of plane kp - 3
       T c[RP + 2], x[RP + 2];
 #pragma unroll
       for (int a = 0; a < RP + 2; ++a) {
-        const T *row = &tq[PB][a == 0 ? qr0 : (a == RP + 1 ? qr3 : b0 + a - 1)][d - 1];
+        const T *row = &tq[PB][b0 + a][d - 1];
         c[a] = row[1];
         x[a] = row[0] + row[2];
       }
@@ -184,14 +218,17 @@ __device__ __forceinline__ void march2(const Sweep &sw, const T *rin, const T *p
         const T o = A2[m] + S;
         A2[m] = S2[m] + (c0 * c[m + 1] + cx * x[m + 1] + cy * y + cxy * (x[m] + x[m + 2]));
         S2[m] = S;
-        pol.fin(m, ko && on[m], own[m], k, cprev[m], o);
+        pol.fin(m, ko && row[m], offR[m], k, cprev[m], o);
         cprev[m] = c[m + 1];
       }
     }
   };
-  if constexpr (D == 1) {  // one copy of the body: the least registers
+  if constexpr (D == 1) {
 #pragma unroll 1
-    for (int s = 0; s < ns; ++s) body(s & 1, std::integral_constant<int, 0>{}, s);
+    for (int s = 0; s < ns; s += 2) {
+      body(0, std::integral_constant<int, 0>{}, s);
+      if (s + 1 < ns) body(1, std::integral_constant<int, 0>{}, s + 1);
+    }
   } else {
     int s = 0;
     for (; s + U <= ns; s += U) {
@@ -210,13 +247,16 @@ __device__ __forceinline__ void march2(const Sweep &sw, const T *rin, const T *p
 template <typename T, int RP>
 struct PolG {
   T r2[RP] = {}, r3[RP] = {};  // r of the two planes behind rown's
+  // (of all lanes, whether their nodes lie in the grid or not: those of the others are left out at the end)
   double pq = 0, rq = 0, qq = 0, qt = 0, rt = 0;
+  bool lane;
   __device__ __forceinline__ void place(int, unsigned, unsigned) {}
   template <int S>
-  __device__ __forceinline__ void center(const unsigned (&)[RP], int) {}
+  __device__ __forceinline__ void center(const unsigned (&)[RP + 1], int) {}
   template <int S>
-  __device__ __forceinline__ T mid(int m, bool on, unsigned, int, T r, T p, T q) {
-    if (on) {
+  __device__ __forceinline__ T mid(int m, bool row, unsigned &, int, T r, T p, T q) {
+    if (row) {
+      __asm__ volatile("");
       pq += (double)p * (double)q;
       rq += (double)r * (double)q;
       qq += (double)q * (double)q;
@@ -225,8 +265,9 @@ struct PolG {
     return q;
   }
   T rcur[RP];
-  __device__ __forceinline__ void fin(int m, bool on, unsigned, int, T c, T t) {
-    if (on) {
+  __device__ __forceinline__ void fin(int m, bool row, unsigned &, int, T c, T t) {
+    if (row) {
+      __asm__ volatile("");
       qt += (double)c * (double)t;
       rt += (double)r3[m] * (double)t;
     }
@@ -241,7 +282,7 @@ struct PolU {
   Grid gu, gpo;  // layouts of u and r, and of pout
   unsigned offo[RP];
   T alpha, alpha1, beta0;
-  bool single;
+  bool single, lane;
   T uu[D][RP];
   T s2[RP] = {}, s3[RP] = {}, scur[RP];  // r1 of this plane and the two behind
   double rho1 = 0, rho2 = 0, cs = 0, cd = 0;
@@ -249,29 +290,31 @@ struct PolU {
     offo[m] = (cj * (unsigned)gpo.sy + ci) * (unsigned)sizeof(T);
   }
   template <int S>
-  __device__ __forceinline__ void center(const unsigned (&own)[RP], int k) {
-    const T *ub = u + (gu.off + k * gu.sz);
+  __device__ __forceinline__ void center(const unsigned (&own)[RP + 1], int k) {
+    const T *ub = plane_of(u, gu, k);
 #pragma unroll
     for (int m = 0; m < RP; ++m) uu[S][m] = ld1<NTP>(at_byte(ub, own[m]));
   }
   template <int S>
-  __device__ __forceinline__ T mid(int m, bool on, unsigned own, int k, T r, T p, T q) {
+  __device__ __forceinline__ T mid(int m, bool row, unsigned &own, int k, T r, T p, T q) {
     const T r1 = r - alpha * q;
     const T v = single ? p : r1 + beta0 * p;
-    if (on) {
-      st1<NTP>(uu[S][m] + alpha * p + alpha1 * v, at_byte(u + (gu.off + k * gu.sz), own));
-      st1<NTP>(v, at_byte(pout + (gpo.off + k * gpo.sz), offo[m]));
+    if (row && lane) {
+      __asm__ volatile("" : "+v"(own), "+v"(offo[m]));
+      st1<NTP>(uu[S][m] + alpha * p + alpha1 * v, at_byte(plane_of(u, gu, k), own));
+      st1<NTP>(v, at_byte(plane_of(pout, gpo, k), offo[m]));
       rho1 += (double)r1 * (double)r1;
       cs += (double)r1 * (double)r;
     }
     scur[m] = r1;
     return v;
   }
-  __device__ __forceinline__ void fin(int m, bool on, unsigned own, int k, T, T t) {
-    if (on) {
+  __device__ __forceinline__ void fin(int m, bool row, unsigned &own, int k, T, T t) {
+    if (row && lane) {
+      __asm__ volatile("" : "+v"(own));
       const T r1 = s3[m];
       const T r2 = r1 - alpha1 * t;
-      st1<NTP>(r2, at_byte(rout + (gu.off + k * gu.sz), own));
+      st1<NTP>(r2, at_byte(plane_of(rout, gu, k), own));
       rho2 += (double)r2 * (double)r2;
       cd += (double)r2 * (double)r1;
     }
@@ -424,14 +467,16 @@ template <typename T, int D, int TY>
 __device__ __forceinline__ bool two_g(const Sweep &sw, const TwoVecs<T> &vec, CgState *cs, double *parts, int bid,
                                       int nb, bool remap) {
   using W = Two<TY>;
-  __shared__ T tp[2][W::PH][W::PW];
-  __shared__ T tq[2][W::QH][W::QW];
+  __shared__ T tp[2][W::PH + 1][W::PW];
+  __shared__ T tq[2][W::QH + 2][W::QW];
   const int n = cs->pairs;
   const TwoBufs<T> b = two_bufs(n, vec, sw.g);
   PolG<T, W::RP> pol;
   if (n == 0) march2<T, D, TY, true>(sw, b.r, b.r, sw.g, T(0), pol, tp, tq, bid, nb, remap);
   else march2<T, D, TY, false>(sw, b.r, b.p, b.gp, (T)cs->beta, pol, tp, tq, bid, nb, remap);
   double v[5] = {pol.pq, pol.rq, pol.qq, pol.qt, pol.rt}, tot[5];
+#pragma unroll
+  for (int k = 0; k < 5; ++k) v[k] = pol.lane ? v[k] : 0.0;
   if (!last_sums<5, W::NT>(v, parts, &cs->count, bid, nb, tot)) return false;
   if (threadIdx.x == 0 && !cs->tune) two_after_g<T>(cs, tot);
   return true;
@@ -441,8 +486,8 @@ template <typename T, int D, bool NTP, int TY>
 __device__ __forceinline__ bool two_u(const Sweep &sw, const TwoVecs<T> &vec, CgState *cs, double *parts, int bid,
                                       int nb, bool remap) {
   using W = Two<TY>;
-  __shared__ T tp[2][W::PH][W::PW];
-  __shared__ T tq[2][W::QH][W::QW];
+  __shared__ T tp[2][W::PH + 1][W::PW];
+  __shared__ T tq[2][W::QH + 2][W::QW];
   const int n = cs->pairs;
   const TwoBufs<T> b = two_bufs(n, vec, sw.g);
   PolU<T, D, NTP, W::RP> pol;
