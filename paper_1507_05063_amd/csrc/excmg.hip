@@ -1367,6 +1367,7 @@ int batch_iterations(excmg_handle *h0, const char *ws, int it, int nb64, int nb3
 }
 
 // The resident CG in a batch.  A launch holds as many grids, in bricks of one kind, as the CUs take workgroups.
+constexpr int kIterGuess = 50;
 struct ResidentPack {
   int brick, blocks;
   std::vector<int> problems;
@@ -1374,10 +1375,13 @@ struct ResidentPack {
 
 // The grids gs (of the problems ps) in launches.  Small bricks iterate fastest, large ones put more grids into a launch:
 // for each kind of brick as the smallest one allowed (a grid that needs more than `cus` of it takes the next), the
-// launches are filled largest grid first, and the kind whose launches together take the least time an iteration is
-// taken.  24 problems of 32 to 64 cells an axis relax their finest grids in three launches of 0.45 ms (2.2 ms the whole
-// batch), where the flattened sweeps, four launches an iteration, took 6 ms (9.7 ms the whole batch).
-std::vector<ResidentPack> pack_residents(const std::vector<int> &ps, const std::vector<Grid> &gs, int cus) {
+// launches are filled, and the kind whose launches together take the least time is taken.  A launch lasts as long as
+// its slowest grid, so grids that are expected to take similar numbers of iterations (like the grid before) go
+// together: 23 grids of 32^3 to 192 x 128 x 64 cells, 37 to 239 iterations each, take 9 ms so and 11 ms by size.
+// 24 problems of 32 to 64 cells an axis relax their finest grids in three launches of 0.45 ms (2.2 ms the whole batch),
+// where the flattened sweeps, four launches an iteration, took 6 ms (9.7 ms the whole batch).
+std::vector<ResidentPack> pack_residents(const std::vector<int> &ps, const std::vector<Grid> &gs, const std::vector<int> &expect,
+                                         int cus) {
   std::vector<ResidentPack> best;
   double least = 1e300;
   const int n = (int)ps.size();
@@ -1396,7 +1400,10 @@ std::vector<ResidentPack> pack_residents(const std::vector<int> &ps, const std::
       for (int k = least_brick; k < kResidentBricks && !found; ++k) found = fits(k);
       for (int k = least_brick - 1; k >= 0 && !found; --k) found = fits(k);
     }
-    std::sort(order.begin(), order.end(), [&](int a, int b) { return nb[a] != nb[b] ? nb[a] > nb[b] : a < b; });
+    std::sort(order.begin(), order.end(), [&](int a, int b) {
+      if (expect[a] != expect[b]) return expect[a] > expect[b];
+      return nb[a] != nb[b] ? nb[a] > nb[b] : a < b;
+    });
     std::vector<ResidentPack> packs;
     double t = 0.0;
     for (int q : order) {
@@ -1404,7 +1411,7 @@ std::vector<ResidentPack> pack_residents(const std::vector<int> &ps, const std::
       for (auto &c : packs)
         if (!p && c.brick == brick[q] && c.blocks + nb[q] <= cus) p = &c;
       if (!p) {
-        t += brick_time(brick[q]);
+        t += brick_time(brick[q]) * expect[q];  // (of the launch's grids the slowest)
         packs.push_back({brick[q], 0, {}});
         p = &packs.back();
       }
@@ -1497,7 +1504,7 @@ int batched_solve(excmg_handle *const *hs, int count, const double *const *f, co
     }
   std::vector<int> lev(count, 0), ph(count, kPhStart), outer(count, 0), inner(count, 0), fresh(count, 0);
   // problems on a grid of one launch this round: direct solves (small, larger), the one-workgroup CG, the resident CG
-  std::vector<int> dsmall, dlarge, small, res;
+  std::vector<int> dsmall, dlarge, small, res, expect;
   std::vector<Grid> res_grid;
   std::vector<char> apart(count, 0);  // a workgroup of the resident CG gave up waiting: this problem runs without it
   int final_status = EXCMG_OK, remaining = count;
@@ -1537,6 +1544,7 @@ int batched_solve(excmg_handle *const *hs, int count, const double *const *f, co
     small.clear();
     res.clear();
     res_grid.clear();
+    expect.clear();
     int lds = 0, unknowns = 0, scells[3] = {}, lcells[3] = {};
     for (int b = 0; b < count; ++b) {
       const int l = lev[b];
@@ -1558,6 +1566,8 @@ int batched_solve(excmg_handle *const *hs, int count, const double *const *f, co
           if (lv.res.threads && !apart[b] && s != hipStreamPerThread) {
             res.push_back(b);
             res_grid.push_back(lv.g);
+            const int before = hstat[b].m[0].iter;  // on the grid below; none where that was solved directly
+            expect.push_back(before > 0 ? before : kIterGuess);
             ph[b] = kPhSmall;
           } else if (kind == kBSmall) {
             small.push_back(b);
@@ -1606,7 +1616,7 @@ int batched_solve(excmg_handle *const *hs, int count, const double *const *f, co
     // one list for all of them, a launch each for a part of it
     for (const auto *v : {&dsmall, &dlarge, &small})
       for (int b : *v) add(kListSmall, lev[b], b, 0, 0, 0);
-    const std::vector<ResidentPack> packs = pack_residents(res, res_grid, cus);
+    const std::vector<ResidentPack> packs = pack_residents(res, res_grid, expect, cus);
     for (const auto &p : packs)
       for (int b : p.problems) add(kListSmall, lev[b], b, brick_blocks(hs[b]->lo.lev[lev[b]].g, p.brick), 0, 0);
     HIPCHECK(hipMemcpyAsync(lists_dev, lists_host, (size_t)kListKinds * lb, hipMemcpyHostToDevice, s));
