@@ -147,8 +147,9 @@ constexpr unsigned kTimingEvent = hipEventDisableSystemFence;
 constexpr size_t kDeferBytes = 144;
 static_assert(sizeof(Outcome) <= kDeferBytes, "a deferred outcome");
 // the outcomes' place in the pinned memory, past a whole CG state, and what a handle pins
-constexpr size_t kPinOutcomes = 4096, kPinBytes = 8192;
-static_assert(sizeof(CgState) <= kPinOutcomes && EXCMG_MAX_LEVELS * sizeof(Outcome) <= kPinBytes - kPinOutcomes, "pinned");
+constexpr size_t kPinOutcomes = 4096, kPinMarks = 7168, kPinBytes = 8192;
+static_assert(sizeof(CgState) <= kPinOutcomes && kPinOutcomes + EXCMG_MAX_LEVELS * sizeof(Outcome) <= kPinMarks &&
+              kPinMarks + (EXCMG_MAX_LEVELS + 1) * sizeof(long long) <= kPinBytes, "pinned");
 
 // The two-step sweeps relax the grids above this size.  On smaller grids a step of the march, about 1.4 us whatever the grid, outweighs the bytes saved: at 127^3 unknowns a
 // pair takes 64 us, four self-finalizing sweeps 62 us.
@@ -256,7 +257,7 @@ struct excmg_handle {
   double *inv_m[3];
   int *flag;
   std::vector<double> inv_m_host[3];
-  hipEvent_t lev_ev[EXCMG_MAX_LEVELS + 1];
+  int clock_khz = 0;  // of wall_clock64()
   // kernel timing
   std::vector<hipEvent_t> pool;
   std::vector<TimedLaunch> timed;
@@ -302,8 +303,6 @@ struct excmg_handle {
   ~excmg_handle() {
     drop_graphs();
     if (cap) (void)hipStreamDestroy(cap);
-    for (int l = 0; l <= EXCMG_MAX_LEVELS; ++l)
-      if (lev_ev[l]) (void)hipEventDestroy(lev_ev[l]);
     for (auto &ev : pool)
       if (ev) (void)hipEventDestroy(ev);
     if (pin_host) (void)hipHostFree(pin_host);
@@ -407,6 +406,12 @@ int read_hist(excmg_handle *h, CgState *dst, const CgState *src) { return read_r
 Outcome *outcome_slot(excmg_handle *h, int l) {
   char *base = h->noalloc ? h->defer_dev : (char *)h->pin_dev + kPinOutcomes;
   return (Outcome *)base + l;
+}
+
+// Where the first kernel of grid l (of what follows the cascade: l = L) puts its start's time.  (An event between two
+// grids keeps the GPU idle for 4.5 us.)
+long long *mark_slot(excmg_handle *h, int l) {
+  return h->noalloc ? nullptr : (long long *)((char *)h->pin_dev + kPinMarks) + l;
 }
 
 // Per-level iteration counts of CG-class timed launches, to drop launches made after convergence.
@@ -912,6 +917,7 @@ int direct_solve(excmg_handle *h, int l, const RhsSrc &rs, const double *gdat, b
   a.st = lv.st;
   a.cs = h->cs;
   a.out = defer ? outcome_slot(h, l) : nullptr;
+  a.mark = mark_slot(h, l);
   a.A = h->r;
   a.B = h->p0;
   a.parts = h->partials;
@@ -1069,7 +1075,6 @@ int cascade(excmg_handle *h, int mode, const double *f, const double *g, excmg_s
       const int e = resolve(l);
       if (e) return e;
     }
-    if (h->lev_ev[l]) HIPCHECK(hipEventRecord(h->lev_ev[l], s));
     RhsSrc rs;
     rs.gf = lo.gdense;
     rs.f = f;
@@ -1102,6 +1107,8 @@ int cascade(excmg_handle *h, int mode, const double *f, const double *g, excmg_s
     } else if (l <= 1) {
       {
         Tick t(h, EXCMG_K_OTHER, l);
+        ResidentInit init = {};
+        if ((init.mark = mark_slot(h, l))) launch_resident_init(init, s);
         launch_set_boundary(lo.gdense, mode == 0 ? g : nullptr, lv.stride, lv.g, lv.u, 1, s);
       }
       // DSOLVE: the sine-transform solve or single-workgroup CG, or on larger grids the CG sweeps from u = 0
@@ -1120,11 +1127,14 @@ int cascade(excmg_handle *h, int mode, const double *f, const double *g, excmg_s
       }
     } else {
       const bool resident = lv.res.threads && !h->apart;
+      ResidentInit init = {};
+      if (resident) init = resident_init(resident_args(h, l, rs, st));
+      init.mark = mark_slot(h, l);
       {
         Tick t(h, EXCMG_K_EXP_FINITE, l);
         launch_initial_guess(guess_kind(h->p.flags), lo.lev[l - 1].g, lo.lev[l - 1].u, lo.lev[l - 2].g,
                              lo.lev[l - 2].u, lo.gdense, mode == 0 ? g : nullptr, lv.stride, lv.g, lv.u,
-                             resident ? resident_init(resident_args(h, l, rs, st)) : ResidentInit{}, s);
+                             init, s);
       }
       e = last_error();
       if (e) return e;
@@ -1155,7 +1165,6 @@ int cascade(excmg_handle *h, int mode, const double *f, const double *g, excmg_s
       st->relres[l] = rr;
     }
   }
-  if (h->lev_ev[L]) HIPCHECK(hipEventRecord(h->lev_ev[L], s));
   finish();
   int e = last_error();
   if (!e) e = resolve(L);
@@ -1187,13 +1196,11 @@ int run_cascade(excmg_handle *h, int mode, const double *f, const double *g, exc
 
 void fill_level_stats(excmg_handle *h, excmg_stats *st) {
   if (!st) return;
-  const bool ev = h->lev_ev[h->lo.L] != nullptr;
-  if (ev) (void)hipEventSynchronize(h->lev_ev[h->lo.L]);
+  const long long *mark = h->noalloc ? nullptr : (const long long *)((const char *)h->pin_host + kPinMarks);
   st->levels = h->lo.L;
   for (int l = 0; l < h->lo.L; ++l) {
     for (int d = 0; d < 3; ++d) st->n[l][d] = h->lo.lev[l].n[d];
-    float ms = 0.0f;
-    if (ev && hipEventElapsedTime(&ms, h->lev_ev[l], h->lev_ev[l + 1]) == hipSuccess) st->ms_level[l] = ms;
+    if (mark && h->clock_khz > 0) st->ms_level[l] = (double)(mark[l + 1] - mark[l]) / h->clock_khz;
   }
 }
 
@@ -1966,12 +1973,7 @@ int excmg_setup(const excmg_problem *p, void *workspace, size_t bytes, void *hip
       return EXCMG_ERR_HIP;
     }
   }
-  for (int l = 0; l <= EXCMG_MAX_LEVELS; ++l) {
-    if (hipEventCreateWithFlags(&h->lev_ev[l], kTimingEvent) != hipSuccess) {
-      delete h;
-      return EXCMG_ERR_HIP;
-    }
-  }
+  if (hipDeviceGetAttribute(&h->clock_khz, hipDeviceAttributeWallClockRate, h->device) != hipSuccess) h->clock_khz = 0;
   if (ensure_pinned(h, kPinBytes) != EXCMG_OK ||
       hipStreamCreateWithFlags(&h->cap, hipStreamNonBlocking) != hipSuccess) {
     delete h;
@@ -2047,10 +2049,11 @@ int solve_on(excmg_handle *h, const double *f, const double *g, double *u, doubl
   auto finish = [&]() {
     if (u_ext) {  // EXP_true also writes u to the caller's array from the same read of u_h
       Tick t(h, EXCMG_K_EXP_TRUE, lo.L - 1);
-      launch_exp_true(fin.g, fin.u, lo.lev[lo.L - 2].g, lo.lev[lo.L - 2].u, lo.gdense, u_ext, u, h->stream);
+      launch_exp_true(fin.g, fin.u, lo.lev[lo.L - 2].g, lo.lev[lo.L - 2].u, lo.gdense, u_ext, u,
+                      mark_slot(h, lo.L), h->stream);
     } else {
       Tick t(h, EXCMG_K_OTHER, lo.L - 1);
-      launch_copy(fin.g, fin.u, lo.gdense, u, h->stream);
+      launch_copy(fin.g, fin.u, lo.gdense, u, mark_slot(h, lo.L), h->stream);
     }
   };
   const int status = run_cascade(h, 0, f, g, st, h->noalloc ? nullptr : &li, [&]() {
@@ -2116,8 +2119,9 @@ int excmg_adjoint(excmg_handle *h, const double *G, double *dLdf, double *dLdg, 
   auto over = [&](const double *out) { return out && overlap(out, nodes, G, nodes); };
   const bool late = over(dLdf) || over(dLdg) || over(lambda_out);
   auto finish = [&]() {
-    launch_adjoint_transposes(fin.g, fin.u, lo.gdense, G, dLdf, dLdg, fin.h[0], fin.h[1], fin.h[2], h->stream);
-    if (lambda_out) launch_copy(fin.g, fin.u, lo.gdense, lambda_out, h->stream);
+    launch_adjoint_transposes(fin.g, fin.u, lo.gdense, G, dLdf, dLdg, fin.h[0], fin.h[1], fin.h[2],
+                              mark_slot(h, lo.L), h->stream);
+    if (lambda_out) launch_copy(fin.g, fin.u, lo.gdense, lambda_out, nullptr, h->stream);
   };
   const int status = run_cascade(h, 1, G, nullptr, st, &li, [&]() {
     if (!late) finish();
@@ -2484,7 +2488,7 @@ int excmg_op_exp_true(const int32_t n[3], const double *uh, const double *u2h, d
   const hipStream_t s = (hipStream_t)hip_stream;
   const Grid gh = dense_grid(n[0], n[1], n[2]);
   const Grid g2 = dense_grid(n[0] / 2, n[1] / 2, n[2] / 2);
-  launch_exp_true(gh, uh, g2, u2h, gh, ut, nullptr, s);
+  launch_exp_true(gh, uh, g2, u2h, gh, ut, nullptr, nullptr, s);
   int e = last_error();
   if (e) return e;
   HIPCHECK(hipStreamSynchronize(s));

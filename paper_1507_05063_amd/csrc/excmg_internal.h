@@ -260,6 +260,7 @@ struct Direct {
   Stencil st;
   CgState *cs;
   Outcome *out;
+  long long *mark;  // (nullable) the time of the first kernel's start, wall_clock64()
   double *A, *B, *parts;
 };
 void launch_direct(const Direct &a, hipStream_t st);
@@ -286,9 +287,10 @@ struct Resident {
 // before launch_resident: the slots it meets by, and no give-up recorded
 struct ResidentInit {
   double *slots;
-  int n;  // 0: nothing to do
+  int n;  // 0: no resident CG
   CgState *cs;
   Outcome *out;
+  long long *mark;  // (nullable) the time, wall_clock64()
 };
 ResidentInit resident_init(const Resident &a);
 void launch_resident_init(const ResidentInit &i, hipStream_t st);
@@ -297,7 +299,9 @@ void launch_resident(const Resident &a, hipStream_t st);
 void launch_outcome(const CgState *cs, Outcome *out, hipStream_t st);
 __device__ __forceinline__ void resident_init_block(const ResidentInit &i) {
   for (int q = threadIdx.x; q < i.n; q += blockDim.x) i.slots[q] = __longlong_as_double((long long)kMissingSlot);
-  if (threadIdx.x == 0 && i.n > 0) {
+  if (threadIdx.x != 0) return;
+  if (i.mark) *i.mark = (long long)wall_clock64();
+  if (i.n > 0) {
     i.cs->abort = 0;
     if (i.out) i.out->abort = 0;
   }
@@ -377,15 +381,16 @@ void launch_set_boundary(const Grid &gg, const double *g, int stride, const Grid
 // Initial guess of a grid from the two coarser solutions: kGuessQuartic = EXP_finite (the paper's), kGuessQuadratic =
 // the same extrapolation with tri-quadratic interpolation, kGuessLinear = trilinear interpolation of u2 alone.
 enum GuessKind { kGuessQuartic = 0, kGuessQuadratic = 1, kGuessLinear = 2 };
-// init (n 0: none): what the resident CG that follows on the grid needs
+// init: the time of the grid's start, and what the resident CG that follows on the grid needs
 void launch_initial_guess(int kind, const Grid &g2, const double *u2, const Grid &g4, const double *u4,
                           const Grid &gg, const double *g, int stride, const Grid &gw, double *w,
                           const ResidentInit &init, hipStream_t st);
 // ut (grid gt) = EXP_true(uh (grid gh), u2 (grid g2))
 void launch_exp_true(const Grid &gh, const double *uh, const Grid &g2, const double *u2, const Grid &gt, double *ut,
-                     double *ucopy, hipStream_t st);
-// copy between layouts (same n)
-void launch_copy(const Grid &gs, const double *src, const Grid &gd, double *dst, hipStream_t st);
+                     double *ucopy, long long *mark, hipStream_t st);
+// copy between layouts (same n).  Here and in the other launchers of what follows a cascade, mark (nullable): where the
+// time of the launch's start goes, wall_clock64()
+void launch_copy(const Grid &gs, const double *src, const Grid &gd, double *dst, long long *mark, hipStream_t st);
 // count of non-finite values in a dense array -> *flag (device int, must be zeroed by the caller)
 void launch_check_finite(const double *a, long long n, int *flag, hipStream_t st);
 
@@ -500,6 +505,6 @@ void launch_gradient(const Grid &gu, const double *u, const Grid &gd, double *ux
 
 // adjoint transposes: dLdf = -R^T lam (all nodes); dLdg = A_IB^T lam + G (boundary), 0 inside
 void launch_adjoint_transposes(const Grid &gl, const double *lam, const Grid &gd, const double *G, double *dLdf,
-                               double *dLdg, double hx, double hy, double hz, hipStream_t st);
+                               double *dLdg, double hx, double hy, double hz, long long *mark, hipStream_t st);
 
 }  // namespace excmg

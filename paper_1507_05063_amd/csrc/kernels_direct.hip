@@ -66,6 +66,7 @@ __device__ __forceinline__ void direct_small_body(const Direct &a) {
   __shared__ double sh[2][kDirectSmall / 64];
   const Grid g = a.g;
   const int nt = blockDim.x, m = threadIdx.x;
+  if (a.mark && m == 0) *a.mark = (long long)wall_clock64();
   const int Lx = g.nx - 1, Ly = g.ny - 1, Lz = g.nz - 1, n = Lx * Ly * Lz;
   double *P = lds, *Sx = P + n, *Sy = Sx + Lx * Lx, *Sz = Sy + Ly * Ly, *half = Sz + Lz * Lz;
   const bool own = m < n;
@@ -180,6 +181,7 @@ __device__ __forceinline__ void direct_forward_body(const Direct &a, int bid) {
   const Grid g = a.g;
   const int k = bid, Lx = g.nx - 1, Ly = g.ny - 1, np = Lx * Ly;
   const bool end = k == 0 || k == g.nz;
+  if (a.mark && k == 0 && threadIdx.x == 0) *a.mark = (long long)wall_clock64();
   for (int e = threadIdx.x; e < (g.nx + 1) * (g.ny + 1); e += DP) {
     const int x = e % (g.nx + 1), y = e / (g.nx + 1);
     if (end || x == 0 || y == 0 || x == g.nx || y == g.ny) a.u[g.at(x, y, k)] = dirichlet(a, x, y, k);
@@ -294,6 +296,7 @@ __device__ __forceinline__ Direct direct_of(const BatchList &L, int e) {
   a.st = E.st;
   a.cs = as_global(E.cs);
   a.out = nullptr;
+  a.mark = nullptr;
   a.A = as_global(E.r);
   a.B = as_global(E.p0);
   a.parts = as_global(E.parts);

@@ -456,7 +456,7 @@ __global__ __launch_bounds__(BX * BY * ZS) void b_resident_cg_kernel(BatchList L
 
 __global__ void b_resident_init_kernel(BatchList L) {
   const BatchEntry &E = entry_at(L, blockIdx.x);
-  resident_init_block({E.p1, slots_of(L.pre[blockIdx.x + 1] - L.pre[blockIdx.x]), E.cs, nullptr});
+  resident_init_block({E.p1, slots_of(L.pre[blockIdx.x + 1] - L.pre[blockIdx.x]), E.cs, nullptr, nullptr});
 }
 
 __global__ void b_mirror_kernel(BatchList L, BatchStatus *stat) {
@@ -508,7 +508,7 @@ ResidentPlan resident_plan(const Grid &g, int blocks) {
 }
 
 ResidentInit resident_init(const Resident &a) {
-  return {a.scratch, slots_of(a.plan.gx * a.plan.gy * a.plan.gz), a.cs, a.out};
+  return {a.scratch, slots_of(a.plan.gx * a.plan.gy * a.plan.gz), a.cs, a.out, nullptr};
 }
 
 void launch_resident_init(const ResidentInit &i, hipStream_t st) { resident_init_kernel<<<1, 256, 0, st>>>(i); }

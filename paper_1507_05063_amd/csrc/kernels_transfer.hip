@@ -17,6 +17,11 @@ __device__ __forceinline__ bool on_boundary(int i, int j, int k, int nx, int ny,
   return i == 0 || j == 0 || k == 0 || i == nx || j == ny || k == nz;
 }
 
+// the time of the launch's start
+__device__ __forceinline__ void set_mark(long long *mark) {
+  if (mark && threadIdx.x == 0 && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0) *mark = (long long)wall_clock64();
+}
+
 // ------------------------------------------------------------------------------------------------------------ rhs
 // b = -R f + A_IB g on the interior of gb, 0 on its boundary.  One thread per column of kRz planes, f of three planes
 // in registers.  A's couplings to the Dirichlet values, which only the outermost interior layer has, are in b already
@@ -91,7 +96,8 @@ __device__ __forceinline__ void copy_block(const Grid &gs, const double *__restr
 }
 
 __global__ __launch_bounds__(256) void copy_kernel(Grid gs, const double *__restrict__ src, Grid gd,
-                                                   double *__restrict__ dst) {
+                                                   double *__restrict__ dst, long long *mark) {
+  set_mark(mark);
   copy_block(gs, src, gd, dst, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
@@ -352,7 +358,9 @@ constexpr int DTX = TTX / 2 + 1, DTY = TTY / 2 + 1, DTZ = TTZ / 2 + 1;
 // made from the same read of u_h).
 __global__ __launch_bounds__(TTX *TTY) void exp_true_kernel(Grid gh, const double *__restrict__ uh, Grid g2,
                                                            const double *__restrict__ u2, Grid gt,
-                                                           double *__restrict__ ut, double *__restrict__ ucopy) {
+                                                           double *__restrict__ ut, double *__restrict__ ucopy,
+                                                           long long *mark) {
+  set_mark(mark);
   __shared__ double D[DTZ][DTY][DTX];
   // blockIdx.x runs along y: consecutive workgroups (which the hardware deals out to the XCDs in turn) take
   // different rows, so all the blocks of one row segment run on one XCD and no cache line is written from two
@@ -434,7 +442,8 @@ __global__ __launch_bounds__(256) void adjoint_kernel(Grid gl, const double *__r
 // dLdg on the boundary nodes; layers as in zero_boundary_kernel, every node in the first layer that holds it
 __global__ __launch_bounds__(256) void adjoint_boundary_kernel(Grid gl, const double *__restrict__ lam, Grid gd,
                                                                const double *G, double *dLdg, double a, double bb,
-                                                               double c) {
+                                                               double c, long long *mark) {
+  set_mark(mark);
   const int layer = blockIdx.y;
   const int np = layer < 2 ? gl.ny : gl.nx, nq = layer < 4 ? gl.nz : gl.ny;
   const long long e = (long long)blockIdx.x * 256 + threadIdx.x;
@@ -531,7 +540,7 @@ void launch_initial_guess(int kind, const Grid &g2, const double *u2, const Grid
                           const Grid &gg, const double *g, int stride, const Grid &gw, double *w,
                           const ResidentInit &init, hipStream_t st) {
   if (kind == kGuessLinear) {
-    if (init.n > 0) launch_resident_init(init, st);
+    if (init.n > 0 || init.mark) launch_resident_init(init, st);
     prolong_linear_kernel<<<node_grid(gw, 256), 256, 0, st>>>(g2, u2, gg, g, stride, gw, w);
     return;
   }
@@ -542,13 +551,13 @@ void launch_initial_guess(int kind, const Grid &g2, const double *u2, const Grid
 }
 
 void launch_exp_true(const Grid &gh, const double *uh, const Grid &g2, const double *u2, const Grid &gt, double *ut,
-                     double *ucopy, hipStream_t st) {
+                     double *ucopy, long long *mark, hipStream_t st) {
   dim3 grid((gh.ny + TTY - 1) / TTY, (gh.nx + TTX - 1) / TTX, (gh.nz + TTZ - 1) / TTZ);
-  exp_true_kernel<<<grid, TTX * TTY, 0, st>>>(gh, uh, g2, u2, gt, ut, ucopy);
+  exp_true_kernel<<<grid, TTX * TTY, 0, st>>>(gh, uh, g2, u2, gt, ut, ucopy, mark);
 }
 
-void launch_copy(const Grid &gs, const double *src, const Grid &gd, double *dst, hipStream_t st) {
-  copy_kernel<<<node_grid(gs, 256), 256, 0, st>>>(gs, src, gd, dst);
+void launch_copy(const Grid &gs, const double *src, const Grid &gd, double *dst, long long *mark, hipStream_t st) {
+  copy_kernel<<<node_grid(gs, 256), 256, 0, st>>>(gs, src, gd, dst, mark);
 }
 
 void launch_check_finite(const double *a, long long n, int *flag, hipStream_t st) {
@@ -559,10 +568,10 @@ void launch_check_finite(const double *a, long long n, int *flag, hipStream_t st
 }
 
 void launch_adjoint_transposes(const Grid &gl, const double *lam, const Grid &gd, const double *G, double *dLdf,
-                               double *dLdg, double hx, double hy, double hz, hipStream_t st) {
+                               double *dLdg, double hx, double hy, double hz, long long *mark, hipStream_t st) {
   // (the boundary first: it reads G, which dLdf or dLdg may lie over)
   adjoint_boundary_kernel<<<dim3(face_blocks(gl), 6), 256, 0, st>>>(gl, lam, gd, G, dLdg, 1.0 / (hx * hx),
-                                                                       1.0 / (hy * hy), 1.0 / (hz * hz));
+                                                                       1.0 / (hy * hy), 1.0 / (hz * hz), mark);
   adjoint_kernel<<<dim3(gl.nx / 64 + 1, gl.ny / 4 + 1, gl.nz / kRz + 1), 256, 0, st>>>(gl, lam, gd, dLdf, dLdg);
 }
 
