@@ -25,13 +25,19 @@ sys.path.insert(0, ROOT)
 
 METRIC = "stencil-CG Gunknown-iters/s (%HBM peak); EXCMG solve time 512³ FP64 vs mixed"
 HBM_PEAK_GBS = 8000.0
-# algorithmic bytes per interior unknown of one launch (FP64; halve for FP32)
-# a grid's first CG iteration (p = r): pass A reads r only, pass B reads r once for both of its operands
-BYTES_PER_UNKNOWN = {"cg_a": 24, "cg_b": 40, "cg_a0": 8, "cg_b0": 32, "cg_a32": 12, "cg_b32": 20}
+# algorithmic bytes per interior unknown of one launch of the two-step sweeps (FP64; halve for FP32), which take a pair
+# of CG iterations: pass G (class cg_a) reads r and p, pass U (cg_b) reads r, p and u and writes all three; in a grid's
+# first pair p = r
+BYTES_PER_UNKNOWN = {"cg_a": 16, "cg_b": 48, "cg_a0": 8, "cg_b0": 40, "cg_a32": 8, "cg_b32": 24}
 # algorithmic bytes of the other finest-grid steps: per interior unknown (residual: reads u, f; writes r) or per node
 # (EXP_finite: writes w, reads u_2h and u_4h; EXP_true: reads u_h and u_2h, writes u~ and the caller's copy of u_h;
 # gradient: per axis reads u and writes one component)
 BYTES_PER_NODE = {"exp_finite": 8 * (1 + 1 / 8 + 1 / 64), "exp_true": 8 * (2 + 1 + 1 / 8), "gradient": 48}
+
+
+def later_pairs(iters):
+    """Launches of each two-step sweep after a grid's first pair."""
+    return max(0, -(-iters // 2) - 1)
 
 
 def unknown_iters(st):
@@ -45,8 +51,7 @@ def trace_summary(db, top=30):
     """Per-kernel summary of a rocprofv3 database (kernel trace and/or counters), grouped by kernel and grid size.
     A CG launch made after its grid converged returns at once; launches shorter than half the longest of their group
     (early exits, or a coarser grid's launches of the same shape) are left out of the 'working' average, and for the
-    CG passes those shorter than 0.9 of it (also a grid's first iteration, whose passes move 8 and 32 B per unknown
-    instead of 24 and 40)."""
+    CG passes those shorter than 0.9 of it (also a grid's first pair, whose passes move fewer bytes)."""
     import re
     import sqlite3
 
@@ -117,7 +122,8 @@ def solve_trace_summary(db):
     groups = {}
     for i in range(last + 1, len(rows) - 1):
         nm, (_, gx, wx, t0, t1) = names[i], rows[i]
-        if not nm.startswith(("cg1_", "cg_selfred_", "cg_pass_", "small_cg", "finalize_")):
+        if not nm.startswith(("cg1_", "cg_selfred_", "cg_pass_", "two_", "resident_", "direct_", "small_cg",
+                              "finalize_")):
             continue
         groups.setdefault((nm, gx, wx), []).append((t1 - t0, rows[i + 1][3] - t1))
     print(f"solve launches after the autotuner: {len(rows) - last - 1} dispatches")
@@ -380,10 +386,11 @@ def bench_slab(ex, synth, torch, args):
             _, _, st = s.solve(f, g, u=u)
             for k in tot:
                 tot[k] += st["kernel_ms_finest"][k]
-                calls[k] += st["kernel_calls_finest"][k]
+                calls[k] += later_pairs(st["iters"][-1])
         unknowns = (n[0] - 1) * (n[1] - 1) * (n[2] - 1)
         out = {"cells": list(n), "finest_iters": st["iters"][-1]}
-        for k, b in (("cg_a", 24), ("cg_b", 40)):
+        for k in tot:
+            b = BYTES_PER_UNKNOWN[k]
             if calls[k]:
                 ms = tot[k] / calls[k]
                 out[k + "_ms"] = round(ms, 4)
@@ -469,7 +476,8 @@ def bench_tolerance(ex, synth, torch, args, f, g, u_exact):
 
 PROBE_BYTES = 2 << 30  # buffer of the streaming probe: its copy kernel reads PROBE_BYTES/2 and writes PROBE_BYTES/2
 COUNTERS_FILE = os.path.join(ROOT, "profiles", "excmg_512_fp64_hbm_counters.txt")
-KERNEL_SOURCES = ["paper_1507_05063_amd/csrc/kernels_cg.hip", "paper_1507_05063_amd/csrc/excmg_internal.h"]
+KERNEL_SOURCES = [f"paper_1507_05063_amd/csrc/{f}"
+                  for f in ("kernels_two.hip", "kernels_cg.hip", "cg_device.h", "excmg_internal.h")]
 
 
 def kernel_source_hash():
@@ -487,7 +495,7 @@ def counter_summary(fetch_db, write_db, min_bytes=512 << 20):
     probe's copy kernel (PROBE_BYTES/2 read, PROBE_BYTES/2 written) reads its known size.  One JSON line per
     (kernel, grid size) that moves at least min_bytes, for the working dispatches (at least 0.9 of the group's
     largest value: this drops launches that return at once, a coarser grid's launches of the same shape, and a grid's
-    first CG iteration, whose passes move 8 and 32 B per unknown instead of 24 and 40)."""
+    first pair of CG iterations, whose passes move fewer bytes)."""
     import re
     import sqlite3
 
@@ -642,7 +650,7 @@ def main():
 
     # roofline of the dominant finest-grid CG sweep, from the HIP events of the timed steps
     tot = {k: sum(st["kernel_ms_finest"][k] for st in stats) for k in ("cg_a", "cg_b")}
-    calls = {k: sum(st["kernel_calls_finest"][k] for st in stats) for k in ("cg_a", "cg_b")}
+    calls = {k: sum(later_pairs(st["iters"][-1]) for st in stats) for k in ("cg_a", "cg_b")}
     dom = max(tot, key=lambda k: tot[k])
     nI = (N - 1) ** 3
     avg_ms = tot[dom] / max(calls[dom], 1)
@@ -651,11 +659,12 @@ def main():
     zc_dom = zc64[-1][0 if dom == "cg_a" else 1]
     dvar = dp64[-1][0 if dom == "cg_a" else 1]  # prefetch depth + 10 (non-temporal policy) + 100 * tile height
     ty = dvar // 100
-    grid_threads = -(-(N - 1) // 64) * -(-(N - 1) // ty) * -(-(N - 1) // zc_dom) * 64 * ty
-    kname = (f"cg_pass_{dom[-1]}_kernel<double, {dvar % 10}, {'true' if (dvar // 10) % 10 else 'false'}, "
-             f"{dvar // 100}>")
+    rows, threads = {4: (4, 256), 8: (12, 512), 16: (13, 1024)}[ty]  # of a two-step tile
+    grid_threads = -(-(N - 1) // 64) * -(-(N - 1) // rows) * -(-(N - 1) // zc_dom) * threads
+    kname = (f"two_g_kernel<double, {2 if ty == 16 else 1}, {ty}>" if dom == "cg_a" else
+             f"two_u_kernel<double, 2, {'true' if (dvar // 10) % 10 else 'false'}, {ty}>")
     traffic = measured_traffic(kname, grid_threads)
-    # stencil-CG sweeps of the finest grid alone: unknown-iterations per second of pass A + pass B kernel time
+    # stencil-CG sweeps of the finest grid alone: unknown-iterations per second of the sweeps' kernel time
     fin_iters = stats[-1]["iters"][-1]
     cg_ms_fin = sum(sum(st["kernel_ms_finest"][k] for k in ("cg_a0", "cg_b0", "cg_a", "cg_b", "finalize"))
                     for st in stats) / args.steps
@@ -669,7 +678,7 @@ def main():
                  ("cg_a", BYTES_PER_UNKNOWN["cg_a"] * nI), ("cg_b", BYTES_PER_UNKNOWN["cg_b"] * nI),
                  ("resid", 24 * nI), ("exp_finite", BYTES_PER_NODE["exp_finite"] * nodes),
                  ("exp_true", BYTES_PER_NODE["exp_true"] * nodes)]:
-        c = sum(st["kernel_calls_finest"][k] for st in stats)
+        c = calls[k] if k in calls else sum(st["kernel_calls_finest"][k] for st in stats)
         if c:
             ms_k = sum(st["kernel_ms_finest"][k] for st in stats) / c
             kernels[k] = {"ms": round(ms_k, 4), "calls_per_step": c / args.steps, "GB": round(b / 1e9, 3),
