@@ -170,7 +170,8 @@ int excmg_setup(const excmg_problem *p, void *workspace, size_t bytes, void *hip
 
 /* Algorithm 1.  f: node array (every node is read); g: node array (only boundary nodes are read).
  * u (out): node array, the finest-grid solution with its boundary equal to g (its contents change during the call:
- * the relaxation keeps a work vector there; after an error other than EXCMG_ERR_NOCONV they are undefined).
+ * the relaxation keeps a work vector there; after an error other than EXCMG_ERR_NOCONV they are undefined, and so are
+ * u_ext's).
  * u_ext (out, nullable): EXP_true(u_h, u_2h), the sixth-order extrapolated solution on the finest grid
  * (Algorithm 1, optional step; Sections 4.2.1 and 4.3); needs at least two grids.
  * stats (host, nullable). */

@@ -816,11 +816,11 @@ int small_cg(excmg_handle *h, int l, const RhsSrc &rs, bool exact, bool finest, 
 }
 
 // The resident CG's bricks of every grid that runs it: the FP64 relaxations, unless EXCMG_TWO_PASS_CG, as far as a
-// grid fits the device's CUs.  (Not on the per-thread default stream, which another thread could not wait for.)
+// grid fits the device's CUs.
 int plan_resident(excmg_handle *h) {
   int cus = 0;
   HIPCHECK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device));
-  if ((h->p.flags & EXCMG_TWO_PASS_CG) || h->stream == hipStreamPerThread || h->device >= kMaxDevices) return EXCMG_OK;
+  if ((h->p.flags & EXCMG_TWO_PASS_CG) || h->device >= kMaxDevices) return EXCMG_OK;
   for (int l = 2; l < h->lo.L; ++l) {
     Level &lv = h->lo.lev[l];
     if (h->p.precision == EXCMG_FP64 || lv.g.interior() < kIrMinUnknowns)
@@ -837,6 +837,21 @@ struct ResidentTurn {
   const excmg_handle *last = nullptr;
 };
 ResidentTurn g_resident[kMaxDevices];
+// launch() of h's resident CG in its turn.  The per-thread default stream is another stream in another thread, which
+// could not wait for it: there the turn ends when the launch has.
+template <typename F>
+int in_turn(excmg_handle *h, F &&launch) {
+  ResidentTurn &turn = g_resident[h->device];
+  std::lock_guard<std::mutex> lock(turn.mu);
+  if (turn.last && turn.last != h) HIPCHECK(hipStreamSynchronize(turn.last->stream));
+  turn.last = h;
+  int e = launch();
+  if (h->stream == hipStreamPerThread) {
+    if (hipStreamSynchronize(h->stream) != hipSuccess && !e) e = EXCMG_ERR_HIP;
+    turn.last = nullptr;
+  }
+  return e;
+}
 struct ResidentCall {
   excmg_handle *h;
   ~ResidentCall() {
@@ -885,11 +900,11 @@ int resident_cg(excmg_handle *h, int l, const RhsSrc &rs, int *iters, double *re
   const Resident a = resident_args(h, l, rs, st);
   {
     Tick t(h, EXCMG_K_CG_A, l, kResidentTick);
-    ResidentTurn &turn = g_resident[h->device];
-    std::lock_guard<std::mutex> lock(turn.mu);
-    if (turn.last && turn.last != h) HIPCHECK(hipStreamSynchronize(turn.last->stream));
-    turn.last = h;
-    launch_resident(a, h->stream);
+    const int e = in_turn(h, [&]() {
+      launch_resident(a, h->stream);
+      return last_error();
+    });
+    if (e) return e;
   }
   int e = last_error();
   *iters = 0;
@@ -1570,7 +1585,7 @@ int batched_solve(excmg_handle *const *hs, int count, const double *const *f, co
           }
           if (l <= 1) add(kListSetB, l, b, nblk(l, b, kLSetB), 0, 0);
           else add(kListExp, l, b, nblk(l, b, kLExp), 0, 0);
-          if (lv.res.threads && !apart[b] && s != hipStreamPerThread) {
+          if (lv.res.threads && !apart[b]) {
             res.push_back(b);
             res_grid.push_back(lv.g);
             const int before = hstat[b].m[0].iter;  // on the grid below; none where that was solved directly
@@ -1651,18 +1666,16 @@ int batched_solve(excmg_handle *const *hs, int count, const double *const *f, co
     if (!packs.empty()) {
       std::vector<long long> key = {(long long)(uintptr_t)ws, -1, at};
       for (const auto &p : packs) key.insert(key.end(), {p.brick, p.blocks, (long long)p.problems.size()});
-      ResidentTurn &turn = g_resident[hs[0]->device];
-      std::lock_guard<std::mutex> lock(turn.mu);
-      if (turn.last && turn.last != hs[0]) HIPCHECK(hipStreamSynchronize(turn.last->stream));
-      turn.last = hs[0];
       const int from = at;
-      e = batch_replay(hs[0], key, [&](hipStream_t st) {
-        at = from;
-        const BatchList all = part(res.size(), 0);
-        launch_b_resident_init(all, st);
-        at = from;
-        for (const auto &p : packs) launch_b_resident(p.brick, part(p.problems.size(), p.blocks), st);
-        launch_b_mirror(all, stat, st);
+      e = in_turn(hs[0], [&]() {
+        return batch_replay(hs[0], key, [&](hipStream_t st) {
+          at = from;
+          const BatchList all = part(res.size(), 0);
+          launch_b_resident_init(all, st);
+          at = from;
+          for (const auto &p : packs) launch_b_resident(p.brick, part(p.problems.size(), p.blocks), st);
+          launch_b_mirror(all, stat, st);
+        });
       });
       if (e) return e;
     }

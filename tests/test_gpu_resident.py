@@ -112,3 +112,31 @@ def test_threads_on_their_own_streams(ex):
     for t in ts:
         t.join()
     assert not bad
+
+
+def test_per_thread_default_stream(ex):
+    """The per-thread default stream, which is another stream in every thread, beside a stream of its own."""
+    import torch
+
+    n, p = (64, 48, 32), synth.smooth(2)
+    f, g, _ = synth.sample(p, n)
+    f, g = dev(f), dev(g)
+    torch.cuda.synchronize()
+    want = ex.Solver(n, p.box, 1e-10).solve(f, g)[0]
+    bad = []
+
+    def work(stream):
+        s = ex.Solver(n, p.box, 1e-10, stream=stream)
+        u = torch.empty_like(f)
+        for _ in range(20):
+            s.solve(f, g, u=u)
+            if not torch.equal(u, want):
+                bad.append(stream)
+
+    per_thread = torch.cuda.ExternalStream(2)  # hipStreamPerThread
+    ts = [threading.Thread(target=work, args=(st,)) for st in (per_thread, per_thread, torch.cuda.Stream())]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    assert not bad
