@@ -3,15 +3,15 @@
 // Per grid of the cascade (coarsest first):
 //   level data   b_l = -R f_l + A_IB g_l, with f_l, g_l the finest arrays at stride 2^(L-1-l)  (Section 2, eq. compact),
 //                formed on the fly by every kernel that needs it (never stored)
-//   grids 0, 1   DSOLVE: single-workgroup CG to rounding                                     (Algorithm 1, coarsest grids)
+//   grids 0, 1   DSOLVE: by sine transforms (kernels_direct.hip), above 64 cells an axis by CG (Algorithm 1, first lines)
 //   grids >= 2   w = EXP_finite(u_{l-1}, u_{l-2}), then CG from w until ||r|| <= tol ||b||   (Algorithm 1, the loop):
 //                one launch of the resident CG on FP64 grids that fit the chip (kernels_resident.hip), pairs of
 //                iterations in two sweeps on the largest grids (kernels_two.hip), else one single-workgroup launch on
 //                grids of at most 8000 unknowns, or two stencil sweeps and their reductions per iteration
 //   finest       u_ext = EXP_true(u_h, u_2h) on request; u copied to the caller's dense array
 // The library allocates no device memory: every array lives in the caller's workspace.  The host reads the CG state
-// back (one small copy and a stream sync) after every batch of iterations; iterations launched after convergence
-// return at once (every CG kernel checks the device-side done flag first).
+// back (one small copy and a stream sync) after every batch of iterations, and the outcomes of the grids solved in one
+// launch at the end; iterations launched after convergence return at once (every CG kernel checks the device-side done flag first).
 #include <math.h>
 #include <stdio.h>
 #include <string.h>
@@ -151,8 +151,8 @@ constexpr size_t kPinOutcomes = 4096, kPinMarks = 7168, kPinBytes = 8192;
 static_assert(sizeof(CgState) <= kPinOutcomes && kPinOutcomes + EXCMG_MAX_LEVELS * sizeof(Outcome) <= kPinMarks &&
               kPinMarks + (EXCMG_MAX_LEVELS + 1) * sizeof(long long) <= kPinBytes, "pinned");
 
-// The two-step sweeps relax the grids above this size.  On smaller grids a step of the march, about 1.4 us whatever the grid, outweighs the bytes saved: at 127^3 unknowns a
-// pair takes 64 us, four self-finalizing sweeps 62 us.
+// The two-step sweeps relax the grids above this size.  On smaller grids a step of the march, about 1.4 us whatever the
+// grid, outweighs the bytes saved: at 127^3 unknowns a pair takes 64 us, four self-finalizing sweeps 62 us.
 constexpr long long kTwoMinUnknowns = 1LL << 21;
 bool two_grid(const Level &lv, const excmg_problem &p) {
   return !(p.flags & EXCMG_TWO_PASS_CG) && lv.g.interior() > kTwoMinUnknowns;
@@ -447,9 +447,9 @@ int next_batch(double rho, double rho0, int done, double stop2, int first, int c
 // halving their bytes saves nothing, while the extra outer steps of the refinement would cost launches.
 constexpr long long kIrMinUnknowns = 1LL << 20;
 
-// Grids with at most kSmallCg interior unknowns (16^3 cells and below) relax in one single-workgroup launch, and so
-// are the direct solves that fit the sine transforms; every other grid runs the multi-workgroup CG sweeps (a direct
-// solve then iterates to the relative residual kDsolveTol).
+// Whether grid l runs the multi-workgroup CG sweeps where the resident CG does not take it: grids of more than kSmallCg
+// interior unknowns (the others have one-workgroup launches), but for direct solves that fit the sine transforms (one
+// that does not iterates to the relative residual kDsolveTol).
 bool swept(const Layout &lo, int l) {
   const Level &lv = lo.lev[l];
   if (lv.g.interior() <= kSmallCg) return false;
@@ -466,9 +466,9 @@ bool self_finalizing(const Level &lv, bool fp32) {
 long long vec_stride(const Level &lv) { return (lv.g.elems + 31) / 32 * 32; }
 
 // The two-step sweeps (kernels_two.hip) relax the large grids (two_grid), unless EXCMG_TWO_PASS_CG asks for two
-// sweeps an iteration.  They need a fourth vector beside r, p0 and p1: below the finest it follows r in r's buffer (which holds
-// the finest grid); the FP32 refinement, which leaves the FP64 p0 idle, has it there; the finest FP64 grid takes an
-// output array of the call (bind_output).  Byte offsets in a plane are 32 bits.
+// sweeps an iteration.  They need a fourth vector beside r, p0 and p1: below the finest it follows r in r's buffer
+// (which holds the finest grid); the FP32 refinement, which leaves the FP64 p0 idle, has it there; the finest FP64 grid
+// takes an output array of the call (bind_output).  Byte offsets in a plane are 32 bits.
 bool plane_fits(const Grid &g, size_t size) { return (unsigned long long)g.sz * size < (1ull << 32); }
 bool two_below(const Layout &lo, const Level &lv) { return vec_stride(lv) + lv.g.elems <= lo.gfin.elems; }
 bool use_two(const excmg_handle *h, int l, int fp32) {
@@ -1126,7 +1126,7 @@ int cascade(excmg_handle *h, int mode, const double *f, const double *g, excmg_s
         if ((init.mark = mark_slot(h, l))) launch_resident_init(init, s);
         launch_set_boundary(lo.gdense, mode == 0 ? g : nullptr, lv.stride, lv.g, lv.u, 1, s);
       }
-      // DSOLVE: the sine-transform solve or single-workgroup CG, or on larger grids the CG sweeps from u = 0
+      // DSOLVE above the sine transforms' size: single-workgroup CG, or on larger grids the CG sweeps, from u = 0
       if (swept(lo, l)) {
         e = cg64(h, l, rs, l == L - 1, &dit, &rr, st);
         if (st) st->dsolve_iters[l] = dit;
@@ -1402,8 +1402,8 @@ struct ResidentPack {
 // together: 23 grids of 32^3 to 192 x 128 x 64 cells, 37 to 239 iterations each, take 9 ms so and 11 ms by size.
 // 24 problems of 32 to 64 cells an axis relax their finest grids in three launches of 0.45 ms (2.2 ms the whole batch),
 // where the flattened sweeps, four launches an iteration, took 6 ms (9.7 ms the whole batch).
-std::vector<ResidentPack> pack_residents(const std::vector<int> &ps, const std::vector<Grid> &gs, const std::vector<int> &expect,
-                                         int cus) {
+std::vector<ResidentPack> pack_residents(const std::vector<int> &ps, const std::vector<Grid> &gs,
+                                         const std::vector<int> &expect, int cus) {
   std::vector<ResidentPack> best;
   double least = 1e300;
   const int n = (int)ps.size();
