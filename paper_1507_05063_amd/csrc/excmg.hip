@@ -1330,8 +1330,15 @@ enum BatchPhase { kPhStart, kPhSmall, kPhIter64, kPhIter32, kPhOuter, kPhCopy, k
 
 // The launches of a round's CG: launch_all(stream), in a graph replayed from the first handle's cache when the round has
 // the launch shape (key) of an earlier one - the lists themselves are read from the batch workspace when the kernels
-// run - else captured and instantiated; directly launched under EXCMG_NO_GRAPHS.
+// run - else captured and instantiated; directly launched under EXCMG_NO_GRAPHS.  The key holds everything that the
+// captured launches do: their shapes, and the places of the status words and of the lists (key_list), which follow from
+// the workspace's address and the batch's count.
 constexpr size_t kBatchGraphCache = 1024;
+
+void key_list(std::vector<long long> &key, const BatchList &L) {
+  key.insert(key.end(), {(long long)(uintptr_t)L.ent, (long long)(uintptr_t)L.pre, (long long)(uintptr_t)L.aux, L.n,
+                         L.total});
+}
 
 template <typename F>
 int batch_replay(excmg_handle *h0, const std::vector<long long> &key, F &&launch_all) {
@@ -1371,8 +1378,8 @@ int batch_replay(excmg_handle *h0, const std::vector<long long> &key, F &&launch
 }
 
 // it rounds of one iteration of the FP64 entries (the first nb64 rounds) and of the FP32 inner solves (the first nb32)
-int batch_iterations(excmg_handle *h0, const char *ws, int it, int nb64, int nb32, const BatchList (&l64)[2],
-                     const BatchList (&l32)[2], BatchStatus *stat) {
+int batch_iterations(excmg_handle *h0, int it, int nb64, int nb32, const BatchList (&l64)[2], const BatchList (&l32)[2],
+                     BatchStatus *stat) {
   auto launch_all = [&](hipStream_t st) {
     for (int q = 0; q < it; ++q) {
       if (q < nb64) launch_b_iteration(0, h0->bty[0], h0->bdepth[0], l64[0], l64[1], stat, st);
@@ -1383,9 +1390,10 @@ int batch_iterations(excmg_handle *h0, const char *ws, int it, int nb64, int nb3
     launch_all(h0->stream);
     return last_error();
   }
-  return batch_replay(h0, {(long long)(uintptr_t)ws, h0->bty[0], h0->bty[1], h0->bdepth[0], h0->bdepth[1], it, nb64,
-                           nb32, l64[0].n, l64[0].total, l64[1].total, l32[0].n, l32[0].total, l32[1].total},
-                      launch_all);
+  std::vector<long long> key = {(long long)(uintptr_t)stat, h0->bty[0], h0->bty[1], h0->bdepth[0], h0->bdepth[1], it,
+                                nb64, nb32};
+  for (const auto *l : {&l64[0], &l64[1], &l32[0], &l32[1]}) key_list(key, *l);
+  return batch_replay(h0, key, launch_all);
 }
 
 // The resident CG in a batch.  A launch holds as many grids, in bricks of one kind, as the CUs take workgroups.
@@ -1664,9 +1672,10 @@ int batched_solve(excmg_handle *const *hs, int count, const double *const *f, co
     launch_b_direct(part(dlarge.size(), 0), lcells, stat, s);
     launch_b_small_cg(part(small.size(), 0), lds, stat, s);
     if (!packs.empty()) {
-      std::vector<long long> key = {(long long)(uintptr_t)ws, -1, at};
+      std::vector<long long> key = {(long long)(uintptr_t)stat, -1};
       for (const auto &p : packs) key.insert(key.end(), {p.brick, p.blocks, (long long)p.problems.size()});
       const int from = at;
+      key_list(key, part(res.size(), 0));
       e = in_turn(hs[0], [&]() {
         return batch_replay(hs[0], key, [&](hipStream_t st) {
           at = from;
@@ -1684,7 +1693,7 @@ int batched_solve(excmg_handle *const *hs, int count, const double *const *f, co
     launch_b_add_correction(dl[kListCorr][0], s);
     launch_b_residual_cast(dl[kListRC][0], stat, s);
     const int it = hl[kListI64].n || hl[kListI32].n ? (nb64 > nb32 ? nb64 : nb32) : 0;
-    if ((e = batch_iterations(hs[0], ws, it, nb64, nb32, dl[kListI64], dl[kListI32], stat))) return e;
+    if ((e = batch_iterations(hs[0], it, nb64, nb32, dl[kListI64], dl[kListI32], stat))) return e;
     if ((e = last_error()) || (e = read_stat())) return e;
     // move every problem on, and size the next round's iteration batches from the residual decay seen so far
     nb64 = nb32 = 1;
