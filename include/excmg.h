@@ -303,6 +303,12 @@ int excmg_set_batch_shape(excmg_handle *h, const int32_t shape[4]);
  * handle's stream first.  Errors: EXCMG_ERR_ARG for a null handle, EXCMG_ERR_HIP if the events cannot be created. */
 int excmg_set_timing(excmg_handle *h, int32_t on);
 
+/* Host only.  How many times a workgroup of the one-launch CG (see EXCMG_TWO_PASS_CG) of this handle's later calls looks
+ * for the others at a meeting before it gives up, upon which the call runs the sweeps instead: 2^20, about a second,
+ * from setup on; 0 gives up at the first meeting.  In a batch it holds for the handle's own problem.  Errors:
+ * EXCMG_ERR_ARG for a null handle or a negative count. */
+int excmg_set_wait_limit(excmg_handle *h, int32_t looks);
+
 void excmg_destroy(excmg_handle *h);
 const char *excmg_strerror(int code);
 

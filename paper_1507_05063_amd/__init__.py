@@ -211,6 +211,11 @@ class Solver:
         sh = (ctypes.c_int32 * 4)(*[int(v) for v in shape])
         _lib.check(_lib.lib().excmg_set_batch_shape(self._h, sh), "excmg_set_batch_shape")
 
+    def set_wait_limit(self, looks: int):
+        """How many times a workgroup of the one-launch CG looks for the others before the call runs the sweeps instead
+        (2**20, about a second, from setup on; 0: at once)."""
+        _lib.check(_lib.lib().excmg_set_wait_limit(self._h, int(looks)), "excmg_set_wait_limit")
+
     def set_timing(self, on: bool):
         """Kernel timing (stats kernel_ms, kernel_calls) on or off for later calls."""
         _lib.check(_lib.lib().excmg_set_timing(self._h, 1 if on else 0), "excmg_set_timing")

@@ -118,6 +118,7 @@ def lib():
             "excmg_batch_graph_counts": ([_P, ctypes.POINTER(ctypes.c_int64), ctypes.POINTER(ctypes.c_int64)], _I),
             "excmg_destroy": ([_P], None),
             "excmg_set_timing": ([_P, ctypes.c_int32], _I),
+            "excmg_set_wait_limit": ([_P, ctypes.c_int32], _I),
             "excmg_get_sweep": ([_P, ctypes.c_int32, ctypes.c_int32, _I32P], _I),
             "excmg_set_sweep": ([_P, ctypes.c_int32, ctypes.c_int32, _I32P], _I),
             "excmg_get_batch_shape": ([_P, _I32P], _I),

@@ -279,6 +279,7 @@ struct excmg_handle {
   int two_pairs = 0;  // pairs of the last two-step solve (kernel timing)
   bool late = false;  // this call's outputs lie over its inputs: nothing is written there while it may start over
   bool apart = false; // this call relaxes no grid by the resident CG (a workgroup of it gave up waiting)
+  int looks = kResidentLooks;  // excmg_set_wait_limit
   // graphs of a batched round's CG iterations (excmg_solve_batched, on the batch's first handle), by launch shape
   struct BatchGraph {
     std::vector<long long> key;
@@ -867,8 +868,7 @@ struct ResidentCall {
   }
 };
 
-// Internal outcome: a workgroup of the resident CG gave up waiting (its grid is as it was: the call starts over with
-// the sweeps).
+// Internal outcome: a workgroup of the resident CG gave up waiting (the call starts over with the sweeps).
 constexpr int kGaveUp = -1001;
 
 // Whether the resident CG leaves grid l's outcome to the cascade's end: always, but for a history to read.
@@ -891,6 +891,7 @@ Resident resident_args(excmg_handle *h, int l, const RhsSrc &rs, const excmg_sta
   a.tol = grid_tol(h->p, l, h->lo.L);
   a.cap = grid_cap(h, l);
   a.hist_on = resident_defers(h, l, st) ? 0 : 1;
+  a.looks = h->looks;
   a.plan = lv.res;
   return a;
 }
@@ -1268,6 +1269,7 @@ void batch_entry(excmg_handle *h, int problem, int l, const double *f, const dou
   E->level = l;
   E->cap = grid_cap(h, l);
   E->max_outer = 30;
+  E->looks = h->looks;
   E->tol = grid_tol(h->p, l, h->lo.L);
   E->eta = h->p.inner_tol > 0.0 ? h->p.inner_tol : 1e-5;
   // every entry of a batched launch has the launch's tile height (bty: the batch's, for the FP64 and the FP32
@@ -2401,6 +2403,12 @@ int excmg_set_timing(excmg_handle *h, int32_t on) {
   DeviceGuard dg(h->device);
   HIPCHECK(hipStreamSynchronize(h->stream));  // no timed launch of an earlier call is still pending
   return set_timing(h, on != 0);
+}
+
+int excmg_set_wait_limit(excmg_handle *h, int32_t looks) {
+  if (!h || looks < 0) return EXCMG_ERR_ARG;
+  h->looks = looks;
+  return EXCMG_OK;
 }
 
 void excmg_destroy(excmg_handle *h) {

@@ -181,7 +181,7 @@ struct CgState {
   // inner solves) instead of the residual's partial sums.
   int iterA, iterB;
   int preset;
-  int abort;       // the resident CG: a workgroup gave up waiting for the others (nothing was written)
+  int abort;       // the resident CG: a workgroup gave up waiting for the others (others may have finished)
   double gbnd2;    // added to the squared norm of the stopping test: the sum of g^2 over the grid's boundary nodes
                    // under EXCMG_STOP_F_G, else 0 (set at setup and by boundary_g2_kernel)
   double rhoA[2];
@@ -247,7 +247,7 @@ constexpr unsigned long long kMissingSlot = 0x7ff8dead0badf00dull;
 struct Outcome {
   double rho, rho0, bnorm2;
   int iter, status;
-  int abort;  // the resident CG gave up waiting (nothing was written)
+  int abort;  // a workgroup of the resident CG gave up waiting: what the grid holds is not its solution
 };
 
 // The direct solve by sine transforms (kernels_direct.hip), with u's boundary values from gdat (null: 0) and the
@@ -282,8 +282,10 @@ struct Resident {
   double *W0, *W1;  // published layers of w, in the grid's layout
   double tol;
   int cap, hist_on;
+  int looks;  // at the slots before a workgroup gives up waiting
   ResidentPlan plan;
 };
+constexpr int kResidentLooks = 1 << 20;  // about a second
 // before launch_resident: the slots it meets by, and no give-up recorded
 struct ResidentInit {
   double *slots;
@@ -415,7 +417,7 @@ enum BatchLaunch {
 
 struct BatchMirror {  // copy of one CG state's scalars, for the host
   int done, iter, status;
-  int abort;  // the resident CG gave up waiting (the grid is as it was)
+  int abort;  // a workgroup of the resident CG gave up waiting: what the grid holds is not its solution
   double rho, bnorm2, rho0, stop2;
 };
 
@@ -433,7 +435,7 @@ struct BatchEntry {
   int level;      // grid index in the problem's cascade
   int cap;        // CG iteration cap (kBIr: per inner solve)
   int max_outer;  // kBIr: outer refinement steps allowed
-  int pad;
+  int looks;      // of the resident CG's workgroups before they give up waiting
   double tol, eta;
   Sweep swA, swB, swR, swA32, swB32;
   Grid g, g32, gd, g2, g4;  // this grid (FP64, FP32 layouts), the problem's dense node layout, grids l-1 and l-2

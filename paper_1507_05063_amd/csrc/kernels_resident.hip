@@ -18,7 +18,9 @@
 // been written holds a NaN that no sum produces; slots rotate through three sets, and a workgroup clears its own slot
 // of the set after next once all have arrived.  There are no more workgroups than CUs and the host keeps two such
 // launches from running at once, so all workgroups of a launch come to run; the wait is bounded nevertheless (another
-// process may hold CUs), and a workgroup that gives up says so in the CG state: the host then runs the sweeps.  (A
+// process may hold CUs), and a workgroup that gives up says so in the CG state: the host then takes the grid up again
+// from its initial guess with the sweeps.  (Others may have got through the same meeting and, if it was the last, have
+// written their part of the solution and the outcome: only the give-up counts then.)  (A
 // cooperative launch would keep launches apart too, but costs about 190 us on this runtime.)
 // Measured per iteration: 128^3 31 -> 11 us (operator and updates 4 us, meeting 3, publishing and the layer 4), 64^3
 // 11 -> 5.1 us, 32^3 10 -> 4.1 us, 16^3 (one workgroup before) 6.5 -> 2.7 us.
@@ -31,7 +33,6 @@ namespace excmg {
 
 namespace {
 
-constexpr int kSpins = 1 << 20;             // looks at the slots before a workgroup gives up (about a second)
 constexpr unsigned long long kMissing = kMissingSlot;
 
 __device__ __forceinline__ void put(double *p, double v) {
@@ -97,11 +98,12 @@ __host__ __device__ constexpr int set_slots(int groups) { return 2 * kGroup * gr
 // the three sets of nb workgroups
 __host__ __device__ constexpr int slots_of(int nb) { return 3 * set_slots((nb + kGroup - 1) / kGroup); }
 
-// Reads slot p of every lane that has one until none is missing (0 in the other lanes); there: whether that happened.
-__device__ __forceinline__ double await(const double *p, bool mine, bool &there) {
+// Reads slot p of every lane that has one until none is missing (0 in the other lanes), at most `looks` times; there:
+// whether that happened.
+__device__ __forceinline__ double await(const double *p, bool mine, int looks, bool &there) {
   double v = 0.0;
   there = false;
-  for (int spin = 0; !there && spin < kSpins; ++spin) {
+  for (int look = 0; !there && look < looks; ++look) {
     if (mine) v = get(p);
     there = __all((unsigned long long)__double_as_longlong(v) != kMissing);
   }
@@ -113,7 +115,8 @@ __device__ __forceinline__ double await(const double *p, bool mine, bool &there)
 // adds up its group, and read the groups' sums (256 workgroups that all read 512 slots get in one another's way: 3.6 us
 // a meeting, against 1.2 us among four).
 template <int NW>
-__device__ __forceinline__ bool meet(double &a, double &b, double *slots, int seq, int bid, int nb, Meeting<NW> &m) {
+__device__ __forceinline__ bool meet(double &a, double &b, double *slots, int seq, int bid, int nb, int looks,
+                                     Meeting<NW> &m) {
   const int groups = (nb + kGroup - 1) / kGroup;
   __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");  // what this thread has published has arrived
   a = wave_sum63(a);
@@ -135,7 +138,7 @@ __device__ __forceinline__ bool meet(double &a, double &b, double *slots, int se
     bool there = true;
     if (leader) {
       const bool mine = kGroup * group + (lane & 31) < nb;
-      x = row_sum(await(&slots[now + 2 * kGroup * group + lane], mine, there));
+      x = row_sum(await(&slots[now + 2 * kGroup * group + lane], mine, looks, there));
       x += dpp<0x142, 0xa>(x);  // lane 31: the group's a, lane 63: its b
       if (groups > 1 && there && (lane & 31) == 31) {
         if (!(x == x)) x = __longlong_as_double(0x7ff8000000000000ll);
@@ -143,7 +146,7 @@ __device__ __forceinline__ bool meet(double &a, double &b, double *slots, int se
       }
     }
     if (groups > 1) {
-      x = await(&slots[now + line + (lane & 15)], lane < 16 && (lane & 7) < groups, there);
+      x = await(&slots[now + line + (lane & 15)], lane < 16 && (lane & 7) < groups, looks, there);
       // lanes 7 and 15: the sums of eight
       x += dpp<0x111>(x);
       x += dpp<0x112>(x);
@@ -329,7 +332,7 @@ __device__ __forceinline__ void resident_cg(const Resident &a, double *u_, doubl
   publish(1, w);
   const double gbnd2 = uniform(cs->gbnd2);
   int seq = 0;
-  bool here = meet(gam, bsum, slots, seq++, bid, nb, meeting);
+  bool here = meet(gam, bsum, slots, seq++, bid, nb, a.looks, meeting);
   const double rho0 = gam, bb = bsum + gbnd2;
   const double stop2 = a.tol * a.tol * bb;
 #pragma unroll
@@ -343,7 +346,7 @@ __device__ __forceinline__ void resident_cg(const Resident &a, double *u_, doubl
   double gold = 1.0, aold = 1.0, gamma = rho0;
   int k = 0, status = 0;
   while (here) {
-    here = meet(gam, del, slots, seq++, bid, nb, meeting);
+    here = meet(gam, del, slots, seq++, bid, nb, a.looks, meeting);
     if (!here) break;
     gamma = gam;
     const double delta = del;
@@ -447,6 +450,7 @@ __global__ __launch_bounds__(BX * BY * ZS) void b_resident_cg_kernel(BatchList L
   a.tol = E.tol;
   a.cap = E.cap;
   a.hist_on = 0;
+  a.looks = E.looks;
   a.out = nullptr;
   double *const scratch = as_global(E.p1);
   const int gx = (E.g.nx - 1 + BX - 1) / BX, gy = (E.g.ny - 1 + BY - 1) / BY;
