@@ -278,7 +278,7 @@ struct excmg_handle {
   Grid gxfin = {};
   int two_pairs = 0;  // pairs of the last two-step solve (kernel timing)
   bool late = false;  // this call's outputs lie over its inputs: nothing is written there while it may start over
-  bool apart = false; // this call relaxes no grid by the resident CG (a workgroup of it gave up waiting)
+  bool apart = false; // no grid is relaxed by the resident CG any more: a workgroup of it gave up waiting
   int looks = kResidentLooks;  // excmg_set_wait_limit
   // graphs of a batched round's CG iterations (excmg_solve_batched, on the batch's first handle), by launch shape
   struct BatchGraph {
@@ -1192,22 +1192,25 @@ void clear_stats(excmg_stats *st) {
 }
 
 // The cascade, once more without the resident CG if a workgroup of it gave up waiting for the others (which takes
-// another process holding CUs for about a second).
+// another process holding CUs for about a second).  The handle's later calls do without it too: what held the CUs may
+// last, and every call would wait for it again.
 template <typename Finish>
 int run_cascade(excmg_handle *h, int mode, const double *f, const double *g, excmg_stats *st, LevelIters *li,
                 Finish &&finish) {
   ResidentCall call{h};
   int e = cascade(h, mode, f, g, st, li, finish);
-  if (e != kGaveUp) return e;
+  if (e != kGaveUp) {
+    // (a grid after the one in error may have given up)
+    if (e != EXCMG_OK && e != EXCMG_ERR_NOCONV) launch_clear_state(h->cs, h->cs2, h->stream);
+    return e;
+  }
   HIPCHECK(hipStreamSynchronize(h->stream));
   clear_stats(st);
   reset_timing(h);
   if (li) *li = LevelIters{};
   launch_clear_state(h->cs, h->cs2, h->stream);
   h->apart = true;
-  e = cascade(h, mode, f, g, st, li, finish);
-  h->apart = false;
-  return e;
+  return cascade(h, mode, f, g, st, li, finish);
 }
 
 void fill_level_stats(excmg_handle *h, excmg_stats *st) {
@@ -1538,7 +1541,6 @@ int batched_solve(excmg_handle *const *hs, int count, const double *const *f, co
   // problems on a grid of one launch this round: direct solves (small, larger), the one-workgroup CG, the resident CG
   std::vector<int> dsmall, dlarge, small, res, expect;
   std::vector<Grid> res_grid;
-  std::vector<char> apart(count, 0);  // a workgroup of the resident CG gave up waiting: this problem runs without it
   int final_status = EXCMG_OK, remaining = count;
   // a problem's grid is finished: record it, then start its next grid (or copy it out)
   auto finish_grid = [&](int b) -> int {
@@ -1595,7 +1597,7 @@ int batched_solve(excmg_handle *const *hs, int count, const double *const *f, co
           }
           if (l <= 1) add(kListSetB, l, b, nblk(l, b, kLSetB), 0, 0);
           else add(kListExp, l, b, nblk(l, b, kLExp), 0, 0);
-          if (lv.res.threads && !apart[b]) {
+          if (lv.res.threads && !hs[b]->apart) {
             res.push_back(b);
             res_grid.push_back(lv.g);
             const int before = hstat[b].m[0].iter;  // on the grid below; none where that was solved directly
@@ -1702,7 +1704,8 @@ int batched_solve(excmg_handle *const *hs, int count, const double *const *f, co
     bool any64 = false, any32 = false;
     for (int b : res)
       if (hstat[b].m[0].abort) {
-        apart[b] = 1;
+        launch_clear_state(hs[b]->cs, hs[b]->cs2, s);
+        hs[b]->apart = true;
         ph[b] = kPhStart;
       }
     for (int b = 0; b < count; ++b) {
@@ -2408,6 +2411,7 @@ int excmg_set_timing(excmg_handle *h, int32_t on) {
 int excmg_set_wait_limit(excmg_handle *h, int32_t looks) {
   if (!h || looks < 0) return EXCMG_ERR_ARG;
   h->looks = looks;
+  h->apart = false;
   return EXCMG_OK;
 }
 

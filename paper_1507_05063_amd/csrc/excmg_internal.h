@@ -192,6 +192,7 @@ struct CgState {
   double cross, alast;   // r.r_before and alpha of the last iteration
   unsigned count;        // workgroups that have finished the current launch (0 between launches)
   int tune;              // the autotuner's trials: the scalars stay as they are
+  int skip, pad_;        // the resident CG's launch does nothing: an earlier one of the call gave up
   double hist[EXCMG_MAX_HISTORY];
 };
 
@@ -286,7 +287,7 @@ struct Resident {
   ResidentPlan plan;
 };
 constexpr int kResidentLooks = 1 << 20;  // about a second
-// before launch_resident: the slots it meets by, and no give-up recorded
+// before launch_resident: the slots it meets by, and whether it has anything to do
 struct ResidentInit {
   double *slots;
   int n;  // 0: no resident CG
@@ -304,7 +305,7 @@ __device__ __forceinline__ void resident_init_block(const ResidentInit &i) {
   if (threadIdx.x != 0) return;
   if (i.mark) *i.mark = (long long)wall_clock64();
   if (i.n > 0) {
-    i.cs->abort = 0;
+    i.cs->skip = i.cs->abort;
     if (i.out) i.out->abort = 0;
   }
 }
@@ -336,7 +337,7 @@ int selfred_max_blocks();
 void launch_selfred_init(CgState *cs, int max_iters, int hist_on, int preset, hipStream_t st);
 // cs->gbnd2 = the sum of g^2 over the boundary nodes of grid g (0 if rs.fg is 0 or rs.mode is 1); one workgroup
 void launch_boundary_g2(const RhsSrc &rs, const Grid &g, CgState *cs, hipStream_t st);
-// gbnd2 and count = 0 for each state (at setup)
+// gbnd2, count and abort = 0 for each state (at setup, and after a give-up)
 void launch_clear_state(CgState *a, CgState *b, hipStream_t st);
 // residual sweep writing [r.r | b.b] partials without a finalize (for the self-finalizing iterations)
 void launch_residual_partials(const Sweep &sw, const double *u, const RhsSrc &rs, double *r, double *parts,
