@@ -106,7 +106,7 @@ __device__ __forceinline__ void mirror(const BatchEntry &E, const CgState *cs, B
   m.bnorm2 = cs->bnorm2;
   m.rho0 = cs->rho0;
   m.stop2 = cs->stop2;
-  if (final_state && E.finest && cs->done && stat[E.problem].t_done == 0)
+  if (final_state && E.finest && cs->done && !cs->abort && stat[E.problem].t_done == 0)
     stat[E.problem].t_done = (long long)wall_clock64();
 }
 

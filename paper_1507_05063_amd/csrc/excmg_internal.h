@@ -306,6 +306,7 @@ __device__ __forceinline__ void resident_init_block(const ResidentInit &i) {
   if (i.mark) *i.mark = (long long)wall_clock64();
   if (i.n > 0) {
     i.cs->skip = i.cs->abort;
+    i.cs->done = 0;
     if (i.out) i.out->abort = 0;
   }
 }
