@@ -76,8 +76,9 @@ extern "C" {
  * - FP64 grids whose vectors fit the chip (up to about 2^21 unknowns, 128^3 cells): the whole CG in one launch, in the
  *   single-reduction form of Chronopoulos and Gear (the same Krylov iterates as Algorithm 1's in exact arithmetic).
  *   Its workgroups wait for one another, so such launches of one process take turns on a device; where another
- *   process keeps them from running together for about a second, the call starts over without that form, and the
- *   handle's later calls do without it (until excmg_set_wait_limit).
+ *   process keeps them from running together for about 0.3 s, the call starts over without that form, and the
+ *   handle's later calls do without it (until excmg_set_wait_limit).  A stream made for a part of the device's CUs
+ *   does without it from the start.
  * - Grids above 2^21 unknowns (in FP64, and in FP32 under EXCMG_FP32_IR): pairs of iterations in two sweeps a pair.  The
  *   first forms M p and M (M p) and sums the products from which the second iteration's coefficients follow, the
  *   second makes both iterations (one where it converges or reaches the cap after the first), at half the bytes of
@@ -306,7 +307,7 @@ int excmg_set_timing(excmg_handle *h, int32_t on);
 
 /* Host only.  How many times a workgroup of the one-launch CG (see EXCMG_TWO_PASS_CG) of this handle's later calls looks
  * for the others at a meeting before it gives up, upon which this call and the handle's later ones run the sweeps
- * instead: 2^20, about a second, from setup on; 0 gives up at the first meeting.  An earlier give-up is forgotten.  In a
+ * instead: 2^20, about 0.3 s, from setup on; 0 gives up at the first meeting.  An earlier give-up is forgotten.  In a
  * batch it holds for the handle's own problem.  Errors: EXCMG_ERR_ARG for a null handle or a negative count. */
 int excmg_set_wait_limit(excmg_handle *h, int32_t looks);
 

@@ -213,7 +213,7 @@ class Solver:
 
     def set_wait_limit(self, looks: int):
         """How many times a workgroup of the one-launch CG looks for the others before this call and later ones run the
-        sweeps instead (2**20, about a second, from setup on; 0: at once).  An earlier give-up is forgotten."""
+        sweeps instead (2**20, about 0.3 s, from setup on; 0: at once).  An earlier give-up is forgotten."""
         _lib.check(_lib.lib().excmg_set_wait_limit(self._h, int(looks)), "excmg_set_wait_limit")
 
     def set_timing(self, on: bool):

@@ -280,6 +280,7 @@ struct excmg_handle {
   bool late = false;  // this call's outputs lie over its inputs: nothing is written there while it may start over
   bool apart = false; // no grid is relaxed by the resident CG any more: a workgroup of it gave up waiting
   int looks = kResidentLooks;  // excmg_set_wait_limit
+  bool whole = false; // the stream may use every CU of the device (what the resident CG asks for)
   // graphs of a batched round's CG iterations (excmg_solve_batched, on the batch's first handle), by launch shape
   struct BatchGraph {
     std::vector<long long> key;
@@ -334,7 +335,7 @@ inline int last_error() { return hipGetLastError() == hipSuccess ? EXCMG_OK : EX
 
 constexpr int kResidentTick = -2;  // TimedLaunch.iter of a resident CG: all iterations' passes in one launch
 
-constexpr int kMaxDevices = 64;
+constexpr int kMaxDevices = 64, kMaxCus = 1024;
 
 // Kernel timing: a pair of events around each launch on the finest grid when EXCMG_WANT_TIMING is set (the coarser
 // grids' launches are replayed from graphs, and their event records would cost as much as the kernels they time).
@@ -817,11 +818,21 @@ int small_cg(excmg_handle *h, int l, const RhsSrc &rs, bool exact, bool finest, 
 }
 
 // The resident CG's bricks of every grid that runs it: the FP64 relaxations, unless EXCMG_TWO_PASS_CG, as far as a
-// grid fits the device's CUs.
+// grid fits the device's CUs.  None on a stream that was made for a part of the CUs: workgroups are dealt out to the XCDs
+// in turn, whatever CUs the mask leaves each, so a launch might wait for workgroups that have no place.
 int plan_resident(excmg_handle *h) {
   int cus = 0;
   HIPCHECK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device));
-  if ((h->p.flags & EXCMG_TWO_PASS_CG) || h->device >= kMaxDevices) return EXCMG_OK;
+  uint32_t mask[kMaxCus / 32] = {};
+  h->whole = true;
+  if (hipExtStreamGetCUMask(h->stream, kMaxCus / 32, mask) == hipSuccess) {
+    int n = 0;
+    for (uint32_t m : mask) n += __builtin_popcount(m);
+    h->whole = n == 0 || n >= cus;
+  } else {
+    (void)hipGetLastError();  // (no mask to be had)
+  }
+  if ((h->p.flags & EXCMG_TWO_PASS_CG) || h->device >= kMaxDevices || !h->whole) return EXCMG_OK;
   for (int l = 2; l < h->lo.L; ++l) {
     Level &lv = h->lo.lev[l];
     if (h->p.precision == EXCMG_FP64 || lv.g.interior() < kIrMinUnknowns)
@@ -1192,7 +1203,7 @@ void clear_stats(excmg_stats *st) {
 }
 
 // The cascade, once more without the resident CG if a workgroup of it gave up waiting for the others (which takes
-// another process holding CUs for about a second).  The handle's later calls do without it too: what held the CUs may
+// another process holding CUs for about 0.3 s).  The handle's later calls do without it too: what held the CUs may
 // last, and every call would wait for it again.
 template <typename Finish>
 int run_cascade(excmg_handle *h, int mode, const double *f, const double *g, excmg_stats *st, LevelIters *li,
@@ -1597,7 +1608,7 @@ int batched_solve(excmg_handle *const *hs, int count, const double *const *f, co
           }
           if (l <= 1) add(kListSetB, l, b, nblk(l, b, kLSetB), 0, 0);
           else add(kListExp, l, b, nblk(l, b, kLExp), 0, 0);
-          if (lv.res.threads && !hs[b]->apart) {
+          if (lv.res.threads && hs[0]->whole && !hs[b]->apart) {
             res.push_back(b);
             res_grid.push_back(lv.g);
             const int before = hstat[b].m[0].iter;  // on the grid below; none where that was solved directly

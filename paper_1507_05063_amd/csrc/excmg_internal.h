@@ -286,7 +286,7 @@ struct Resident {
   int looks;  // at the slots before a workgroup gives up waiting
   ResidentPlan plan;
 };
-constexpr int kResidentLooks = 1 << 20;  // about a second
+constexpr int kResidentLooks = 1 << 20;  // about 0.3 s
 // before launch_resident: the slots it meets by, and whether it has anything to do
 struct ResidentInit {
   double *slots;

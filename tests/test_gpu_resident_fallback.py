@@ -135,3 +135,35 @@ def test_batch_time_counts_the_sweeps(ex):
             s.set_wait_limit(0)
             times[two_pass] = ex.solve_batched([s], [dev(f)], [dev(g)])[2][0]
     assert times[False] >= 0.5 * times[True], times
+
+
+@gpu
+def test_stream_of_half_the_cus(ex):
+    """A stream made for half of the CUs, where 256 workgroups cannot run together: the sweeps from the start, alone and
+    in a batch that it leads, without a wait for the others."""
+    import time
+
+    import torch
+
+    hip = ctypes.CDLL("libamdhip64.so")
+    raw = ctypes.c_void_p(0)
+    mask = (ctypes.c_uint32 * 8)(*[0xFFFF] * 8)
+    if hip.hipExtStreamCreateWithCUMask(ctypes.byref(raw), 8, mask) != 0:
+        pytest.skip("no stream with a CU mask to be had")
+    n, nc = (128, 128, 128), (16, 16, 16)
+    f, g, _ = (dev(v) for v in synth.sample(synth.smooth(1), n))
+    part = ex.Solver(n, (1.0,) * 3, 1e-10, nc, stream=torch.cuda.ExternalStream(raw.value))
+    whole = ex.Solver(n, (1.0,) * 3, 1e-10, nc)
+    want = ex.Solver(n, (1.0,) * 3, 1e-10, nc, two_pass_cg=True).solve(f, g)[0]
+    for s in (part, whole):
+        s.set_wait_limit(1 << 22)  # a wait of more than a second
+    torch.cuda.synchronize()
+    t = time.perf_counter()
+    u = part.solve(f, g)[0]
+    us, _, _ = ex.solve_batched([part, whole], [f, f], [g, g])
+    t = time.perf_counter() - t
+    part.close()
+    assert hip.hipStreamDestroy(raw) == 0
+    assert torch.equal(u, want) and t < 0.5, t
+    for v in us:
+        assert torch.linalg.vector_norm(v - want) <= 1e-9 * torch.linalg.vector_norm(want)
