@@ -75,10 +75,10 @@ extern "C" {
  * Default, from the third grid on and with the same iterates up to rounding and so the same iteration counts:
  * - FP64 grids whose vectors fit the chip (up to about 2^21 unknowns, 128^3 cells): the whole CG in one launch, in the
  *   single-reduction form of Chronopoulos and Gear (the same Krylov iterates as Algorithm 1's in exact arithmetic).
- *   Its workgroups wait for one another, so such launches of one process take turns on a device; where another
- *   process keeps them from running together for about 0.3 s, the call starts over without that form, and the
- *   handle's later calls do without it (until excmg_set_wait_limit).  A stream made for a part of the device's CUs
- *   does without it from the start.
+ *   Its workgroups wait for one another, so such launches of one process that have no room on a device together take
+ *   turns there; where another process or another long kernel keeps them from running together for about 0.3 s, the
+ *   call starts over without that form, and the handle's later calls do without it (until excmg_set_wait_limit).  A
+ *   stream made for a part of the device's CUs does without it from the start.
  * - Grids above 2^21 unknowns (in FP64, and in FP32 under EXCMG_FP32_IR): pairs of iterations in two sweeps a pair.  The
  *   first forms M p and M (M p) and sums the products from which the second iteration's coefficients follow, the
  *   second makes both iterations (one where it converges or reaches the cap after the first), at half the bytes of

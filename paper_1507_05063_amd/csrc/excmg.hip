@@ -20,6 +20,7 @@
 #include <chrono>
 #include <mutex>
 #include <new>
+#include <thread>
 #include <vector>
 
 #include "excmg_internal.h"
@@ -281,6 +282,11 @@ struct excmg_handle {
   bool apart = false; // no grid is relaxed by the resident CG any more: a workgroup of it gave up waiting
   int looks = kResidentLooks;  // excmg_set_wait_limit
   bool whole = false; // the stream may use every CU of the device (what the resident CG asks for)
+  int cus = 0;        // of the device
+  // this call's place among the device's calls with resident launches (ResidentTurn; 0 workgroups: none)
+  excmg_handle *turn_next = nullptr;
+  int turn_wgs = 0;
+  hipEvent_t turn_done = nullptr, turn_wait = nullptr;
   // graphs of a batched round's CG iterations (excmg_solve_batched, on the batch's first handle), by launch shape
   struct BatchGraph {
     std::vector<long long> key;
@@ -305,6 +311,8 @@ struct excmg_handle {
   ~excmg_handle() {
     drop_graphs();
     if (cap) (void)hipStreamDestroy(cap);
+    for (hipEvent_t ev : {turn_done, turn_wait})
+      if (ev) (void)hipEventDestroy(ev);
     for (auto &ev : pool)
       if (ev) (void)hipEventDestroy(ev);
     if (pin_host) (void)hipHostFree(pin_host);
@@ -824,6 +832,7 @@ int plan_resident(excmg_handle *h) {
   int cus = 0;
   HIPCHECK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device));
   uint32_t mask[kMaxCus / 32] = {};
+  h->cus = cus;
   h->whole = true;
   if (hipExtStreamGetCUMask(h->stream, kMaxCus / 32, mask) == hipSuccess) {
     int n = 0;
@@ -841,41 +850,108 @@ int plan_resident(excmg_handle *h) {
   return EXCMG_OK;
 }
 
-// Per device, the handle whose call in progress launched the resident CG last.  Its workgroups wait for one another, so
-// those of two launches must never compete for the CUs: a launch first waits for the other handle's stream (calls on
-// different handles only overlap from different host threads).  A call gives the place up when its work is done.
+// Measured, solves of 32^3 / 64 x 48 x 32 / 128^3 cells from eight threads, us a solve: 153 / 374 / 1230 so, 382 / 510 /
+// 1120 where every launch waited for the call before it, 296 / 528 / 1410 as sweeps, which wait for nothing.
+// Per device, the calls in progress that have launched the resident CG, and how many workgroups of it each may have
+// running at once (the largest of its launches: a call's own follow one another).  Its workgroups wait for one another,
+// so all calls' together must have room on the CUs: a launch that would take more than are left runs after what as many of
+// the other calls have launched so far as would free enough, those first whose last launch is the oldest.  (So of the
+// launches that run at one time, the one launched last has counted all the others.)  Workgroups are dealt out to the
+// XCDs in turn and, there, to four shader engines, so a launch counts as its next multiple of 32.  A call leaves its
+// place when its work is done.
 struct ResidentTurn {
   std::mutex mu;
-  const excmg_handle *last = nullptr;
+  excmg_handle *first = nullptr;  // by the age of the last launch
+  void leave(excmg_handle *h) {
+    excmg_handle **p = &first;
+    while (*p != h) p = &(*p)->turn_next;
+    *p = h->turn_next;
+  }
+  void join(excmg_handle *h) {
+    excmg_handle **p = &first;
+    while (*p) p = &(*p)->turn_next;
+    *p = h;
+    h->turn_next = nullptr;
+  }
 };
 ResidentTurn g_resident[kMaxDevices];
-// launch() of h's resident CG in its turn.  The per-thread default stream is another stream in another thread, which
-// could not wait for it: there the turn ends when the launch has.
-template <typename F>
-int in_turn(excmg_handle *h, F &&launch) {
-  ResidentTurn &turn = g_resident[h->device];
-  std::lock_guard<std::mutex> lock(turn.mu);
-  if (turn.last && turn.last != h) HIPCHECK(hipStreamSynchronize(turn.last->stream));
-  turn.last = h;
-  int e = launch();
-  if (h->stream == hipStreamPerThread) {
-    if (hipStreamSynchronize(h->stream) != hipSuccess && !e) e = EXCMG_ERR_HIP;
-    turn.last = nullptr;
+constexpr int kTurnRound = 4 * kXcds;
+
+int need_event(hipEvent_t *ev) {
+  if (*ev) return EXCMG_OK;
+  HIPCHECK(hipEventCreateWithFlags(ev, hipEventDisableTiming));
+  return EXCMG_OK;
+}
+
+// What h launches next runs after what o has launched so far.  o's stream cannot be named in this thread if it is the
+// per-thread default stream, so o has left an event behind its launch.  A handle without events waits on the host.
+int run_after(excmg_handle *h, excmg_handle *o) {
+  const bool named = o->stream != hipStreamPerThread;
+  if (named && o->stream == h->stream) return EXCMG_OK;
+  if (h->noalloc) {
+    HIPCHECK(named ? hipStreamSynchronize(o->stream) : hipEventSynchronize(o->turn_done));
+    return EXCMG_OK;
   }
+  hipEvent_t ev = o->turn_done;
+  if (named) {
+    const int e = need_event(&h->turn_wait);
+    if (e) return e;
+    ev = h->turn_wait;
+    HIPCHECK(hipEventRecord(ev, o->stream));
+  }
+  HIPCHECK(hipStreamWaitEvent(h->stream, ev, 0));
+  return EXCMG_OK;
+}
+
+// Before a call's first resident launch: until its stream has come to the call, whose first kernel writes the first
+// mark.  A call that waits for work queued before it on its stream so keeps no other call waiting.  (It mostly has by
+// then: the direct solves are queued.)
+int stream_reached(excmg_handle *h) {
+  if (h->noalloc) return EXCMG_OK;
+  const volatile long long *mark = (const volatile long long *)((const char *)h->pin_host + kPinMarks);
+  for (int look = 0; *mark == 0 && look < 100; ++look) std::this_thread::yield();
+  if (*mark == 0) HIPCHECK(hipStreamSynchronize(h->stream));
+  return EXCMG_OK;
+}
+
+// launch() of h's resident CG, at most wgs workgroups at once, in its turn.
+template <typename F>
+int in_turn(excmg_handle *h, int wgs, F &&launch) {
+  ResidentTurn &turn = g_resident[h->device];
+  const bool per_thread = h->stream == hipStreamPerThread;
+  int e = EXCMG_OK;
+  if (per_thread && !h->noalloc && (e = need_event(&h->turn_done))) return e;
+  std::lock_guard<std::mutex> lock(turn.mu);
+  const int round = (wgs + kTurnRound - 1) / kTurnRound * kTurnRound, mine = round > h->turn_wgs ? round : h->turn_wgs;
+  if (h->turn_wgs != 0) turn.leave(h);
+  int others = 0;
+  for (excmg_handle *o = turn.first; o; o = o->turn_next) others += o->turn_wgs;
+  for (excmg_handle *o = turn.first; o && !e && others + mine > h->cus; o = o->turn_next) {
+    e = run_after(h, o);
+    others -= o->turn_wgs;
+  }
+  if (h->turn_wgs != 0) turn.join(h);
+  if (e) return e;
+  if (per_thread && h->noalloc) {  // no event to leave: the place is kept until the launch has ended
+    e = launch();
+    if (hipStreamSynchronize(h->stream) != hipSuccess && !e) e = EXCMG_ERR_HIP;
+    return e;
+  }
+  if (h->turn_wgs == 0) turn.join(h);
+  h->turn_wgs = mine;
+  e = launch();
+  if (per_thread && hipEventRecord(h->turn_done, h->stream) != hipSuccess && !e) e = EXCMG_ERR_HIP;
   return e;
 }
 struct ResidentCall {
   excmg_handle *h;
   ~ResidentCall() {
-    if (h->device < 0 || h->device >= kMaxDevices) return;
-    ResidentTurn &t = g_resident[h->device];
-    {
-      std::lock_guard<std::mutex> lock(t.mu);
-      if (t.last != h) return;
-    }
+    if (h->turn_wgs == 0) return;  // (set by this thread only)
     (void)hipStreamSynchronize(h->stream);
+    ResidentTurn &t = g_resident[h->device];
     std::lock_guard<std::mutex> lock(t.mu);
-    if (t.last == h) t.last = nullptr;
+    t.leave(h);
+    h->turn_wgs = 0;
   }
 };
 
@@ -910,9 +986,13 @@ Resident resident_args(excmg_handle *h, int l, const RhsSrc &rs, const excmg_sta
 // The resident CG of grid l from the current u, in one launch (the grid's initial guess has set its slots).
 int resident_cg(excmg_handle *h, int l, const RhsSrc &rs, int *iters, double *relres, excmg_stats *st) {
   const Resident a = resident_args(h, l, rs, st);
+  if (h->turn_wgs == 0) {
+    const int e = stream_reached(h);
+    if (e) return e;
+  }
   {
     Tick t(h, EXCMG_K_CG_A, l, kResidentTick);
-    const int e = in_turn(h, [&]() {
+    const int e = in_turn(h, a.plan.gx * a.plan.gy * a.plan.gz, [&]() {
       launch_resident(a, h->stream);
       return last_error();
     });
@@ -1060,6 +1140,7 @@ int cascade(excmg_handle *h, int mode, const double *f, const double *g, excmg_s
   Layout &lo = h->lo;
   const int L = lo.L;
   const hipStream_t s = h->stream;
+  if (!h->noalloc) *((volatile long long *)((char *)h->pin_host + kPinMarks)) = 0;  // (stream_reached)
   int final_status = EXCMG_OK;
   bool deferred[EXCMG_MAX_LEVELS] = {};  // grids solved in one launch whose outcome is read after the loop
   // The outcomes of the deferred solves of the grids below `upto`, in one read: their stats, NOCONV into
@@ -1203,7 +1284,7 @@ void clear_stats(excmg_stats *st) {
 }
 
 // The cascade, once more without the resident CG if a workgroup of it gave up waiting for the others (which takes
-// another process holding CUs for about 0.3 s).  The handle's later calls do without it too: what held the CUs may
+// another process or another long kernel holding CUs for about 0.3 s).  The handle's later calls do without it too: what held the CUs may
 // last, and every call would wait for it again.
 template <typename Finish>
 int run_cascade(excmg_handle *h, int mode, const double *f, const double *g, excmg_stats *st, LevelIters *li,
@@ -1691,7 +1772,9 @@ int batched_solve(excmg_handle *const *hs, int count, const double *const *f, co
       for (const auto &p : packs) key.insert(key.end(), {p.brick, p.blocks, (long long)p.problems.size()});
       const int from = at;
       key_list(key, part(res.size(), 0));
-      e = in_turn(hs[0], [&]() {
+      int wgs = 0;
+      for (const auto &p : packs) wgs = std::max(wgs, p.blocks);
+      e = in_turn(hs[0], wgs, [&]() {
         return batch_replay(hs[0], key, [&](hipStream_t st) {
           at = from;
           const BatchList all = part(res.size(), 0);
