@@ -247,6 +247,8 @@ int excmg_batch_graph_counts(const excmg_handle *h, int64_t *replays, int64_t *c
  * launch holds all the batch's grids, so one height and depth are chosen per precision (those whose fastest chunks
  * sum to the least time), and the chunks, height and depth are kept in those problems' handles (replacing what
  * excmg_autotune chose there; results do not depend on them; excmg_get_sweep and excmg_get_batch_shape read them).
+ * On grids that run iterations in pairs alone (see EXCMG_TWO_PASS_CG) the chunks hold for batches only; the pairs are
+ * back at their default.
  * Trial launches touch only the handles' work buffers and CG states.
  * batch_ws: as for excmg_solve_batched.  zc_out (host, nullable, 2 * EXCMG_MAX_LEVELS entries): zc_out[2 t + p] the
  * chunk chosen for grid t in precision p (0 FP64, 1 FP32), 0 where no problem relaxes that grid that way. */
@@ -265,7 +267,8 @@ int excmg_autotune_batched(excmg_handle *const *hs, int32_t count, void *batch_w
  * zc_out, depth_out (host, nullable, 4 * levels entries each): per grid, pass A and pass B in FP64, then in FP32 (0
  * where the grid is not relaxed that way): the chunk, and depth + 10 (if the non-temporal policy won) + 100 * tile
  * height.  Batched solves (excmg_solve_batched) keep the chunk and use the handle's batch shape
- * (excmg_get_batch_shape; excmg_autotune_batched chooses it).
+ * (excmg_get_batch_shape; excmg_autotune_batched chooses it); on grids that run iterations in pairs, which a batch
+ * relaxes in two passes an iteration, they keep their own default chunk.
  * Optional: without it the handle uses a default: for pairs of iterations the shape whose rounds of resident
  * workgroups take the least estimated time, else 16 planes, fewer on small grids; 4 rows; depth 2; ordinary. */
 int excmg_autotune(excmg_handle *h, int32_t *zc_out, int32_t *depth_out);

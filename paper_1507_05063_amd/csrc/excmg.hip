@@ -35,6 +35,8 @@ using namespace excmg;
 
 namespace {
 
+enum ShapeFrom : unsigned char { kFromDefault, kFromAlone, kFromBatch, kFromCaller };  // excmg_autotune, ..._batched, set
+
 struct Level {
   int n[3];
   double h[3];
@@ -46,7 +48,11 @@ struct Level {
   Sweep swA, swB, swA32, swB32;  // CG passes A and B in FP64 and FP32 (z chunk chosen by the autotuner)
   Sweep swA0, swB0;  // the FP64 passes of a grid's first iterations (p = r), on grids launched without graphs
   ResidentPlan res;  // the resident CG's bricks (threads 0: the grid does not run it)
-  bool shaped;       // the CG passes' shapes were tuned or set (else batched solves take their own default)
+  // Grids that run iterations in pairs alone and in two passes in a batch (two_grid): where the shapes of swA, swB, swA32
+  // and swB32 come from, and the pairs' defaults.  Shapes timed for the one form are not used for the other.
+  bool two;
+  ShapeFrom from[4];
+  Sweep pair[4];
   double *u;   // this grid's solution, all nodes (boundary = g)
 };
 
@@ -192,7 +198,11 @@ int make_layout(const excmg_problem *p, Layout *Lo) {
     }
     lv.swA0 = lv.swA;
     lv.swB0 = lv.swB;
-    lv.shaped = false;
+    lv.two = two_grid(lv, *p);
+    for (int k = 0; k < 4; ++k) {
+      lv.from[k] = kFromDefault;
+      lv.pair[k] = k < 2 ? (k ? lv.swB : lv.swA) : (k == 3 ? lv.swB32 : lv.swA32);
+    }
     lv.res = {};
     lv.u = nullptr;
     Lo->off_u[l] = off;
@@ -532,6 +542,12 @@ struct OutputBinding {
   }
 };
 
+// The shape of grid l's pairs (k: swA, swB, swA32, swB32): one that was timed for a batch's passes is not theirs.
+const Sweep &pair_shape(const Level &lv, int k) {
+  if (lv.from[k] == kFromBatch) return lv.pair[k];
+  return k < 2 ? (k ? lv.swB : lv.swA) : (k == 3 ? lv.swB32 : lv.swA32);
+}
+
 // Iterations 2 * pair and 2 * pair + 1 of grid l by the two-step sweeps.
 void launch_pair(excmg_handle *h, int l, int fp32, hipStream_t s, int pair, int outer) {
   Level &lv = h->lo.lev[l];
@@ -539,20 +555,20 @@ void launch_pair(excmg_handle *h, int l, int fp32, hipStream_t s, int pair, int 
     const TwoVecs<float> v = two_vecs32(h, l);
     {
       Tick t(h, EXCMG_K_CG_A32, l, pair, outer);
-      launch_two_g<float>(lv.swA32, v, h->cs2, h->partials, s);
+      launch_two_g<float>(pair_shape(lv, 2), v, h->cs2, h->partials, s);
     }
     Tick t(h, EXCMG_K_CG_B32, l, pair, outer);
-    launch_two_u<float>(lv.swB32, v, h->cs2, h->partials, s);
+    launch_two_u<float>(pair_shape(lv, 3), v, h->cs2, h->partials, s);
     return;
   }
   const TwoVecs<double> v = two_vecs64(h, l);
   const bool first = pair == 0;  // (never in a graph)
   {
     Tick t(h, EXCMG_K_CG_A, l, pair);
-    launch_two_g<double>(first ? lv.swA0 : lv.swA, v, h->cs, h->partials, s);
+    launch_two_g<double>(first ? lv.swA0 : pair_shape(lv, 0), v, h->cs, h->partials, s);
   }
   Tick t(h, EXCMG_K_CG_B, l, pair);
-  launch_two_u<double>(first ? lv.swB0 : lv.swB, v, h->cs, h->partials, s);
+  launch_two_u<double>(first ? lv.swB0 : pair_shape(lv, 1), v, h->cs, h->partials, s);
 }
 
 // One CG iteration of grid l on stream s: FP64 (fp32 = 0) on u, r, p, or the FP32 inner solve (fp32 = 1) on d32, r32,
@@ -1369,12 +1385,15 @@ void batch_entry(excmg_handle *h, int problem, int l, const double *f, const dou
   E->eta = h->p.inner_tol > 0.0 ? h->p.inner_tol : 1e-5;
   // every entry of a batched launch has the launch's tile height (bty: the batch's, for the FP64 and the FP32
   // passes); a grid tuned alone to another keeps its z chunk here
-  const Sweep own = make_sweep(lv.g, lv.st, 0), own32 = make_sweep(lv.g32, lv.st, 0);
-  E->swA = with_height(lv.shaped ? lv.swA : own, bty[0]);
-  E->swB = with_height(lv.shaped ? lv.swB : own, bty[0]);
+  auto passes = [&](int k, const Sweep &sw) {  // (a chunk timed for pairs does not suit them)
+    const bool own = lv.two && (lv.from[k] == kFromDefault || lv.from[k] == kFromAlone);
+    return with_height(own ? make_sweep(sw.g, lv.st, 0) : sw, bty[k / 2]);
+  };
+  E->swA = passes(0, lv.swA);
+  E->swB = passes(1, lv.swB);
   E->swR = default_height(lv.sw);
-  E->swA32 = with_height(lv.shaped ? lv.swA32 : own32, bty[1]);
-  E->swB32 = with_height(lv.shaped ? lv.swB32 : own32, bty[1]);
+  E->swA32 = passes(2, lv.swA32);
+  E->swB32 = passes(3, lv.swB32);
   E->g = lv.g;
   E->g32 = lv.g32;
   E->gd = lo.gdense;
@@ -1982,7 +2001,7 @@ int batched_autotune(excmg_handle *const *hs, int count, char *ws, int32_t *zc_o
           const Sweep sw = make_sweep(prec ? lv.g32 : lv.g, lv.st, zc, depth, 1, ty);
           if (prec) lv.swA32 = lv.swB32 = sw;
           else lv.swA = lv.swB = sw;
-          lv.shaped = true;
+          lv.from[2 * prec] = lv.from[2 * prec + 1] = kFromBatch;
         }
         if (zc_out) zc_out[2 * t + prec] = zc;
       }
@@ -2385,7 +2404,7 @@ int excmg_autotune(excmg_handle *h, int32_t *zc_out, int32_t *depth_out) {
         }
         if (rc) break;
         dst = bsw;
-        lv.shaped = true;
+        if (!first) lv.from[2 * prec + pass] = kFromAlone;
       }
     }
   }
@@ -2464,7 +2483,7 @@ int excmg_set_sweep(excmg_handle *h, int32_t level, int32_t kind, const int32_t 
   DeviceGuard dg(h->device);
   HIPCHECK(hipStreamSynchronize(h->stream));  // no launch of an earlier call still uses the old shape
   *sw = nw;
-  h->lo.lev[level].shaped = true;
+  if (kind <= EXCMG_SWEEP_B32) h->lo.lev[level].from[kind] = kFromCaller;
   h->drop_graphs();  // captured with the old sweep shapes
   return EXCMG_OK;
 }
