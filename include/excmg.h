@@ -243,12 +243,13 @@ int excmg_batch_graph_counts(const excmg_handle *h, int64_t *replays, int64_t *c
  * run together, so the z chunk a problem prefers alone is not the one the batch prefers.  For each grid counted from
  * the problems' finest (t = 0 each problem's finest grid, t = 1 the next coarser, ...) and each precision, every z
  * chunk in {2, 4, ..., 128} planes is timed as one flattened launch of the two CG passes over all problems whose grid
- * t relaxes in that precision, at each tile height (4, 8, 16 rows) and prefetch depth (2, 3, 4, 6 planes); a batched
- * launch holds all the batch's grids, so one height and depth are chosen per precision (those whose fastest chunks
- * sum to the least time), and the chunks, height and depth are kept in those problems' handles (replacing what
- * excmg_autotune chose there; results do not depend on them; excmg_get_sweep and excmg_get_batch_shape read them).
- * On grids that run iterations in pairs alone (see EXCMG_TWO_PASS_CG) the chunks hold for batches only; the pairs are
- * back at their default.
+ * t relaxes in that precision by sweeps (where no grid does in FP64, over those relaxed in one launch, which run the
+ * sweeps without that form, see EXCMG_TWO_PASS_CG), at each tile height (4, 8, 16 rows) and prefetch depth (2, 3, 4, 6
+ * planes); a batched launch holds all the batch's grids, so one height and depth are chosen per precision (those whose
+ * fastest chunks sum to the least time), and the chunks, height and depth are kept in those problems' handles
+ * (replacing what excmg_autotune chose there; results do not depend on them; excmg_get_sweep and
+ * excmg_get_batch_shape read them).  On grids that run iterations in pairs alone (see EXCMG_TWO_PASS_CG) the chunks
+ * hold for batches only; the pairs are back at their default.
  * Trial launches touch only the handles' work buffers and CG states.
  * batch_ws: as for excmg_solve_batched.  zc_out (host, nullable, 2 * EXCMG_MAX_LEVELS entries): zc_out[2 t + p] the
  * chunk chosen for grid t in precision p (0 FP64, 1 FP32), 0 where no problem relaxes that grid that way. */

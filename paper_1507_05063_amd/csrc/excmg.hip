@@ -1911,15 +1911,22 @@ int batched_autotune(excmg_handle *const *hs, int count, char *ws, int32_t *zc_o
   std::vector<int> bzc(2 * kH * (size_t)S, 0);
   float total[2][kH] = {};
   bool used[2] = {false, false};
+  // The grids that the batch's FP64 sweeps relax: not those of the resident CG, unless there are no others (they run the
+  // sweeps after a give-up).
+  auto resident = [&](int b, int l) { return hs[b]->lo.lev[l].res.threads && hs[0]->whole && !hs[b]->apart; };
+  bool sweeps = false;
+  for (int b = 0; b < count; ++b)
+    for (int l = 0; l < hs[b]->lo.L; ++l) sweeps = sweeps || (batch_kind(hs[b], l) == kBCg64 && !resident(b, l));
+  auto relaxes = [&](int b, int l, int prec) {
+    if (l < 0) return false;
+    const int kind = batch_kind(hs[b], l);
+    return prec ? kind == kBIr : kind == kBCg64 && !(sweeps && resident(b, l));
+  };
   for (int t = 0; t < S && rc == EXCMG_OK; ++t) {
     for (int prec = 0; prec < 2 && rc == EXCMG_OK; ++prec) {
       std::vector<int> probs;  // the problems whose grid L-1-t relaxes in this precision
-      for (int b = 0; b < count; ++b) {
-        const int l = hs[b]->lo.L - 1 - t;
-        if (l < 0) continue;
-        const int kind = batch_kind(hs[b], l);
-        if ((prec == 0 && kind == kBCg64) || (prec == 1 && kind == kBIr)) probs.push_back(b);
-      }
+      for (int b = 0; b < count; ++b)
+        if (relaxes(b, hs[b]->lo.L - 1 - t, prec)) probs.push_back(b);
       if (probs.empty()) continue;
       used[prec] = true;
       for (int hi = 0; hi < kH && rc == EXCMG_OK; ++hi) {
@@ -1994,9 +2001,7 @@ int batched_autotune(excmg_handle *const *hs, int count, char *ws, int32_t *zc_o
         if (zc == 0) continue;  // no problem relaxes grid t in this precision
         for (int b = 0; b < count; ++b) {
           const int l = hs[b]->lo.L - 1 - t;
-          if (l < 0) continue;
-          const int kind = batch_kind(hs[b], l);
-          if (!((prec == 0 && kind == kBCg64) || (prec == 1 && kind == kBIr))) continue;
+          if (!relaxes(b, l, prec)) continue;
           Level &lv = hs[b]->lo.lev[l];
           const Sweep sw = make_sweep(prec ? lv.g32 : lv.g, lv.st, zc, depth, 1, ty);
           if (prec) lv.swA32 = lv.swB32 = sw;

@@ -57,3 +57,14 @@ def test_single_after_the_tuner_of_batches(ex, data, ir):
     zc = ex.autotune_batched([s])
     assert s.get_sweep(s.levels - 1, "b32" if ir else "b")[0] == zc[0][ir]
     assert torch.equal(s.solve(f, g)[0], want)
+
+
+def test_tuner_of_batches_times_what_sweeps(ex):
+    """The batch's tuner times the grids that the sweeps relax, not those relaxed in one launch beside them; in a batch of
+    the latter alone it times them."""
+    big, small = ex.Solver(N, BOX, 1e-10, NC), ex.Solver((64, 48, 32), BOX, 1e-10, (16, 12, 8))
+    zc = ex.autotune_batched([big, small])
+    assert set(zc) == {0} and zc[0][0] > 0, zc
+    default = ex.Solver((64, 48, 32), BOX, 1e-10, (16, 12, 8)).get_sweep(2, "a")
+    assert small.get_sweep(2, "a") == default
+    assert ex.autotune_batched([small])[0][0] > 0
