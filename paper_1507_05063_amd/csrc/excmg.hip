@@ -2301,8 +2301,12 @@ int excmg_autotune(excmg_handle *h, int32_t *zc_out, int32_t *depth_out) {
   HIPCHECK(hipEventCreateWithFlags(&eb, kTimingEvent));
   int rc = EXCMG_OK;
   double *pa = h->partials, *pb = h->partials + lo.npart;
-  OutputBinding binding{h};  // the finest grid's trials have its own solution array for the fourth vector
-  h->xfin = lo.lev[lo.L - 1].u;
+  // The finest FP64 grid's pairs have no array for the fourth vector here.  Pass U reads or writes it in turn; its trials
+  // are of a pair that reads it, from p0, where the pair's r goes: a line is read, then written, as two arrays' would be.
+  // (In a pair that writes it, into u's array, u and p shared their lines: 1.24 ms at 511^3 where a solve's pass U takes
+  // 1.40 ms; so 1.41 ms.)
+  OutputBinding binding{h};
+  h->xfin = h->p0;
   h->gxfin = lo.gfin;
   for (int l = 0; l < lo.L && rc == EXCMG_OK; ++l) {
     Level &lv = lo.lev[l];
@@ -2337,7 +2341,7 @@ int excmg_autotune(excmg_handle *h, int32_t *zc_out, int32_t *depth_out) {
           float tmin = 1e30f;
           for (int rep = 0; rep < reps && rc == EXCMG_OK; ++rep) {
             if (two) {
-              launch_tune_state(h->cs2, first ? 0 : 1, s);
+              launch_tune_state(h->cs2, first ? 0 : (l == lo.L - 1 && prec == 0 && pass == 1) ? 2 : 1, s);
               if (burst) launch_delay(kTuneDelayUs, s);
             } else if (burst) {
               launch_tune_selfred(h->cs2, pass ? pa : pb, nb_other, s);
