@@ -192,7 +192,7 @@ struct CgState {
   double cross, alast;   // r.r_before and alpha of the last iteration
   unsigned count;        // workgroups that have finished the current launch (0 between launches)
   int tune;              // the autotuner's trials: the scalars stay as they are
-  int skip, pad_;        // the resident CG's launch does nothing: an earlier one of the call gave up
+  int looks, pad_;       // of the resident CG's launch before it gives up: 0 once an earlier one of the call has
   double hist[EXCMG_MAX_HISTORY];
 };
 
@@ -287,10 +287,11 @@ struct Resident {
   ResidentPlan plan;
 };
 constexpr int kResidentLooks = 1 << 20;  // about 0.3 s
-// before launch_resident: the slots it meets by, and whether it has anything to do
+// before launch_resident: the slots it meets by, and how long it may wait for them
 struct ResidentInit {
   double *slots;
   int n;  // 0: no resident CG
+  int looks;  // before the launch's workgroups give up waiting
   CgState *cs;
   Outcome *out;
   long long *mark;  // (nullable) the time, wall_clock64()
@@ -305,7 +306,7 @@ __device__ __forceinline__ void resident_init_block(const ResidentInit &i) {
   if (threadIdx.x != 0) return;
   if (i.mark) *i.mark = (long long)wall_clock64();
   if (i.n > 0) {
-    i.cs->skip = i.cs->abort;
+    i.cs->looks = i.cs->abort ? 0 : i.looks;
     i.cs->done = 0;
     if (i.out) i.out->abort = 0;
   }

@@ -21,7 +21,7 @@
 // process may hold CUs), and a workgroup that gives up says so in the CG state: the host then takes the grid up again
 // from its initial guess with the sweeps.  (Others may have got through the same meeting and, if it was the last, have
 // written their part of the solution and the outcome: only the give-up counts then.)  Until the host has seen it, later
-// launches of the same call end before their first meeting (CgState::skip), instead of waiting once more each.  (A
+// launches of the same call end at their first meeting (CgState::looks), instead of waiting once more each.  (A
 // cooperative launch would keep launches apart too, but costs about 190 us on this runtime.)
 // Measured per iteration: 128^3 31 -> 11 us (operator and updates 4 us, meeting 3, publishing and the layer 4), 64^3
 // 11 -> 5.1 us, 32^3 10 -> 4.1 us, 16^3 (one workgroup before) 6.5 -> 2.7 us.
@@ -91,6 +91,7 @@ struct Meeting {
   double mine[2][NW];  // the waves' sums of the workgroup's own values
   double sum[2];       // the sums over all workgroups
   int there;           // whether all have arrived
+  int looks;           // at the slots before this workgroup gives up
 };
 
 // A set of slots: per group of 32 workgroups 32 slots of a and 32 of b, then one line of the groups' sums.
@@ -116,8 +117,7 @@ __device__ __forceinline__ double await(const double *p, bool mine, int looks, b
 // adds up its group, and read the groups' sums (256 workgroups that all read 512 slots get in one another's way: 3.6 us
 // a meeting, against 1.2 us among four).
 template <int NW>
-__device__ __forceinline__ bool meet(double &a, double &b, double *slots, int seq, int bid, int nb, int looks,
-                                     Meeting<NW> &m) {
+__device__ __forceinline__ bool meet(double &a, double &b, double *slots, int seq, int bid, int nb, Meeting<NW> &m) {
   const int groups = (nb + kGroup - 1) / kGroup;
   __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");  // what this thread has published has arrived
   a = wave_sum63(a);
@@ -139,7 +139,7 @@ __device__ __forceinline__ bool meet(double &a, double &b, double *slots, int se
     bool there = true;
     if (leader) {
       const bool mine = kGroup * group + (lane & 31) < nb;
-      x = row_sum(await(&slots[now + 2 * kGroup * group + lane], mine, looks, there));
+      x = row_sum(await(&slots[now + 2 * kGroup * group + lane], mine, m.looks, there));
       x += dpp<0x142, 0xa>(x);  // lane 31: the group's a, lane 63: its b
       if (groups > 1 && there && (lane & 31) == 31) {
         if (!(x == x)) x = __longlong_as_double(0x7ff8000000000000ll);
@@ -147,7 +147,7 @@ __device__ __forceinline__ bool meet(double &a, double &b, double *slots, int se
       }
     }
     if (groups > 1) {
-      x = await(&slots[now + line + (lane & 15)], lane < 16 && (lane & 7) < groups, looks, there);
+      x = await(&slots[now + line + (lane & 15)], lane < 16 && (lane & 7) < groups, m.looks, there);
       // lanes 7 and 15: the sums of eight
       x += dpp<0x111>(x);
       x += dpp<0x112>(x);
@@ -211,6 +211,7 @@ __device__ __forceinline__ void resident_cg(const Resident &a, double *u_, doubl
   // more than 2^29 elements
   const unsigned own = (unsigned)(g.at(i, j, k0 + lz) * (long long)sizeof(double));
   auto node = [&](auto *base, int q) { return at_byte(base + q * g.sz, own); };
+  if (tid == 0) meeting.looks = cs->looks;
   // u of the brick and its layer (0 outside the interior)
   for (int e = tid; e < plane * (BZ + 2); e += nt) {
     const int x = e % PX, yz = e / PX, y = yz % PY, z = yz / PY;
@@ -333,7 +334,7 @@ __device__ __forceinline__ void resident_cg(const Resident &a, double *u_, doubl
   publish(1, w);
   const double gbnd2 = uniform(cs->gbnd2);
   int seq = 0;
-  bool here = !__builtin_amdgcn_readfirstlane(cs->skip) && meet(gam, bsum, slots, seq++, bid, nb, a.looks, meeting);
+  bool here = meet(gam, bsum, slots, seq++, bid, nb, meeting);
   const double rho0 = gam, bb = bsum + gbnd2;
   const double stop2 = a.tol * a.tol * bb;
 #pragma unroll
@@ -347,7 +348,7 @@ __device__ __forceinline__ void resident_cg(const Resident &a, double *u_, doubl
   double gold = 1.0, aold = 1.0, gamma = rho0;
   int k = 0, status = 0;
   while (here) {
-    here = meet(gam, del, slots, seq++, bid, nb, a.looks, meeting);
+    here = meet(gam, del, slots, seq++, bid, nb, meeting);
     if (!here) break;
     gamma = gam;
     const double delta = del;
@@ -451,7 +452,6 @@ __global__ __launch_bounds__(BX * BY * ZS) void b_resident_cg_kernel(BatchList L
   a.tol = E.tol;
   a.cap = E.cap;
   a.hist_on = 0;
-  a.looks = E.looks;
   a.out = nullptr;
   double *const scratch = as_global(E.p1);
   const int gx = (E.g.nx - 1 + BX - 1) / BX, gy = (E.g.ny - 1 + BY - 1) / BY;
@@ -461,7 +461,7 @@ __global__ __launch_bounds__(BX * BY * ZS) void b_resident_cg_kernel(BatchList L
 
 __global__ void b_resident_init_kernel(BatchList L) {
   const BatchEntry &E = entry_at(L, blockIdx.x);
-  resident_init_block({E.p1, slots_of(L.pre[blockIdx.x + 1] - L.pre[blockIdx.x]), E.cs, nullptr, nullptr});
+  resident_init_block({E.p1, slots_of(L.pre[blockIdx.x + 1] - L.pre[blockIdx.x]), E.looks, E.cs, nullptr, nullptr});
 }
 
 __global__ void b_mirror_kernel(BatchList L, BatchStatus *stat) {
@@ -513,7 +513,7 @@ ResidentPlan resident_plan(const Grid &g, int blocks) {
 }
 
 ResidentInit resident_init(const Resident &a) {
-  return {a.scratch, slots_of(a.plan.gx * a.plan.gy * a.plan.gz), a.cs, a.out, nullptr};
+  return {a.scratch, slots_of(a.plan.gx * a.plan.gy * a.plan.gz), a.looks, a.cs, a.out, nullptr};
 }
 
 void launch_resident_init(const ResidentInit &i, hipStream_t st) { resident_init_kernel<<<1, 256, 0, st>>>(i); }
