@@ -140,3 +140,35 @@ def test_per_thread_default_stream(ex):
     for t in ts:
         t.join()
     assert not bad
+
+
+# every brick kind, and strongly unequal meshsizes
+@pytest.mark.parametrize("n,nc,box", [
+    ((32, 32, 32), (8, 8, 8), (1.0, 1.0, 1.0)),
+    ((72, 40, 48), (18, 10, 12), (1.5, 0.8, 1.1)),
+    ((80, 64, 72), (20, 16, 18), (1.0, 0.8, 0.9)),
+    ((96, 96, 96), (12, 12, 12), (1.0, 1.0, 1.0)),
+    ((128, 96, 64), (16, 12, 8), (1.0, 0.3, 1.7)),
+    ((128, 128, 128), (16, 16, 16), (1.0, 1.0, 1.0)),
+])
+def test_true_residual_at_a_tight_tolerance(ex, n, nc, box):
+    """The stopping test sees the residual that the iteration updates; the true one is off from it by rounding, in this form
+    of CG by at most about twice as much as where M p is applied anew.  A two-pass solve to 1e-15 shows how much that is
+    (its true residual is that difference, and 1e-15)."""
+    import torch
+
+    f, g, _ = (dev(v) for v in synth.sample(synth.smooth(4, box), n))
+    b = ex.op_rhs(f, g, n, box)
+
+    def true(tol, **kw):
+        u, _, st = ex.Solver(n, box, tol, n_coarse=nc, **kw).solve(f, g)
+        for d in range(3):
+            u.select(d, 0).zero_()
+            u.select(d, n[2 - d]).zero_()
+        return float(torch.linalg.vector_norm(b - ex.op_apply(u, n, box)) / torch.linalg.vector_norm(b)), st["iters"]
+
+    r, it = true(1e-13)
+    r2, it2 = true(1e-13, two_pass_cg=True)
+    rounding = true(1e-15, two_pass_cg=True)[0]
+    assert r <= 1e-13 + 2 * rounding and r2 <= 1e-13 + 2 * rounding, (r, r2, rounding)
+    assert all(abs(a - c) <= 1 for a, c in zip(it, it2)), (it, it2)
