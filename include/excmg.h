@@ -171,9 +171,10 @@ int excmg_plan(const excmg_problem *p, int32_t *levels, int32_t n_coarse_out[3])
 int excmg_setup(const excmg_problem *p, void *workspace, size_t bytes, void *hip_stream, excmg_handle **h);
 
 /* Algorithm 1.  f: node array (every node is read); g: node array (only boundary nodes are read).
- * u (out): node array, the finest-grid solution with its boundary equal to g (its contents change during the call:
- * the relaxation keeps a work vector there; after an error other than EXCMG_ERR_NOCONV they are undefined, and so are
- * u_ext's).
+ * u (out): node array, the finest-grid solution with its boundary equal to g.  Where the finest grid runs iterations in
+ * pairs (see EXCMG_TWO_PASS_CG) the relaxation keeps a work vector there, so that u's contents (also where u is f or g)
+ * change during the call and are undefined after an EXCMG_ERR_BREAKDOWN.  Otherwise an error of the solve other than
+ * EXCMG_ERR_NOCONV leaves u as it was, and u_ext always.
  * u_ext (out, nullable): EXP_true(u_h, u_2h), the sixth-order extrapolated solution on the finest grid
  * (Algorithm 1, optional step; Sections 4.2.1 and 4.3); needs at least two grids.
  * stats (host, nullable). */
@@ -204,7 +205,7 @@ int excmg_gradient(excmg_handle *h, const double *u, double *ux, double *uy, dou
  * upstream gradient G = dL/du (node array).  Solves M lambda = G_I (M = -A_h restricted to the interior, the same
  * symmetric operator) by the same cascade with the level data taken from G, then
  *   dLdf = -R^T lambda on every node (R f = (6 f_c + sum of the 6 face neighbours)/2, eq. compact),
- *   dLdg = A_IB^T lambda + G on boundary nodes, 0 inside (dLdf or dLdg serves as a work vector during the call).
+ *   dLdg = A_IB^T lambda + G on boundary nodes, 0 inside (dLdf or dLdg may serve as a work vector, as u in excmg_solve).
  * lambda_out (nullable): lambda as a node array with zero boundary.  Uses the handle's tolerance and precision. */
 int excmg_adjoint(excmg_handle *h, const double *G, double *dLdf, double *dLdg, double *lambda_out,
                   excmg_stats *stats);

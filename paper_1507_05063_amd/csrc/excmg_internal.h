@@ -192,7 +192,8 @@ struct CgState {
   double cross, alast;   // r.r_before and alpha of the last iteration
   unsigned count;        // workgroups that have finished the current launch (0 between launches)
   int tune;              // the autotuner's trials: the scalars stay as they are
-  int looks, pad_;       // of the resident CG's launch before it gives up: 0 once an earlier one of the call has
+  int looks;             // of the resident CG's launch before it gives up: 0 once an earlier one of the call has
+  int failed;            // a grid whose outcome waits for the cascade's end ended in an error (no iteration cap)
   double hist[EXCMG_MAX_HISTORY];
 };
 
@@ -300,7 +301,17 @@ ResidentInit resident_init(const Resident &a);
 void launch_resident_init(const ResidentInit &i, hipStream_t st);
 void launch_resident(const Resident &a, hipStream_t st);
 // cs's outcome into out
-void launch_outcome(const CgState *cs, Outcome *out, hipStream_t st);
+void launch_outcome(CgState *cs, Outcome *out, hipStream_t st);
+// the outcome for the host
+__device__ __forceinline__ void set_outcome(CgState *cs, Outcome *out, double rho, double rho0, double bnorm2, int iter,
+                                            int status) {
+  out->rho = rho;
+  out->rho0 = rho0;
+  out->bnorm2 = bnorm2;
+  out->iter = iter;
+  out->status = status;
+  if (status == EXCMG_ERR_BREAKDOWN || !isfinite(bnorm2)) cs->failed = 1;
+}
 __device__ __forceinline__ void resident_init_block(const ResidentInit &i) {
   for (int q = threadIdx.x; q < i.n; q += blockDim.x) i.slots[q] = __longlong_as_double((long long)kMissingSlot);
   if (threadIdx.x != 0) return;
@@ -339,7 +350,7 @@ int selfred_max_blocks();
 void launch_selfred_init(CgState *cs, int max_iters, int hist_on, int preset, hipStream_t st);
 // cs->gbnd2 = the sum of g^2 over the boundary nodes of grid g (0 if rs.fg is 0 or rs.mode is 1); one workgroup
 void launch_boundary_g2(const RhsSrc &rs, const Grid &g, CgState *cs, hipStream_t st);
-// gbnd2, count and abort = 0 for each state (at setup, and after a give-up)
+// gbnd2, count, abort and failed = 0 for each state (at setup, and after a give-up or an error)
 void launch_clear_state(CgState *a, CgState *b, hipStream_t st);
 // residual sweep writing [r.r | b.b] partials without a finalize (for the self-finalizing iterations)
 void launch_residual_partials(const Sweep &sw, const double *u, const RhsSrc &rs, double *r, double *parts,
@@ -390,12 +401,18 @@ enum GuessKind { kGuessQuartic = 0, kGuessQuadratic = 1, kGuessLinear = 2 };
 void launch_initial_guess(int kind, const Grid &g2, const double *u2, const Grid &g4, const double *u4,
                           const Grid &gg, const double *g, int stride, const Grid &gw, double *w,
                           const ResidentInit &init, hipStream_t st);
+// Of the launches that follow a cascade, which the host queues before it has read the outcomes: where the time of the
+// launch's start goes, wall_clock64(), and the cascade's state: nothing is written where a grid of it failed or gave up
+// (both nullable).
+struct After {
+  long long *mark;
+  const CgState *cs;
+};
 // ut (grid gt) = EXP_true(uh (grid gh), u2 (grid g2))
 void launch_exp_true(const Grid &gh, const double *uh, const Grid &g2, const double *u2, const Grid &gt, double *ut,
-                     double *ucopy, long long *mark, hipStream_t st);
-// copy between layouts (same n).  Here and in the other launchers of what follows a cascade, mark (nullable): where the
-// time of the launch's start goes, wall_clock64()
-void launch_copy(const Grid &gs, const double *src, const Grid &gd, double *dst, long long *mark, hipStream_t st);
+                     double *ucopy, const After &after, hipStream_t st);
+// copy between layouts (same n)
+void launch_copy(const Grid &gs, const double *src, const Grid &gd, double *dst, const After &after, hipStream_t st);
 // count of non-finite values in a dense array -> *flag (device int, must be zeroed by the caller)
 void launch_check_finite(const double *a, long long n, int *flag, hipStream_t st);
 
@@ -510,6 +527,6 @@ void launch_gradient(const Grid &gu, const double *u, const Grid &gd, double *ux
 
 // adjoint transposes: dLdf = -R^T lam (all nodes); dLdg = A_IB^T lam + G (boundary), 0 inside
 void launch_adjoint_transposes(const Grid &gl, const double *lam, const Grid &gd, const double *G, double *dLdf,
-                               double *dLdg, double hx, double hy, double hz, long long *mark, hipStream_t st);
+                               double *dLdg, double hx, double hy, double hz, const After &after, hipStream_t st);
 
 }  // namespace excmg

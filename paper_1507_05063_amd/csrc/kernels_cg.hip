@@ -865,6 +865,8 @@ __global__ void clear_state_kernel(CgState *a, CgState *b) {
   b->count = 0;
   a->abort = 0;
   b->abort = 0;
+  a->failed = 0;
+  b->failed = 0;
 }
 
 // --------------------------------------------------------------------------------------------------------- finalize

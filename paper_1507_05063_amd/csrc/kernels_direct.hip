@@ -48,11 +48,7 @@ __device__ void direct_outcome(const Direct &a, double rho, double bb) {
   cs->status = (isfinite(rho) && isfinite(bnorm2)) ? 0 : EXCMG_ERR_BREAKDOWN;
   cs->done = 1;
   if (a.out) {
-    a.out->iter = 0;
-    a.out->rho = rho;
-    a.out->rho0 = rho;
-    a.out->bnorm2 = bnorm2;
-    a.out->status = cs->status;
+    set_outcome(cs, a.out, rho, rho, bnorm2, 0, cs->status);
     a.out->abort = 0;
   }
 }

@@ -52,12 +52,8 @@ __device__ __forceinline__ double uniform(double v) {
 
 __global__ void resident_init_kernel(ResidentInit i) { resident_init_block(i); }
 
-__global__ void outcome_kernel(const CgState *cs, Outcome *out) {
-  out->rho = cs->rho;
-  out->rho0 = cs->rho0;
-  out->bnorm2 = cs->bnorm2;
-  out->iter = cs->iter;
-  out->status = cs->status;
+__global__ void outcome_kernel(CgState *cs, Outcome *out) {
+  set_outcome(cs, out, cs->rho, cs->rho0, cs->bnorm2, cs->iter, cs->status);
   out->abort = 0;
 }
 
@@ -419,13 +415,7 @@ __device__ __forceinline__ void resident_cg(const Resident &a, double *u_, doubl
     cs->stop2 = stop2;
     cs->status = status;
     cs->done = 1;
-    if (a.out) {
-      a.out->rho = gamma;
-      a.out->rho0 = rho0;
-      a.out->bnorm2 = bb;
-      a.out->iter = k;
-      a.out->status = status;
-    }
+    if (a.out) set_outcome(cs, a.out, gamma, rho0, bb, k, status);
   }
 }
 
@@ -518,7 +508,7 @@ ResidentInit resident_init(const Resident &a) {
 
 void launch_resident_init(const ResidentInit &i, hipStream_t st) { resident_init_kernel<<<1, 256, 0, st>>>(i); }
 
-void launch_outcome(const CgState *cs, Outcome *out, hipStream_t st) { outcome_kernel<<<1, 1, 0, st>>>(cs, out); }
+void launch_outcome(CgState *cs, Outcome *out, hipStream_t st) { outcome_kernel<<<1, 1, 0, st>>>(cs, out); }
 
 void launch_resident(const Resident &a, hipStream_t st) {
   const ResidentPlan &p = a.plan;

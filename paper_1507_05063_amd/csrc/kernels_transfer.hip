@@ -17,9 +17,11 @@ __device__ __forceinline__ bool on_boundary(int i, int j, int k, int nx, int ny,
   return i == 0 || j == 0 || k == 0 || i == nx || j == ny || k == nz;
 }
 
-// the time of the launch's start
-__device__ __forceinline__ void set_mark(long long *mark) {
-  if (mark && threadIdx.x == 0 && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0) *mark = (long long)wall_clock64();
+// the time of the launch's start; whether there is anything to write
+__device__ __forceinline__ bool begin(const After &a) {
+  if (a.mark && threadIdx.x == 0 && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0)
+    *a.mark = (long long)wall_clock64();
+  return !a.cs || !(a.cs->failed | a.cs->abort);
 }
 
 // ------------------------------------------------------------------------------------------------------------ rhs
@@ -96,8 +98,8 @@ __device__ __forceinline__ void copy_block(const Grid &gs, const double *__restr
 }
 
 __global__ __launch_bounds__(256) void copy_kernel(Grid gs, const double *__restrict__ src, Grid gd,
-                                                   double *__restrict__ dst, long long *mark) {
-  set_mark(mark);
+                                                   double *__restrict__ dst, After after) {
+  if (!begin(after)) return;
   copy_block(gs, src, gd, dst, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
@@ -359,8 +361,8 @@ constexpr int DTX = TTX / 2 + 1, DTY = TTY / 2 + 1, DTZ = TTZ / 2 + 1;
 __global__ __launch_bounds__(TTX *TTY) void exp_true_kernel(Grid gh, const double *__restrict__ uh, Grid g2,
                                                            const double *__restrict__ u2, Grid gt,
                                                            double *__restrict__ ut, double *__restrict__ ucopy,
-                                                           long long *mark) {
-  set_mark(mark);
+                                                           After after) {
+  if (!begin(after)) return;
   __shared__ double D[DTZ][DTY][DTX];
   // blockIdx.x runs along y: consecutive workgroups (which the hardware deals out to the XCDs in turn) take
   // different rows, so all the blocks of one row segment run on one XCD and no cache line is written from two
@@ -421,7 +423,9 @@ __device__ __forceinline__ double lam_at(const Grid &g, const double *lam, int i
 
 // dLdf on every node, and dLdg = 0 inside
 __global__ __launch_bounds__(256) void adjoint_kernel(Grid gl, const double *__restrict__ lam, Grid gd,
-                                                      double *__restrict__ dLdf, double *__restrict__ dLdg) {
+                                                      double *__restrict__ dLdf, double *__restrict__ dLdg,
+                                                      After after) {
+  if (!begin(after)) return;
   const int i = blockIdx.x * 64 + (threadIdx.x & 63), j = blockIdx.y * 4 + (threadIdx.x >> 6), k0 = blockIdx.z * kRz;
   if (i > gl.nx || j > gl.ny) return;
   const int k1 = min(k0 + kRz, gl.nz + 1);
@@ -442,8 +446,8 @@ __global__ __launch_bounds__(256) void adjoint_kernel(Grid gl, const double *__r
 // dLdg on the boundary nodes; layers as in zero_boundary_kernel, every node in the first layer that holds it
 __global__ __launch_bounds__(256) void adjoint_boundary_kernel(Grid gl, const double *__restrict__ lam, Grid gd,
                                                                const double *G, double *dLdg, double a, double bb,
-                                                               double c, long long *mark) {
-  set_mark(mark);
+                                                               double c, After after) {
+  if (!begin(after)) return;
   const int layer = blockIdx.y;
   const int np = layer < 2 ? gl.ny : gl.nx, nq = layer < 4 ? gl.nz : gl.ny;
   const long long e = (long long)blockIdx.x * 256 + threadIdx.x;
@@ -551,13 +555,13 @@ void launch_initial_guess(int kind, const Grid &g2, const double *u2, const Grid
 }
 
 void launch_exp_true(const Grid &gh, const double *uh, const Grid &g2, const double *u2, const Grid &gt, double *ut,
-                     double *ucopy, long long *mark, hipStream_t st) {
+                     double *ucopy, const After &after, hipStream_t st) {
   dim3 grid((gh.ny + TTY - 1) / TTY, (gh.nx + TTX - 1) / TTX, (gh.nz + TTZ - 1) / TTZ);
-  exp_true_kernel<<<grid, TTX * TTY, 0, st>>>(gh, uh, g2, u2, gt, ut, ucopy, mark);
+  exp_true_kernel<<<grid, TTX * TTY, 0, st>>>(gh, uh, g2, u2, gt, ut, ucopy, after);
 }
 
-void launch_copy(const Grid &gs, const double *src, const Grid &gd, double *dst, long long *mark, hipStream_t st) {
-  copy_kernel<<<node_grid(gs, 256), 256, 0, st>>>(gs, src, gd, dst, mark);
+void launch_copy(const Grid &gs, const double *src, const Grid &gd, double *dst, const After &after, hipStream_t st) {
+  copy_kernel<<<node_grid(gs, 256), 256, 0, st>>>(gs, src, gd, dst, after);
 }
 
 void launch_check_finite(const double *a, long long n, int *flag, hipStream_t st) {
@@ -568,11 +572,11 @@ void launch_check_finite(const double *a, long long n, int *flag, hipStream_t st
 }
 
 void launch_adjoint_transposes(const Grid &gl, const double *lam, const Grid &gd, const double *G, double *dLdf,
-                               double *dLdg, double hx, double hy, double hz, long long *mark, hipStream_t st) {
+                               double *dLdg, double hx, double hy, double hz, const After &after, hipStream_t st) {
   // (the boundary first: it reads G, which dLdf or dLdg may lie over)
   adjoint_boundary_kernel<<<dim3(face_blocks(gl), 6), 256, 0, st>>>(gl, lam, gd, G, dLdg, 1.0 / (hx * hx),
-                                                                       1.0 / (hy * hy), 1.0 / (hz * hz), mark);
-  adjoint_kernel<<<dim3(gl.nx / 64 + 1, gl.ny / 4 + 1, gl.nz / kRz + 1), 256, 0, st>>>(gl, lam, gd, dLdf, dLdg);
+                                                                       1.0 / (hy * hy), 1.0 / (hz * hz), after);
+  adjoint_kernel<<<dim3(gl.nx / 64 + 1, gl.ny / 4 + 1, gl.nz / kRz + 1), 256, 0, st>>>(gl, lam, gd, dLdf, dLdg, {nullptr, after.cs});
 }
 
 int b_blocks_nodes(const Grid &g) { return ((g.nx + 1 + 255) / 256) * (g.ny + 1) * (g.nz + 1); }
