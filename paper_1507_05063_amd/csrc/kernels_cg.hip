@@ -25,6 +25,7 @@
 // stopping test) on the device.  Results are bitwise reproducible.
 #include <math.h>
 
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -794,11 +795,9 @@ __global__ __launch_bounds__(NT) void apply_kernel(Sweep sw, const double *x, Gr
 
 // A's couplings to the Dirichlet values, written at every interior node next to the boundary (the six layers
 // i = 1, i = nx-1, j = 1, ...; nodes on two layers are written twice with the same value).  blockIdx.z = layer.
-__device__ __forceinline__ void boundary_terms_block(const RhsSrc &rs, const Grid &g, double *out, int bx, int by,
-                                                     int layer) {
+__device__ __forceinline__ void boundary_terms_node(const RhsSrc &rs, const Grid &g, double *out, int a, int b,
+                                                    int layer) {
   // layer 0,1: x layers; 2,3: y layers; 4,5: z layers
-  const int a = 1 + bx * 256 + threadIdx.x;
-  const int b = 1 + by;
   int i, j, k;
   if (layer < 2) {
     if (a >= g.ny || b >= g.nz) return;
@@ -814,8 +813,9 @@ __device__ __forceinline__ void boundary_terms_block(const RhsSrc &rs, const Gri
 }
 
 __global__ __launch_bounds__(256) void boundary_terms_kernel(RhsSrc rs, Grid g, double *out) {
-  const int gx = (max(g.nx, max(g.ny, g.nz)) - 1 + 255) / 256;
-  boundary_terms_block(rs, g, out, blockIdx.x % gx, blockIdx.x / gx, blockIdx.y);
+  const int layer = blockIdx.y;
+  const unsigned na = (layer < 2 ? g.ny : g.nx) - 1, e = blockIdx.x * 256 + threadIdx.x;
+  boundary_terms_node(rs, g, out, 1 + e % na, 1 + e / na, layer);
 }
 
 // cs->gbnd2 = the sum of g^2 over the boundary nodes of grid g, the boundary half of the squared norm of the stopping
@@ -1286,7 +1286,7 @@ __global__ __launch_bounds__(256) void b_boundary_terms_kernel(BatchList L) {
   const int m = max(g.nx, max(g.ny, g.nz)) - 1;
   const int gx = (m + 255) / 256;
   const int lb = blockIdx.x - L.pre[e];
-  boundary_terms_block(E.rs, g, E.r, lb % gx, (lb / gx) % m, lb / (gx * m));
+  boundary_terms_node(E.rs, g, E.r, 1 + lb % gx * 256 + threadIdx.x, 1 + (lb / gx) % m, lb / (gx * m));
 }
 
 __global__ __launch_bounds__(NT) void b_residual_kernel(BatchList L) {
@@ -1495,9 +1495,10 @@ static void with_shape(const Sweep &sw, F &&f) {
 
 void launch_boundary_terms(const RhsSrc &rs, const Grid &g, double *out, hipStream_t st) {
   if (rs.mode != 0) return;
-  const int m = (g.nx > g.ny ? (g.nx > g.nz ? g.nx : g.nz) : (g.ny > g.nz ? g.ny : g.nz)) - 1;
-  dim3 grid((m + 255) / 256 * m, 6);
-  boundary_terms_kernel<<<grid, 256, 0, st>>>(rs, g, out);
+  // (the nodes of the largest face, not the longest axis squared: that takes 6 M workgroups for 16384 x 4 x 4 cells)
+  const long long x = g.nx - 1, y = g.ny - 1, z = g.nz - 1;
+  const long long m = std::max(x * y, std::max(x * z, y * z));
+  boundary_terms_kernel<<<dim3((unsigned)((m + 255) / 256), 6), 256, 0, st>>>(rs, g, out);
 }
 
 static void launch_resid(const Sweep &sw_in, const double *u, const RhsSrc &rs, double *r, double *parts,

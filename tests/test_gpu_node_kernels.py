@@ -49,3 +49,28 @@ def test_adjoint(ex, orc, n):
     ref = orc.adjoint(G, box, n, 1e-10)
     for a, k in [(lam, "lam"), (dLdf, "dLdf"), (dLdg, "dLdg")]:
         assert relmax(a.cpu().numpy(), ref[k]) <= 1e-12
+
+
+# one axis as long as a call may have it, on each axis (the other two as short as they come)
+@pytest.mark.parametrize("n", [(70000, 2, 3), (3, 65000, 2), (2, 3, 65000)])
+def test_rhs_long_axis(ex, orc, n):
+    test_rhs(ex, orc, n)
+
+
+def test_rhs_time_of_a_thin_grid(ex):
+    """Launches follow the faces, not the longest axis squared: as many nodes in a thin box take less than ten times the
+    time of a cube (with the latter, 50 times)."""
+    import time
+
+    import torch
+
+    took = []
+    for n in ((64, 64, 64), (16384, 4, 4)):
+        f = torch.ones((n[2] + 1, n[1] + 1, n[0] + 1), dtype=torch.float64, device="cuda")
+        times = []
+        for _ in range(20):
+            t = time.perf_counter()
+            ex.op_rhs(f, f, n, (1.0, 1.0, 1.0))
+            times.append(time.perf_counter() - t)
+        took.append(sorted(times)[10])
+    assert took[1] < 10 * took[0], took
