@@ -80,14 +80,15 @@ def test_solve(ex, oracle, n, nc, history):
 
 
 @gpu
+@pytest.mark.parametrize("looks", [0, 1 << 20])
 @pytest.mark.parametrize("n,nc", [((64, 48, 32), (16, 12, 8)), ((160, 112, 144), (20, 14, 18))])
-def test_outputs_over_inputs(ex, n, nc):
-    """The call that starts over reads its inputs again: u over f or g, and the adjoint's outputs over G."""
+def test_outputs_over_inputs(ex, n, nc, looks):
+    """u over f or g, and the adjoint's outputs over G: a call that starts over reads its inputs again."""
     import torch
 
     f, g, _ = synth.sample(synth.smooth(5, BOX), n)
     s = ex.Solver(n, BOX, 1e-10, n_coarse=nc)
-    s.set_wait_limit(0)
+    s.set_wait_limit(looks)
     want = s.solve(dev(f), dev(g))[0]
     for which in (0, 1):
         fg = [dev(f), dev(g)]
