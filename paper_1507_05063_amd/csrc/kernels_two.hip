@@ -323,62 +323,6 @@ struct PolU {
   }
 };
 
-// Sums of K values over the whole grid of a launch (or one problem's nb workgroups), in the workgroup that finishes
-// last: every workgroup writes its partials past the XCD's own L2 (agent-scope stores), waits for them and counts
-// itself in; the last one to do so reads all partials the same way and adds them in workgroup order.  Only the
-// values themselves are coherent; nothing else is fenced (an agent-scope fence writes back the XCD's L2).  This saves
-// the separate reduction launch.  True in every thread of the last workgroup, tot valid in thread 0; the count is
-// back at 0 then.
-template <int K, int NTB>
-__device__ __forceinline__ bool last_sums(double (&v)[K], double *parts, unsigned *count, int bid, int nb,
-                                          double (&tot)[K]) {
-  constexpr int NW = NTB / 64;
-  __shared__ double sh[K][NW];
-  __shared__ int last;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-#pragma unroll
-  for (int k = 0; k < K; ++k) {
-    const double x = wave_sum(v[k]);
-    if (lane == 0) sh[k][w] = x;
-  }
-  __syncthreads();
-  // lane k < K of the first wave adds the waves' sums of value k
-  auto waves = [&]() {
-    double x = 0.0;
-    if (lane < K) {
-#pragma unroll 1
-      for (int q = 0; q < NW; ++q) x += sh[lane][q];
-    }
-    return x;
-  };
-  if (threadIdx.x < 64) {
-    const double x = waves();
-    if (lane < K)
-      __hip_atomic_store(&parts[(long long)lane * nb + bid], x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    if (lane == 0)
-      last = __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)nb - 1;
-  }
-  __syncthreads();
-  if (!last) return false;
-#pragma unroll
-  for (int k = 0; k < K; ++k) {
-    double x = 0.0;
-    for (int q = threadIdx.x; q < nb; q += NTB)
-      x += __hip_atomic_load(&parts[(long long)k * nb + q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    x = wave_sum(x);
-    if (lane == 0) sh[k][w] = x;
-  }
-  __syncthreads();
-  if (threadIdx.x < 64) {
-    const double x = waves();
-#pragma unroll
-    for (int k = 0; k < K; ++k) tot[k] = __shfl(x, k, 64);
-    if (lane == 0) __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-  return true;
-}
-
 // After pass G: alpha, and the second iteration's beta0 and alpha1.  With r1 = r - alpha q and p1 = r1 + beta0 p,
 //   r1.r1 = r.r - 2 alpha r.q + alpha^2 q.q,
 //   p1.M p1 = r.Mr + alpha^2 q.t + beta0^2 p.q - 2 alpha r.t + 2 beta0 r.q - 2 alpha beta0 q.q,
