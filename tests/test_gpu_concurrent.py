@@ -94,25 +94,52 @@ def test_not_behind_other_streams_work(ex, per_thread):
     import torch
 
     n = (128, 128, 128)
-    slow = torch.cuda.ExternalStream(2) if per_thread else torch.cuda.Stream()
-    a, b = case(ex, n, 1, slow), case(ex, n, 2, torch.cuda.Stream())
-    want = [s.solve(f, g)[0].clone() for s, f, g in (a, b)]
-    out = [torch.empty_like(v) for v in want]
-    torch.cuda.synchronize()
     hip = ctypes.CDLL("libamdhip64.so")
-    wait = ctypes.CFUNCTYPE(None, ctypes.c_void_p)(lambda _: time.sleep(0.5))
-    took, started = {}, threading.Event()
+    pause = lambda seconds: ctypes.CFUNCTYPE(None, ctypes.c_void_p)(lambda _: time.sleep(seconds))
+    short, long = pause(0.05), pause(0.5)
+    slow = torch.cuda.ExternalStream(2) if per_thread else torch.cuda.Stream()
+    put = lambda fn: hip.hipLaunchHostFunc(ctypes.c_void_p(slow.cuda_stream), fn, None)
+    a = case(ex, n, 1, slow)
+    cells, got, took, ready = torch.zeros(64, device="cuda"), [], {}, [threading.Event(), threading.Event()]
+    want, out = [a[0].solve(*a[1:])[0].clone()], [torch.empty_like(a[1]), torch.empty_like(a[1])]
+    torch.cuda.synchronize()
 
     def first():
-        assert hip.hipLaunchHostFunc(ctypes.c_void_p(slow.cuda_stream), wait, None) == 0
+        # a stream whose hardware queue is not this one's too
+        for stream in [torch.cuda.Stream() for _ in range(16)]:
+            assert put(short) == 0
+            t = time.perf_counter()
+            with torch.cuda.stream(stream):
+                cells.add_(1.0)
+            stream.synchronize()
+            t = time.perf_counter() - t
+            hip.hipStreamSynchronize(ctypes.c_void_p(slow.cuda_stream))
+            if t < 0.02:
+                got.append(stream)
+                break
+        ready[0].set()
+        ready[1].wait(30)
+        if not got:
+            return
+        assert put(long) == 0
         t = time.perf_counter()
-        started.set()
+        ready[0].set()
         a[0].solve(a[1], a[2], u=out[0])
         took["a"] = time.perf_counter() - t
         assert torch.equal(out[0], want[0])
 
     def second():
-        started.wait()
+        ready[0].wait(30)
+        if not got:
+            ready[1].set()
+            return
+        b = case(ex, n, 2, got[0])
+        torch.cuda.synchronize()
+        want.append(b[0].solve(b[1], b[2])[0].clone())
+        torch.cuda.synchronize()
+        ready[0].clear()
+        ready[1].set()
+        ready[0].wait(30)
         time.sleep(0.1)
         t = time.perf_counter()
         b[0].solve(b[1], b[2], u=out[1])
@@ -120,4 +147,6 @@ def test_not_behind_other_streams_work(ex, per_thread):
         assert torch.equal(out[1], want[1])
 
     run([first, second])
+    if not got:
+        pytest.skip("no stream with another hardware queue")
     assert took["a"] > 0.3 and took["b"] < 0.1, took
