@@ -23,8 +23,10 @@
 // written their part of the solution and the outcome: only the give-up counts then.)  Until the host has seen it, later
 // launches of the same call end at their first meeting (CgState::looks), instead of waiting once more each.  (A
 // cooperative launch would keep launches apart too, but costs about 190 us on this runtime.)
-// Measured per iteration: 128^3 31 -> 11 us (operator and updates 4 us, meeting 3, publishing and the layer 4), 64^3
-// 11 -> 5.1 us, 32^3 10 -> 4.1 us, 16^3 (one workgroup before) 6.5 -> 2.7 us.
+// Measured per iteration (per-grid times of solves capped at 24 and at 4 iterations): 128^3 41 -> 11.5 us (operator and
+// updates 4 us, meeting 3, publishing and the layer 4), 64^3 12.3 -> 5.1 us, 32^3 16.8 -> 4.1 us, 16^3 5.0 -> 3.6 us.  A
+// launch spends another 113, 32, 26 and 38 us (kernel trace) before its first iteration: u's loads, the right-hand side
+// node by node, two operators and the first meeting.
 #include <math.h>
 
 #include "cg_device.h"
