@@ -16,7 +16,8 @@
  *     the device that was current at excmg_setup, unless a comment says "host".
  *   - Ownership: the caller owns every array and the workspace; the library allocates no device memory.  The handle
  *     owns only host-side state; excmg_destroy frees it.
- *   - Streams: all device work is enqueued on the stream given at setup.  Calls that report iteration counts wait
+ *   - Streams: all device work is enqueued on the stream given at setup (a call of another thread may record an event
+ *     there while this handle's call is in progress, see EXCMG_TWO_PASS_CG).  Calls that report iteration counts wait
  *     for their own work on that stream before returning; their outputs are complete when they return.
  *   - Errors: every int-returning call returns EXCMG_OK (0) or a negative EXCMG_ERR_* code; excmg_strerror names it.
  *     No exception crosses the ABI.  On EXCMG_ERR_NOCONV the outputs hold the last iterate and the stats are filled.
