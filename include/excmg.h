@@ -236,8 +236,8 @@ int excmg_solve_batched(excmg_handle *const *hs, int32_t count, const double *co
 /* Host only.  Batched solves run the CG iterations of each round as a graph: replayed from a cache on the batch's
  * first handle when a round has the launch shape of an earlier one (the same batch workspace and number of problems,
  * iteration counts and, per launch, numbers of problems and workgroups; which problems a launch covers is read from the
- * workspace when it runs), else captured and instantiated (1024 are kept, the least recently used dropped first; EXCMG_NO_GRAPHS on
- * that handle launches them directly).  replays, captures (host): the graphs replayed and captured on h so far. */
+ * workspace when it runs), else captured and instantiated (1024 are kept, the least recently used dropped first;
+ * EXCMG_NO_GRAPHS on that handle launches them directly).  replays, captures (host): the graphs replayed and captured on h so far. */
 int excmg_batch_graph_counts(const excmg_handle *h, int64_t *replays, int64_t *captures);
 
 /* Autotuner of excmg_solve_batched for a batch of handles (host call, device work on the stream of hs[0]; the same

@@ -693,6 +693,8 @@ int grid_cap(const excmg_handle *h, int l) {
 // FP64 CG on level l from the current u (Algorithm 1, the while loop; one iteration per pass; on grids 0 and 1 the
 // direct solve, to the relative residual kDsolveTol).
 
+void leave_turn(excmg_handle *h);
+
 int cg64(excmg_handle *h, int l, const RhsSrc &rs, bool finest, int *iters, double *relres, excmg_stats *st) {
   Level &lv = h->lo.lev[l];
   const hipStream_t s = h->stream;
@@ -721,6 +723,7 @@ int cg64(excmg_handle *h, int l, const RhsSrc &rs, bool finest, int *iters, doub
     if (e) return e;
     e = read_state(h, &hs, h->cs);
     if (e) return e;
+    leave_turn(h);
     if (hs.done) break;
     nb = next_batch(hs.rho, hs.rho0, hs.iter, hs.stop2, kSolveFirst, kSolveMax);
   }
@@ -762,6 +765,7 @@ int cg_ir(excmg_handle *h, int l, const RhsSrc &rs, bool finest, int *iters, int
     if (e) return e;
     e = read_state(h, &ho, h->cs);
     if (e) return e;
+    leave_turn(h);
     if (ho.done) {
       status = ho.status;
       break;
@@ -866,15 +870,15 @@ int plan_resident(excmg_handle *h) {
   return EXCMG_OK;
 }
 
-// Measured, solves of 32^3 / 64 x 48 x 32 / 128^3 cells from eight threads, us a solve: 153 / 374 / 1230 so, 382 / 510 /
-// 1120 where every launch waited for the call before it, 296 / 528 / 1410 as sweeps, which wait for nothing.
 // Per device, the calls in progress that have launched the resident CG, and how many workgroups of it each may have
 // running at once (the largest of its launches: a call's own follow one another).  Its workgroups wait for one another,
 // so all calls' together must have room on the CUs: a launch that would take more than are left runs after what as many of
 // the other calls have launched so far as would free enough, those first whose last launch is the oldest.  (So of the
 // launches that run at one time, the one launched last has counted all the others.)  Workgroups are dealt out to the
 // XCDs in turn and, there, to four shader engines, so a launch counts as its next multiple of 32.  A call leaves its
-// place when its work is done.
+// place at the first look at a swept grid, or when its work is done.
+// Measured, solves of 32^3 / 64 x 48 x 32 / 128^3 cells from eight threads, us a solve: 153 / 374 / 1230 so, 382 / 510 /
+// 1120 where every launch waited for the call before it, 296 / 528 / 1410 as sweeps, which wait for nothing.
 struct ResidentTurn {
   std::mutex mu;
   excmg_handle *first = nullptr;  // by the age of the last launch
@@ -959,15 +963,20 @@ int in_turn(excmg_handle *h, int wgs, F &&launch) {
   if (per_thread && hipEventRecord(h->turn_done, h->stream) != hipSuccess && !e) e = EXCMG_ERR_HIP;
   return e;
 }
+// Once the host has waited for h's stream: its resident launches are done.
+void leave_turn(excmg_handle *h) {
+  if (h->turn_wgs == 0) return;  // (set by the call's own thread only)
+  ResidentTurn &t = g_resident[h->device];
+  std::lock_guard<std::mutex> lock(t.mu);
+  t.leave(h);
+  h->turn_wgs = 0;
+}
 struct ResidentCall {
   excmg_handle *h;
   ~ResidentCall() {
-    if (h->turn_wgs == 0) return;  // (set by this thread only)
+    if (h->turn_wgs == 0) return;
     (void)hipStreamSynchronize(h->stream);
-    ResidentTurn &t = g_resident[h->device];
-    std::lock_guard<std::mutex> lock(t.mu);
-    t.leave(h);
-    h->turn_wgs = 0;
+    leave_turn(h);
   }
 };
 
@@ -1306,8 +1315,8 @@ void clear_stats(excmg_stats *st) {
 }
 
 // The cascade, once more without the resident CG if a workgroup of it gave up waiting for the others (which takes
-// another process or another long kernel holding CUs for about 0.3 s).  The handle's later calls do without it too: what held the CUs may
-// last, and every call would wait for it again.
+// another process or another long kernel holding CUs for about 0.3 s).  The handle's later calls do without it too: what
+// held the CUs may last, and every call would wait for it again.
 template <typename Finish>
 int run_cascade(excmg_handle *h, int mode, const double *f, const double *g, excmg_stats *st, LevelIters *li,
                 Finish &&finish) {
@@ -1818,6 +1827,7 @@ int batched_solve(excmg_handle *const *hs, int count, const double *const *f, co
     const int it = hl[kListI64].n || hl[kListI32].n ? (nb64 > nb32 ? nb64 : nb32) : 0;
     if ((e = batch_iterations(hs[0], it, nb64, nb32, dl[kListI64], dl[kListI32], stat))) return e;
     if ((e = last_error()) || (e = read_stat())) return e;
+    leave_turn(hs[0]);
     // move every problem on, and size the next round's iteration batches from the residual decay seen so far
     nb64 = nb32 = 1;
     bool any64 = false, any32 = false;

@@ -16,9 +16,9 @@
 // there is no counter, no fence (one writes back the whole L2) and one store-to-load latency.  All workgroups add the
 // partial sums in one order: the scalars, and so every decision, are the same bits everywhere.  A slot that has not
 // been written holds a NaN that no sum produces; slots rotate through three sets, and a workgroup clears its own slot
-// of the set after next once all have arrived.  There are no more workgroups than CUs and the host lets such launches run
-// at once only where they have room together, so all workgroups of a launch come to run; the wait is bounded nevertheless (another
-// process may hold CUs), and a workgroup that gives up says so in the CG state: the host then takes the grid up again
+// of the set after next once all have arrived.  There are no more workgroups than CUs and the host lets such launches
+// run at once only where they have room together, so all workgroups of a launch come to run; the wait is bounded
+// nevertheless (another process may hold CUs), and a workgroup that gives up says so in the CG state: the host then takes the grid up again
 // from its initial guess with the sweeps.  (Others may have got through the same meeting and, if it was the last, have
 // written their part of the solution and the outcome: only the give-up counts then.)  Until the host has seen it, later
 // launches of the same call end at their first meeting (CgState::looks), instead of waiting once more each.  (A
