@@ -877,7 +877,7 @@ int plan_resident(excmg_handle *h) {
 // launches that run at one time, the one launched last has counted all the others.)  Workgroups are dealt out to the
 // XCDs in turn and, there, to four shader engines, so a launch counts as its next multiple of 32.  A call leaves its
 // place at the first look at a swept grid, or when its work is done.
-// Measured, solves of 32^3 / 64 x 48 x 32 / 128^3 cells from eight threads, us a solve: 153 / 374 / 1230 so, 382 / 510 /
+// Measured, solves of 32^3 / 64 x 48 x 32 / 128^3 cells from eight threads, us a solve: 161 / 375 / 1200 so, 382 / 510 /
 // 1120 where every launch waited for the call before it, 296 / 528 / 1410 as sweeps, which wait for nothing.
 struct ResidentTurn {
   std::mutex mu;
